@@ -1,0 +1,77 @@
+"""The race kernels evaluate an entry's key in fp64 only where its fp32 bounds let it win: parity with the oracle (every key in
+fp64) where those bounds are at their limits - vocabularies around a round of the scan and rows that cannot be read in 16-byte
+words, weights beyond the range of fp32, residuals that cancel to rounding noise or vanish."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import sampler as oracle_sampler
+from tests.test_gpu_sampler import _run_gpu
+
+pytestmark = pytest.mark.gpu
+
+SIZES = [3, 1023, 4096, 16384, 16388, 65541, 70000]
+
+
+def _softmax(z):
+    e = np.exp(z - z.max(-1, keepdims=True))
+    return e / e.sum(-1, keepdims=True)
+
+
+@pytest.mark.parametrize("V", SIZES)
+@pytest.mark.parametrize("temperature,offset", [(1.0, 0.0), (0.02, 0.0), (0.7, 5000.0)])
+@pytest.mark.parametrize("draft_kind", ["loose", "noise", "zero", "one-hot"])
+def test_reject_races_at_the_limits_of_their_bounds(V, temperature, offset, draft_kind):
+    B, k = 4, 2
+    rng = np.random.default_rng(V)
+    logits = (rng.standard_normal((B, k + 1, V)) * 3 + offset).astype(np.float32)
+    p = _softmax(logits[:, :k].astype(np.float64) / temperature)
+    if draft_kind == "loose":
+        q = _softmax((logits[:, :k].astype(np.float64) + rng.standard_normal((B, k, V))) / temperature).astype(np.float32)
+    elif draft_kind == "zero":                      # q above p everywhere: the residual is identically zero
+        q = (3.0 * p + 1e-30).astype(np.float32)
+    else:
+        q = p.astype(np.float32)
+    draft = rng.integers(0, V, size=(B, k)).astype(np.int32)
+    draft[:, 0] = logits[:, 0].argmax(-1)
+    if draft_kind == "noise":                       # p - q is rounding noise except where the rejected draft sits
+        np.put_along_axis(q, draft[..., None], (2.5 * np.take_along_axis(p, draft[..., None], -1)).astype(np.float32), -1)
+    if draft_kind == "one-hot":
+        explicit = np.zeros_like(q)
+        np.put_along_axis(explicit, draft[..., None], 1.0, -1)
+        from paper_2604_26779_amd import binding as sv
+        dl, dd = torch.from_numpy(logits).cuda(), torch.from_numpy(draft).cuda()
+        n, out = torch.empty(B, dtype=torch.int32, device="cuda"), torch.empty((B, k + 1), dtype=torch.int32, device="cuda")
+        ws = torch.empty(sv.spec_sample_workspace_bytes(B, k), dtype=torch.uint8, device="cuda")
+        sv.spec_reject_sample(B, k, V, dl, None, dd, temperature, 77, 4, n, out, None, ws)
+        n_gpu, out_gpu = n.cpu().numpy(), out.cpu().numpy()
+        q = explicit
+    else:
+        n_gpu, out_gpu, _ = _run_gpu(logits, q, draft, temperature, 77, 4)
+    n_or, out_or = oracle_sampler.reject_sample(logits, q, draft, temperature, 77, 4)
+    assert np.array_equal(n_gpu, n_or) and np.array_equal(out_gpu, out_or)
+
+
+@pytest.mark.parametrize("V", SIZES)
+@pytest.mark.parametrize("temperature", [1.0, 0.02])
+@pytest.mark.parametrize("mapped", [False, True])
+def test_draft_draw_at_the_limits_of_its_bounds(V, temperature, mapped):
+    from paper_2604_26779_amd import binding as sv
+    B = 3
+    rng = np.random.default_rng(V + 1)
+    logits = (rng.standard_normal((B, V)) * 3).astype(np.float32)
+    token_map = np.arange(V, dtype=np.int32) * 2 + 1
+    width = 2 * V + 1 if mapped else V
+    dl = torch.from_numpy(logits).cuda()
+    tok, q = torch.empty(B, dtype=torch.int32, device="cuda"), torch.full((B, width), -1.0, device="cuda")
+    if mapped:
+        sv.spec_draft_sample_mapped(B, V, dl, V, temperature, 5, 2, 1, tok, 1, None, 1, q, width, torch.from_numpy(token_map).cuda(), width)
+        x_or, q_or = oracle_sampler.draft_sample_mapped(logits, token_map, width, temperature, 5, 2, 1)[:2]
+    else:
+        sv.spec_draft_sample(B, V, dl, V, temperature, 5, 2, 1, tok, 1, None, 1, q, V)
+        x_or, q_or = oracle_sampler.draft_sample(logits, temperature, 5, 2, 1)[:2]
+    x_or, q_or = (x_or, q_or) if np.ndim(x_or) == 1 else (q_or, x_or)
+    assert np.array_equal(tok.cpu().numpy(), x_or)
+    # q is an fp64 softmax rounded to fp32 on both sides: at most one unit apart (below the smallest normal number: flushed)
+    got = q.cpu().numpy()
+    assert np.all(np.abs(got - q_or) <= 2.0 ** -23 * q_or + 1.2e-38)
