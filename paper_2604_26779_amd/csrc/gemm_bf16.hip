@@ -23,21 +23,17 @@
 #include <type_traits>
 
 #include "common.h"
+#include "gemm_common.h"
 #include "operand.h"
 
 namespace specv {
 
-typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
-typedef __attribute__((__vector_size__(8 * sizeof(_Float16)))) _Float16 f16x8_t;
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
-typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-
-constexpr int GEMM_KS = 4;          // k-steps (of 16) per LDS slab
 constexpr int GEMM_WD = 4;          // slabs of weight fragments each wavefront keeps in flight
-constexpr int GEMM_KUNIT = GEMM_KS * GEMM_WD;
-constexpr int GEMM_XCDS = 8;        // accelerator dies, each with its own L2; workgroup i of a launch runs on die i % 8   // k-steps per split are a multiple of this
-constexpr int GEMM_THREADS = 256;
-constexpr int GEMM_EPI_PLAIN = 0, GEMM_EPI_SWIGLU = 1;
+constexpr int GEMM_KUNIT = GEMM_KS * GEMM_WD;       // k-steps per split are a multiple of this
+
+// from gemm_big.hip
+spec_status launch_gemm_big(const PackedW& W, const bf16_t* Xp, int M, int mb, int mb_pad, float* out, int ldo, int kps, bool swiglu,
+                            dim3 grid, hipStream_t s);
 
 size_t bf16_packed_elems(int N, int K) { return (size_t)cdiv(N, 32) * 32 * (size_t)K; }
 
@@ -192,9 +188,6 @@ spec_status w8_pack_matrix(const unsigned char* const* dev_parts, const float* c
 }
 
 // ------------------------------------------------------------------ the GEMM
-// s_waitcnt operand: at most n vector-memory operations outstanding, the other counters not waited for
-constexpr int vmcnt_imm(int n) { return (n & 15) | 0x70 | 0xF00 | ((n >> 4) << 14); }
-
 // Wp : [k_steps / KS][n_blocks][KS][64] u32x4_t   Xp : [k_steps][mb_pad][hi|lo][64] u32x4_t
 // out: [splits][M][ldo] fp32 (slice stride = split_stride floats)
 // MB row blocks (of 32) per workgroup tile; the 4 wavefronts are arranged WM along the rows x 4/WM
@@ -204,10 +197,7 @@ constexpr int vmcnt_imm(int n) { return (n & 15) | 0x70 | 0xF00 | ((n >> 4) << 1
 // GROUPED (mixture of experts): blockIdx.z walks a device-side list of row tiles, tiles[0] = number of
 // tiles, then (group, first row block) pairs; group g multiplies by the matrix at Wp + g * w_group_stride
 // (all groups have the same shape).  Tiles past the list's end exit at once.
-// Large row counts (MB = 6 or 8: 192 or 256 rows per tile) take NBW_T = 4 column blocks per wavefront, i.e. a 256-column
-// tile: a wavefront then owns 3-4 x 4 accumulator blocks (192-256 accumulation registers, one workgroup per CU) and
-// every fragment it fetches feeds 4 (weights: 6-8) MFMAs, which halves the LDS and vector-memory traffic per MFMA
-// that bounds the 128 x 128 tile.  Its two LDS slabs (96-128 KiB) are dynamic shared memory.
+// (Large row counts take the 192- and 256-row x 256-column tiles of gemm_big.hip.)
 // W8: the weights are E4M3 codes, two k-steps per 16-byte word (half the weight bytes and load instructions); a
 // fragment is widened to bf16 in registers right before its MFMAs (exact) and the output column's scale is applied to
 // the accumulators in the epilogue.
@@ -215,7 +205,7 @@ constexpr int vmcnt_imm(int n) { return (n & 15) | 0x70 | 0xF00 | ((n >> 4) << 1
 // weight fragment and row block; XF_F16 = one fp16 value against fp16 weights, one MFMA.  The fused SwiGLU epilogue
 // writes its output in the same format (gate/up and down projection take the same one).
 template <int MB, int WM, int WD, int EPI, bool GROUPED = false, int NBW_T = WM, bool W8 = false, int XF = XF_HILO>
-__global__ __launch_bounds__(GEMM_THREADS, (MB >= 6 || (MB >= 3 && WM == 1 && NBW_T == 2)) ? 1 : 2) void gemm_bf16_kernel(
+__global__ __launch_bounds__(GEMM_THREADS, (MB >= 3 && WM == 1 && NBW_T == 2) ? 1 : 2) void gemm_bf16_kernel(
     const u32x4_t* __restrict__ Wp, const u32x4_t* __restrict__ Xp, float* __restrict__ out, int n_blocks, int k_steps,
     int ksteps_per_split, int mb_pad, int M, int N, int ldo, int64_t split_stride,
     const int32_t* __restrict__ tiles = nullptr, int64_t w_group_stride = 0, const float* __restrict__ wscale = nullptr)
@@ -224,33 +214,23 @@ __global__ __launch_bounds__(GEMM_THREADS, (MB >= 6 || (MB >= 3 && WM == 1 && NB
     constexpr int KSW = W8 ? KS / 2 : KS;               // 16-byte words of one column block per lane and slab
     constexpr int MBW = MB / WM, NBW = NBW_T;
     constexpr int TILE_NB = (4 / WM) * NBW;             // 32-column blocks per workgroup tile
-    constexpr bool BIG = MB >= 6;
     static_assert(MB % WM == 0, "row blocks must divide over the wavefronts");
     constexpr int SLAB = KS * MB * 64 * XF;             // u32x4_t per slab (XF operand words per lane and k-step)
     constexpr int XPT = SLAB / GEMM_THREADS;            // u32x4_t per thread per slab
     static_assert(SLAB % GEMM_THREADS == 0, "a slab must divide over the threads");
     // the fused SwiGLU epilogue re-uses the slabs as an fp32 transpose tile, which may be the larger of the two
-    constexpr int EPI_WORDS = EPI != GEMM_EPI_SWIGLU ? 0 : (BIG ? (MB / WM) * 32 * 129 : WM == 1 ? 32 * 129 : MB * 32 * 65) / 4 + 1;
+    constexpr int EPI_WORDS = EPI != GEMM_EPI_SWIGLU ? 0 : (WM == 1 ? 32 * 129 : MB * 32 * 65) / 4 + 1;
     constexpr int LDS_WORDS = 2 * SLAB > EPI_WORDS ? 2 * SLAB : EPI_WORDS;
-    extern __shared__ u32x4_t lds_dyn[];
-    __shared__ u32x4_t lds_static[BIG ? 1 : LDS_WORDS];
-    u32x4_t* const lds = BIG ? lds_dyn : lds_static;
+    __shared__ u32x4_t lds[LDS_WORDS];
 
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int mh = wave % WM, np = wave / WM;
-    // Which tile this workgroup computes.  Workgroups go to the 8 XCDs (each with an L2 of its own) round robin in
-    // launch order, so the launch index is re-mapped: XCD j takes a contiguous stretch of the tiles in the order
-    // (row tile fastest, then column tile, then k-split).  The workgroups that share a weight tile then share an L2,
-    // and an XCD reads the activations of one or two k-splits instead of all of them.
     int bx = blockIdx.x, by = blockIdx.y, bz = blockIdx.z;
     if constexpr (!GROUPED) {
-        const int nx = gridDim.x, ny = gridDim.y, nz = gridDim.z;
-        const int total = nx * ny * nz, lin = bx + nx * (by + ny * bz);
-        const int xcd = lin % GEMM_XCDS, slot = lin / GEMM_XCDS;
-        const int v = xcd * (total / GEMM_XCDS) + (xcd < total % GEMM_XCDS ? xcd : total % GEMM_XCDS) + slot;
-        bz = v % nz;
-        bx = (v / nz) % nx;
-        by = v / (nz * nx);
+        const GemmTile tile_of = gemm_tile_of_workgroup();
+        bx = tile_of.bx;
+        by = tile_of.by;
+        bz = tile_of.bz;
     }
     const int nb0 = bx * TILE_NB + np * NBW;
     const int ks0 = by * ksteps_per_split;
@@ -286,24 +266,11 @@ __global__ __launch_bounds__(GEMM_THREADS, (MB >= 6 || (MB >= 3 && WM == 1 && NB
 
     // the weight stream runs WD slabs ahead of the MFMAs: a register ring, each entry refilled
     // right after its last use
-    u32x4_t w[WD][KSW][NBW], xr[XPT];
+    u32x4_t w[WD][KSW][NBW];
 
-    auto load_x = [&](int slab) {
-#pragma unroll
-        for (int j = 0; j < XPT; ++j) {
-            int idx = threadIdx.x + GEMM_THREADS * j;
-            int kl = idx / (MB * 64 * XF), rem = idx % (MB * 64 * XF);
-            xr[j] = xbase[((int64_t)(slab * KS + kl) * mb_pad) * (64 * XF) + rem];
-        }
-    };
-    auto store_x = [&](int buf) {
-#pragma unroll
-        for (int j = 0; j < XPT; ++j) lds[buf * SLAB + threadIdx.x + GEMM_THREADS * j] = xr[j];
-    };
-    // The 128-column tiles skip the registers: their activation slabs go from global memory straight into LDS
-    // (global_load ... lds: no staging registers, no LDS store instructions).  Each instruction moves 64 x 16 bytes:
-    // per-lane global addresses, LDS address = the wavefront-uniform base given here + 16 * lane.  (The 256-column
-    // tile measured slightly faster with its stores spread under the MFMAs, and keeps them.)
+    // The activation slabs go from global memory straight into LDS (global_load ... lds: no staging registers, no LDS store
+    // instructions).  Each instruction moves 64 x 16 bytes: per-lane global addresses, LDS address = the wavefront-uniform
+    // base given here + 16 * lane.
     auto stage_x = [&](int slab, int tobuf) {
 #pragma unroll
         for (int j = 0; j < XPT; ++j) {
@@ -325,7 +292,7 @@ __global__ __launch_bounds__(GEMM_THREADS, (MB >= 6 || (MB >= 3 && WM == 1 && NB
         const int s_w = s + WD < n_slabs ? s + WD : n_slabs - 1;
         const int s_x = s + 1 < n_slabs ? s + 1 : n_slabs - 1;
         // the next slab's activations are the oldest loads of this slab: what is waited for at its end
-        if constexpr (BIG) load_x(s_x); else stage_x(s_x, buf ^ 1);
+        stage_x(s_x, buf ^ 1);
         // keep these loads HERE: left alone, the scheduler sinks them to the end of the slab, next to the LDS
         // stores that consume them, and the whole round trip to L2 is then paid once per slab
         __builtin_amdgcn_sched_barrier(0);
@@ -343,31 +310,12 @@ __global__ __launch_bounds__(GEMM_THREADS, (MB >= 6 || (MB >= 3 && WM == 1 && NB
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk) {
             if (kk + 1 < KS) read_a((kk + 1) & 1, kk + 1);
-            if constexpr (BIG) {
-                // a slab of the 256-row tile lasts longer than the trip to L2: the next slab's activations go to LDS
-                // under the MFMAs of the last two k-steps instead of after them
-                if (kk >= KS - 2) {
-#pragma unroll
-                    for (int j = (kk - (KS - 2)) * (XPT / 2); j < (kk - (KS - 2) + 1) * (XPT / 2); ++j)
-                        lds[(buf ^ 1) * SLAB + threadIdx.x + GEMM_THREADS * j] = xr[j];
-                }
-            }
             __builtin_amdgcn_sched_barrier(0);
             u32x4_t wk[NBW];                             // this k-step's weight fragments in the activations' 16-bit type
 #pragma unroll
             for (int j = 0; j < NBW; ++j) {
-                if constexpr (W8 && XF == XF_F16) {
-                    const unsigned int wa = w[SLOT][kk >> 1][j][(kk & 1) * 2], wb = w[SLOT][kk >> 1][j][(kk & 1) * 2 + 1];
-                    wk[j] = u32x4_t{__builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(wa, 1.0f, false)),
-                                    __builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(wa, 1.0f, true)),
-                                    __builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(wb, 1.0f, false)),
-                                    __builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(wb, 1.0f, true))};
-                } else if constexpr (W8) {
-                    const unsigned int wa = w[SLOT][kk >> 1][j][(kk & 1) * 2], wb = w[SLOT][kk >> 1][j][(kk & 1) * 2 + 1];
-                    wk[j] = u32x4_t{__builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(wa, 1.0f, false)),
-                                    __builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(wa, 1.0f, true)),
-                                    __builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(wb, 1.0f, false)),
-                                    __builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(wb, 1.0f, true))};
+                if constexpr (W8) {
+                    wk[j] = widen_e4m3x8<XF == XF_F16>(w[SLOT][kk >> 1][j][(kk & 1) * 2], w[SLOT][kk >> 1][j][(kk & 1) * 2 + 1]);
                 } else {
                     wk[j] = w[SLOT][kk][j];
                 }
@@ -396,15 +344,11 @@ __global__ __launch_bounds__(GEMM_THREADS, (MB >= 6 || (MB >= 3 && WM == 1 && NB
         // ... and the weight loads of this slab stay above the LDS stores, so that waiting for the (older)
         // activation loads does not drain the weight stream
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (BIG) {
-            __syncthreads();
-        } else {
-            // Wait for the transfers into LDS only: the slab's own weight reloads (KSW * NBW of them) were issued later
-            // and stay in flight (__syncthreads would drain the whole queue).  No wavefront reads the other buffer
-            // before this barrier, and all have finished reading this one when they pass the next.
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm(KSW * NBW));
-            __builtin_amdgcn_s_barrier();
-        }
+        // Wait for the transfers into LDS only: the slab's own weight reloads (KSW * NBW of them) were issued later
+        // and stay in flight (__syncthreads would drain the whole queue).  No wavefront reads the other buffer
+        // before this barrier, and all have finished reading this one when they pass the next.
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(KSW * NBW));
+        __builtin_amdgcn_s_barrier();
         buf ^= 1;
     };
 
@@ -426,15 +370,9 @@ __global__ __launch_bounds__(GEMM_THREADS, (MB >= 6 || (MB >= 3 && WM == 1 && NB
 #pragma unroll
                 for (int j = 0; j < NBW; ++j) w[d][i][j] = __builtin_nontemporal_load(wptr[j] + (int64_t)sd * wslab + i * 64);
         }
-        if constexpr (BIG) {
-            load_x(0);
-            store_x(0);
-            __syncthreads();
-        } else {
-            stage_x(0, 0);
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-            __builtin_amdgcn_s_barrier();
-        }
+        stage_x(0, 0);
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+        __builtin_amdgcn_s_barrier();
         if constexpr (W8) {
 #pragma unroll
             for (int j = 0; j < NBW; ++j) asm volatile("" : "+v"(wsc[j]));
@@ -447,44 +385,7 @@ __global__ __launch_bounds__(GEMM_THREADS, (MB >= 6 || (MB >= 3 && WM == 1 && NB
         }
     }
 
-    if constexpr (EPI == GEMM_EPI_SWIGLU && BIG) {
-        // 256-column tile: a wavefront's four accumulator columns are (gate, up) of two groups of 32 hidden channels.
-        // Same transpose through LDS as below, one half of the rows (the wavefronts with the same mh) at a time.
-        static_assert(!BIG || NBW == 4, "the 256-column tile has four column blocks per wavefront");
-        float* tile = (float*)lds;                              // [MBW*32 rows][129]
-        uint4* xo = (uint4*)out;
-#pragma unroll
-        for (int half = 0; half < WM; ++half) {
-            __syncthreads();
-            if (mh == half) {
-#pragma unroll
-                for (int i = 0; i < MBW; ++i)
-#pragma unroll
-                    for (int cg = 0; cg < 2; ++cg)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) {
-                            float g = acc[i][2 * cg][r], u = acc[i][2 * cg + 1][r];
-                            if constexpr (W8) {
-                                g *= wsc[2 * cg];
-                                u *= wsc[2 * cg + 1];
-                            }
-                            int row = i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                            tile[row * 129 + (np * 2 + cg) * 32 + (lane & 31)] = g / (1.0f + __expf(-g)) * u;
-                        }
-            }
-            __syncthreads();
-            for (int e = threadIdx.x; e < MBW * 32 * 16; e += GEMM_THREADS) {
-                int row = e >> 4, g8 = e & 15;
-                int m = (mblk0 + half * MBW) * 32 + row, f = bx * 128 + g8 * 8;
-                if (m >= M || f >= N / 2) continue;
-                float v[8];
-#pragma unroll
-                for (int j = 0; j < 8; ++j) v[j] = tile[row * 129 + g8 * 8 + j];
-                xp_store8_t<XF>(xo, m, f, mb_pad, v);
-            }
-        }
-        return;
-    } else if constexpr (EPI == GEMM_EPI_SWIGLU && WM == 1 && NBW == 1) {
+    if constexpr (EPI == GEMM_EPI_SWIGLU && WM == 1 && NBW == 1) {
         // 128-column tile of the 1 x 4 arrangement with one column block per wavefront: wavefronts 0 and 2 hold the gates,
         // 1 and 3 the ups of 2 x 32 hidden channels.  The raw accumulators go through LDS one row block at a time, and
         // silu(gate) * up is formed on the way out.
@@ -708,20 +609,6 @@ spec_status launch_gemm_bf16(const PackedW& W, const bf16_t* Xp, int M, float* o
         else { if (W.f16) CALL(__VA_ARGS__, false, XF_F16); else CALL(__VA_ARGS__, false, XF_HILO); } } while (0)
 #define SPEC_GEMM_LAUNCH_96(E) SPEC_GEMM_BY_TYPE(SPEC_GEMM_LAUNCH_96W, E)
 #define SPEC_GEMM_LAUNCH(MBV, WMV, WDV, E) SPEC_GEMM_BY_TYPE(SPEC_GEMM_LAUNCH_W, MBV, WMV, WDV, E)
-    // the 256-column tile: two LDS slabs of MB * 8 KiB as dynamic shared memory (beyond the 64 KiB a kernel gets by default)
-#define SPEC_GEMM_LAUNCH_BIG_W(MBV, E, W8V, XFV) do { \
-        auto kern = gemm_bf16_kernel<MBV, 2, 1, E, false, 4, W8V, XFV>; \
-        constexpr int slab_bytes = 2 * GEMM_KS * MBV * 64 * XFV * 16, epi_bytes = E == GEMM_EPI_SWIGLU ? (MBV / 2) * 32 * 129 * 4 + 16 : 0; \
-        constexpr int lds_bytes = slab_bytes > epi_bytes ? slab_bytes : epi_bytes; \
-        static bool raised = false; \
-        if (!raised) { \
-            hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes); \
-            if (e != hipSuccess) { set_error("gemm: cannot reserve %d bytes of LDS: %s", lds_bytes, hipGetErrorString(e)); return SPEC_EHIP; } \
-            raised = true; \
-        } \
-        kern<<<grid, GEMM_THREADS, lds_bytes, s>>>(wp, xp, out, W.n_blocks, W.k_steps, kps, mb_pad, M, W.N, ldo, stride, nullptr, 0, W.scale); \
-    } while (0)
-#define SPEC_GEMM_LAUNCH_BIG(MBV, E) SPEC_GEMM_BY_TYPE(SPEC_GEMM_LAUNCH_BIG_W, MBV, E)
     switch (mb) {
         case 1: SPEC_GEMM_LAUNCH(1, 1, GEMM_WD, GEMM_EPI_PLAIN); break;
         case 2:
@@ -735,8 +622,7 @@ spec_status launch_gemm_bf16(const PackedW& W, const bf16_t* Xp, int M, float* o
             else if (g.wide) SPEC_GEMM_LAUNCH_96(GEMM_EPI_PLAIN);
             else SPEC_GEMM_LAUNCH(3, 1, GEMM_WD, GEMM_EPI_PLAIN);
             break;
-        case 6: if (swiglu) SPEC_GEMM_LAUNCH_BIG(6, GEMM_EPI_SWIGLU); else SPEC_GEMM_LAUNCH_BIG(6, GEMM_EPI_PLAIN); break;
-        case 8: if (swiglu) SPEC_GEMM_LAUNCH_BIG(8, GEMM_EPI_SWIGLU); else SPEC_GEMM_LAUNCH_BIG(8, GEMM_EPI_PLAIN); break;
+        case 6: case 8: return launch_gemm_big(W, Xp, M, mb, mb_pad, out, ldo, kps, swiglu, grid, s);
         default:
             if (g.one_block) {                               // fp16 activations only
                 if (W.w8) { if (swiglu) SPEC_GEMM_LAUNCH_1BW(GEMM_EPI_SWIGLU, true, XF_F16); else SPEC_GEMM_LAUNCH_1BW(GEMM_EPI_PLAIN, true, XF_F16); }
@@ -748,12 +634,10 @@ spec_status launch_gemm_bf16(const PackedW& W, const bf16_t* Xp, int M, float* o
             else SPEC_GEMM_LAUNCH(4, 2, 2, GEMM_EPI_PLAIN);
             break;
     }
-#undef SPEC_GEMM_LAUNCH_BIG
 #undef SPEC_GEMM_BY_TYPE
 #undef SPEC_GEMM_LAUNCH_96
 #undef SPEC_GEMM_LAUNCH_96W
 #undef SPEC_GEMM_LAUNCH_1BW
-#undef SPEC_GEMM_LAUNCH_BIG_W
 #undef SPEC_GEMM_LAUNCH
 #undef SPEC_GEMM_LAUNCH_W
     SPEC_LAUNCH_CHECK("gemm_bf16_kernel");

@@ -1,0 +1,51 @@
+// What the GEMM kernels share: operand vector types, the K slab of the tiled weights, and the order of the tiles over the dies.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+namespace specv {
+
+typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
+typedef __attribute__((__vector_size__(8 * sizeof(_Float16)))) _Float16 f16x8_t;
+typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
+typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2v_t __attribute__((ext_vector_type(2)));
+
+constexpr int GEMM_KS = 4;          // k-steps (of 16) per slab of the tiled weights
+constexpr int GEMM_XCDS = 8;        // accelerator dies, each with its own L2; workgroup i of a launch runs on die i % 8
+constexpr int GEMM_THREADS = 256;
+constexpr int GEMM_EPI_PLAIN = 0, GEMM_EPI_SWIGLU = 1;
+
+// s_waitcnt operand: at most n vector-memory operations outstanding, the other counters not waited for
+constexpr int vmcnt_imm(int n) { return (n & 15) | 0x70 | 0xF00 | ((n >> 4) << 14); }
+
+// eight E4M3 codes (two words) -> eight fp16 or bf16, exact
+template <bool F16>
+__device__ inline u32x4_t widen_e4m3x8(unsigned int wa, unsigned int wb)
+{
+    if constexpr (F16)
+        return u32x4_t{__builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(wa, 1.0f, false)),
+                       __builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(wa, 1.0f, true)),
+                       __builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(wb, 1.0f, false)),
+                       __builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(wb, 1.0f, true))};
+    else
+        return u32x4_t{__builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(wa, 1.0f, false)),
+                       __builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(wa, 1.0f, true)),
+                       __builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(wb, 1.0f, false)),
+                       __builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(wb, 1.0f, true))};
+}
+
+// Which tile a workgroup computes.  Workgroups go to the dies round robin in launch order, so the launch index is re-mapped:
+// die j takes a contiguous stretch of the tiles in the order (row tile fastest, then column tile, then k-split).  The workgroups
+// that share a weight tile then share an L2, and a die reads the activations of one or two k-splits instead of all of them.
+struct GemmTile { int bx, by, bz; };       // column tile, k-split, row tile
+__device__ inline GemmTile gemm_tile_of_workgroup()
+{
+    const int nx = gridDim.x, ny = gridDim.y, nz = gridDim.z;
+    const int total = nx * ny * nz, lin = blockIdx.x + nx * (blockIdx.y + ny * blockIdx.z);
+    const int xcd = lin % GEMM_XCDS, slot = lin / GEMM_XCDS;
+    const int v = xcd * (total / GEMM_XCDS) + (xcd < total % GEMM_XCDS ? xcd : total % GEMM_XCDS) + slot;
+    return GemmTile{(v / nz) % nx, v / (nz * nx), v % nz};
+}
+
+}  // namespace specv

@@ -209,6 +209,29 @@ def test_w8_large_row_tiles(B, k, big_from):
     assert ok, (max_err, worst)
 
 
+@pytest.mark.parametrize("w8", [False, True])
+@pytest.mark.parametrize("f16_inputs", [12, 0])
+@pytest.mark.parametrize("B,k", [(64, 3), (33, 7)])
+def test_large_row_tiles_shortest_k_splits(B, k, f16_inputs, w8):
+    """The ring of LDS slabs of the 256- and 192-row tiles (M = 256 and 264) at its shortest: 8 k-steps per K split, as many as
+    the ring holds or one more, in every operand format and both weight types; column counts that are no multiple of 256."""
+    from paper_2604_26779_amd import binding as sv
+    want = {"gemm_big_min_blocks": 8, "gemm_big_min_tiles": 1, "gemm_min_ksteps": 8, "splits_qkv": 64, "splits_o": 64, "splits_down": 64,
+            "gemm_f16_inputs": f16_inputs}
+    before = {n: sv.spec_tune_get(n) for n in want}
+    try:
+        for n, v in want.items():
+            sv.spec_tune_set(n, v)
+        rng = np.random.default_rng(B * 10 + k)
+        ctx = [int(c) for c in rng.integers(3, 120, size=B)]
+        ok, max_err, worst = _run_custom_bf16(ctx, k=k, seed=B + k, vocab=1000, **(W8 if w8 else {}))
+    finally:
+        for n, v in before.items():
+            sv.spec_tune_set(n, v)
+    print("B=%d k=%d, fp16 inputs %d, 8-bit matrices %s: logits max abs err %.3e" % (B, k, f16_inputs, w8, max_err))
+    assert ok, (max_err, worst)
+
+
 def test_w8_description_checks():
     """8-bit matrices are refused where the kernels have no path for them, with an error and nothing launched."""
     from paper_2604_26779_amd import binding as sv
