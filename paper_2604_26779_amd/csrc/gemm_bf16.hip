@@ -387,7 +387,7 @@ __global__ __launch_bounds__(GEMM_THREADS, (MB >= 3 && WM == 1 && NBW_T == 2) ? 
 
     if constexpr (EPI == GEMM_EPI_SWIGLU && WM == 1 && NBW == 1) {
         // 128-column tile of the 1 x 4 arrangement with one column block per wavefront: wavefronts 0 and 2 hold the gates,
-        // 1 and 3 the ups of 2 x 32 hidden channels.  The raw accumulators go through LDS one row block at a time, and
+        // 1 and 3 the ups of 2 x 32 hidden channels (the column blocks of a pair are both inside the matrix or both outside).  The raw accumulators go through LDS one row block at a time, and
         // silu(gate) * up is formed on the way out.
         float* tile = (float*)lds;                              // [32 rows][129]
         uint4* xo = (uint4*)out;
@@ -408,7 +408,7 @@ __global__ __launch_bounds__(GEMM_THREADS, (MB >= 3 && WM == 1 && NBW_T == 2) ? 
                     const float* src = tile + row * 129 + (g8 >> 2) * 64 + (g8 & 3) * 8;
                     float v[8];
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) { const float g = src[j], u = src[32 + j]; v[j] = g / (1.0f + __expf(-g)) * u; }
+                    for (int j = 0; j < 8; ++j) { const float g = src[j], u = src[32 + j]; v[j] = g / (1.0f + (MB % 2 ? expf(-g) : __expf(-g))) * u; }
                     xp_store8_t<XF>(xo, m, f, mb_pad, v);
                 }
             }
@@ -558,7 +558,10 @@ static GemmShape gemm_shape(const PackedW& W, int M, bool fused_swiglu)
     // (the pair of 64-row tiles fetches each twice: the second time as an L2 hit, but through the same L1 and memory
     // pipeline as the weight stream), at the price of one LDS read per MFMA, which the single fp16 MFMA per fragment leaves room for:
     // gate/up 56 -> 50 us, down 31 -> 26 us at the 8B shape.  With hi + lo operands the pair stays ahead.
-    if (g.mb == 4 && g.m_tiles == 1 && W.f16 && tune("gemm_one_block") != 0 && W.n_blocks % 4 == 0) {
+    // 33..64 rows: the same arrangement instead of 2 x 2, in either format (at 64 rows of the 8B shape gate/up 56.3 -> 42.1 us,
+    // down 29.0 -> 24.6, QKV and output projection 16.3 -> 14.7 on average): the activation slab is half as large and the second
+    // fetch of every weight fragment was what the 2 x 2 arrangement waited for.
+    if ((g.mb == 2 || (g.mb == 4 && W.f16)) && g.m_tiles == 1 && tune("gemm_one_block") != 0 && W.n_blocks % 4 == 0) {
         g.one_block = true; g.tile_nb = 4; g.n_tiles = W.n_blocks / 4; g.kunit = GEMM_KS * 2;
         return g;
     }
@@ -588,7 +591,16 @@ int gemm_pick_splits(const PackedW& W, int M, int forced)
 // out must hold splits * M * ldo floats; with swiglu (gate/up projection, splits == 1, an even number
 // of row blocks) out is instead the hi + lo operand buffer of silu(gate) * up, [N/2] channels wide.
 // Returns SPEC_EUNSUPPORTED (nothing launched) if swiglu is asked for a shape it cannot fuse.
-bool gemm_can_fuse_swiglu(const PackedW& W, int M, int splits) { if (splits != 1) return false; const GemmShape g = gemm_shape(W, M, true); return g.mb % 2 == 0 || (g.wide && g.mb == 3) || g.one_block; }
+bool gemm_can_fuse_swiglu(const PackedW& W, int M, int splits)
+{
+    if (splits != 1) return false;
+    const GemmShape g = gemm_shape(W, M, true);
+    // odd row-block counts (a tile with one column block per wavefront): where K would not be split anyway - with few column
+    // tiles the split projection and its pass over the slices keep more of the chip busy.  (At 4 rows of the 8B shape the fused
+    // launch takes the 37.5 us of the plain one and saves the 4.6 us pass per layer.)
+    if (g.mb % 2 != 0 && !g.wide) return gemm_pick_splits(W, M, 0) == 1;
+    return true;
+}
 
 spec_status launch_gemm_bf16(const PackedW& W, const bf16_t* Xp, int M, float* out, int ldo, int splits, bool swiglu, hipStream_t s)
 {
@@ -601,7 +613,7 @@ spec_status launch_gemm_bf16(const PackedW& W, const bf16_t* Xp, int M, float* o
     const u32x4_t* xp = (const u32x4_t*)Xp;
     if (swiglu && !gemm_can_fuse_swiglu(W, M, splits)) { set_error("gemm: SwiGLU cannot be fused for this shape"); return SPEC_EUNSUPPORTED; }
 #define SPEC_GEMM_LAUNCH_W(MBV, WMV, WDV, E, W8V, XFV) gemm_bf16_kernel<MBV, WMV, WDV, E, false, (MBV % 2 == 0 && WMV == 1) ? 2 : WMV, W8V, XFV><<<grid, GEMM_THREADS, 0, s>>>(wp, xp, out, W.n_blocks, W.k_steps, kps, mb_pad, M, W.N, ldo, stride, nullptr, 0, W.scale)
-#define SPEC_GEMM_LAUNCH_1BW(E, W8V, XFV) gemm_bf16_kernel<4, 1, 2, E, false, 1, W8V, XFV><<<grid, GEMM_THREADS, 0, s>>>(wp, xp, out, W.n_blocks, W.k_steps, kps, mb_pad, M, W.N, ldo, stride, nullptr, 0, W.scale)
+#define SPEC_GEMM_LAUNCH_1BW(MBV, E, W8V, XFV) gemm_bf16_kernel<MBV, 1, 2, E, false, 1, W8V, XFV><<<grid, GEMM_THREADS, 0, s>>>(wp, xp, out, W.n_blocks, W.k_steps, kps, mb_pad, M, W.N, ldo, stride, nullptr, 0, W.scale)
 #define SPEC_GEMM_LAUNCH_96W(E, W8V, XFV) gemm_bf16_kernel<3, 1, 2, E, false, 2, W8V, XFV><<<grid, GEMM_THREADS, 0, s>>>(wp, xp, out, W.n_blocks, W.k_steps, kps, mb_pad, M, W.N, ldo, stride, nullptr, 0, W.scale)
     // the four combinations of 8-bit or 16-bit weights and hi + lo or fp16 activations
 #define SPEC_GEMM_BY_TYPE(CALL, ...) do { \
@@ -610,9 +622,10 @@ spec_status launch_gemm_bf16(const PackedW& W, const bf16_t* Xp, int M, float* o
 #define SPEC_GEMM_LAUNCH_96(E) SPEC_GEMM_BY_TYPE(SPEC_GEMM_LAUNCH_96W, E)
 #define SPEC_GEMM_LAUNCH(MBV, WMV, WDV, E) SPEC_GEMM_BY_TYPE(SPEC_GEMM_LAUNCH_W, MBV, WMV, WDV, E)
     switch (mb) {
-        case 1: SPEC_GEMM_LAUNCH(1, 1, GEMM_WD, GEMM_EPI_PLAIN); break;
+        case 1: if (swiglu) SPEC_GEMM_LAUNCH(1, 1, GEMM_WD, GEMM_EPI_SWIGLU); else SPEC_GEMM_LAUNCH(1, 1, GEMM_WD, GEMM_EPI_PLAIN); break;
         case 2:
-            if (g.wide && swiglu) SPEC_GEMM_LAUNCH(2, 1, 2, GEMM_EPI_SWIGLU);
+            if (g.one_block) { if (swiglu) SPEC_GEMM_BY_TYPE(SPEC_GEMM_LAUNCH_1BW, 2, GEMM_EPI_SWIGLU); else SPEC_GEMM_BY_TYPE(SPEC_GEMM_LAUNCH_1BW, 2, GEMM_EPI_PLAIN); }
+            else if (g.wide && swiglu) SPEC_GEMM_LAUNCH(2, 1, 2, GEMM_EPI_SWIGLU);
             else if (g.wide) SPEC_GEMM_LAUNCH(2, 1, 2, GEMM_EPI_PLAIN);
             else if (swiglu) SPEC_GEMM_LAUNCH(2, 2, 2, GEMM_EPI_SWIGLU);
             else SPEC_GEMM_LAUNCH(2, 2, 2, GEMM_EPI_PLAIN);
@@ -620,13 +633,14 @@ spec_status launch_gemm_bf16(const PackedW& W, const bf16_t* Xp, int M, float* o
         case 3:
             if (g.wide && swiglu) SPEC_GEMM_LAUNCH_96(GEMM_EPI_SWIGLU);
             else if (g.wide) SPEC_GEMM_LAUNCH_96(GEMM_EPI_PLAIN);
+            else if (swiglu) SPEC_GEMM_LAUNCH(3, 1, GEMM_WD, GEMM_EPI_SWIGLU);
             else SPEC_GEMM_LAUNCH(3, 1, GEMM_WD, GEMM_EPI_PLAIN);
             break;
         case 6: case 8: return launch_gemm_big(W, Xp, M, mb, mb_pad, out, ldo, kps, swiglu, grid, s);
         default:
             if (g.one_block) {                               // fp16 activations only
-                if (W.w8) { if (swiglu) SPEC_GEMM_LAUNCH_1BW(GEMM_EPI_SWIGLU, true, XF_F16); else SPEC_GEMM_LAUNCH_1BW(GEMM_EPI_PLAIN, true, XF_F16); }
-                else { if (swiglu) SPEC_GEMM_LAUNCH_1BW(GEMM_EPI_SWIGLU, false, XF_F16); else SPEC_GEMM_LAUNCH_1BW(GEMM_EPI_PLAIN, false, XF_F16); }
+                if (W.w8) { if (swiglu) SPEC_GEMM_LAUNCH_1BW(4, GEMM_EPI_SWIGLU, true, XF_F16); else SPEC_GEMM_LAUNCH_1BW(4, GEMM_EPI_PLAIN, true, XF_F16); }
+                else { if (swiglu) SPEC_GEMM_LAUNCH_1BW(4, GEMM_EPI_SWIGLU, false, XF_F16); else SPEC_GEMM_LAUNCH_1BW(4, GEMM_EPI_PLAIN, false, XF_F16); }
             }
             else if (g.wide && swiglu) SPEC_GEMM_LAUNCH(4, 1, 2, GEMM_EPI_SWIGLU);
             else if (g.wide) SPEC_GEMM_LAUNCH(4, 1, 2, GEMM_EPI_PLAIN);

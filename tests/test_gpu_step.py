@@ -650,3 +650,22 @@ def test_long_random_walk_of_the_bookkeeping_against_the_oracle_book():
     assert held + len(book.free) == n_pages
     print("bookkeeping walk: %d pages held, %d free after 60 steps; longest sequence %d" % (held, len(book.free), max(book.ctx_len[s] for s in range(S))))
     sess.close()
+
+
+@pytest.mark.parametrize("w8", [False, True])
+@pytest.mark.parametrize("f16_inputs", [12, 0])
+@pytest.mark.parametrize("B,k", [(1, 0), (8, 3), (11, 2), (16, 3), (13, 4), (12, 7)])
+def test_bf16_one_column_block_per_wavefront(B, k, f16_inputs, w8):
+    """Tiles of 1, 2 and 3 row blocks x 128 columns with one column block per wavefront and the SwiGLU in their epilogue:
+    M = 1, 32, 33, 64, 65 and 96 rows, in either operand format and weight type."""
+    from paper_2604_26779_amd import binding as sv
+    before = sv.spec_tune_get("gemm_f16_inputs")
+    sv.spec_tune_set("gemm_f16_inputs", f16_inputs)
+    try:
+        rng = np.random.default_rng(B * 10 + k)
+        ctx = [int(c) for c in rng.integers(3, 120, size=B)]
+        ok, max_err, worst = _run_custom_bf16(ctx, k=k, seed=B + k, vocab=1000, **(dict(w_dtype="fp8_e4m3") if w8 else {}))
+    finally:
+        sv.spec_tune_set("gemm_f16_inputs", before)
+    print("M=%d, fp16 inputs %d, 8-bit matrices %s: logits max abs err %.3e" % (B * (k + 1), f16_inputs, w8, max_err))
+    assert ok, (max_err, worst)
