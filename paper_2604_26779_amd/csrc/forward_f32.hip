@@ -2,6 +2,10 @@
 // a bring-up reference for shapes the MFMA path does not cover).  Same step order as the bf16
 // path: embed -> per layer [RMSNorm, QKV, rotary + speculative KV write, causal attention over the
 // paged cache, O + residual, RMSNorm, gate/up, SwiGLU, down + residual] -> final RMSNorm -> head.
+#include <initializer_list>
+#include <type_traits>
+#include <utility>
+
 #include "common.h"
 
 namespace specv {
@@ -65,6 +69,70 @@ __global__ __launch_bounds__(256) void f32_gemm_kernel(const float* __restrict__
                 *dst = ACCUM ? *dst + acc[i][j] : acc[i][j];
             }
         }
+}
+
+// The same product for few rows: up to three matrices over the same input side by side (their columns follow each other in y).
+// A wavefront computes 8 rows x 4 columns with K spread over its lanes, so that a narrow projection still gives hundreds of
+// wavefronts, every load is 16 bytes and the only wait is one trip to memory per 256 of K; the 32 sums are folded over the
+// lanes by exchanging halves (32 shuffles).  K % 4 == 0, rows and matrices 16-byte aligned.
+struct F32Parts { const float* w[3]; int end[3]; int n; };
+
+template <bool ACCUM>
+__global__ __launch_bounds__(256) void f32_gemm_rows_kernel(const float* __restrict__ a, F32Parts parts, int M, int N, int K,
+                                                            float* __restrict__ y, int ldy)
+{
+    const int lane = threadIdx.x & 63, n0 = (blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * 4, m0 = blockIdx.y * 8;
+    if (n0 >= N) return;
+    const float *wr[4], *ar[8];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int n = n0 + j < N ? n0 + j : N - 1;
+        const int p = n < parts.end[0] ? 0 : (n < parts.end[1] ? 1 : 2);
+        wr[j] = parts.w[p] + (int64_t)(n - (p > 0 ? parts.end[p - 1] : 0)) * K;
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) ar[i] = a + (int64_t)(m0 + i < M ? m0 + i : M - 1) * K;
+    float acc[32];
+#pragma unroll
+    for (int r = 0; r < 32; ++r) acc[r] = 0.f;
+    for (int k = lane * 4; k < K; k += 256) {
+        float4 wv[4], av[8];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) wv[j] = *(const float4*)(wr[j] + k);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) av[i] = *(const float4*)(ar[i] + k);
+        __builtin_amdgcn_sched_barrier(0);                 // all twelve loads before the first use of one
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                float& r = acc[i * 4 + j];
+                r += av[i].x * wv[j].x; r += av[i].y * wv[j].y; r += av[i].z * wv[j].z; r += av[i].w * wv[j].w;
+            }
+    }
+    // a lane keeps the half of its sums that its bit selects and hands the other half over: sum lane / 2 ends up in lanes
+    // 2 r and 2 r + 1
+    // (a compile-time size for every step: the array has to stay in registers)
+    auto fold = [&](auto half_c) {
+        constexpr int HALF = decltype(half_c)::value, OFF = 2 * HALF;
+        const bool up = lane & OFF;
+#pragma unroll
+        for (int r = 0; r < HALF; ++r) {
+            const float give = up ? acc[r] : acc[r + HALF], keep = up ? acc[r + HALF] : acc[r];
+            acc[r] = keep + __shfl_xor(give, OFF);
+        }
+    };
+    fold(std::integral_constant<int, 16>{});
+    fold(std::integral_constant<int, 8>{});
+    fold(std::integral_constant<int, 4>{});
+    fold(std::integral_constant<int, 2>{});
+    fold(std::integral_constant<int, 1>{});
+    const float v = acc[0] + __shfl_xor(acc[0], 1);
+    const int m = m0 + (lane >> 3), n = n0 + ((lane >> 1) & 3);
+    if ((lane & 1) == 0 && m < M && n < N) {
+        float* dst = y + (int64_t)m * ldy + n;
+        *dst = ACCUM ? *dst + v : v;
+    }
 }
 
 // rotary embedding of q (in place) and k, and the speculative write of k, v into the paged cache.
@@ -133,11 +201,14 @@ __global__ __launch_bounds__(64) void f32_attention_kernel(const float* __restri
     for (int p0 = 0; p0 < visible; p0 += 64) {
         int pos = p0 + lane;
         float s = -INFINITY;
+        int my_page = 0;                                  // page of this lane's position
         if (pos < visible) {
-            int64_t page = kv.page_table[(int64_t)seq * kv.max_pages + pos / SPEC_PAGE_SIZE];
+            my_page = kv.page_table[(int64_t)seq * kv.max_pages + pos / SPEC_PAGE_SIZE];
+            const int64_t page = my_page;
             const float* kr = pool + ((((int64_t)layer_pool * kv.n_pages + page) * 2 + 0) * Hkv + g) * block +
                               (int64_t)(pos % SPEC_PAGE_SIZE) * dh;
             float d = 0.f;
+#pragma unroll 16
             for (int c = 0; c < dh; ++c) d += kr[c] * sq[c];
             s = d * scale;
         }
@@ -158,12 +229,18 @@ __global__ __launch_bounds__(64) void f32_attention_kernel(const float* __restri
             int c = lane + 64 * a;
             if (c < dh) {
                 float o = acc[a] * corr;
-                for (int t = 0; t < cnt; ++t) {
-                    int pp = p0 + t;
-                    int64_t page = kv.page_table[(int64_t)seq * kv.max_pages + pp / SPEC_PAGE_SIZE];
-                    const float* vr = pool + ((((int64_t)layer_pool * kv.n_pages + page) * 2 + 1) * Hkv + g) * block +
-                                      (int64_t)(pp % SPEC_PAGE_SIZE) * dh;
-                    o += sp[t] * vr[c];
+                // a page of positions at a time (p0 is a multiple of the page size), its loads in flight together: the
+                // slots past the last visible position re-read that one and are left out of the sum
+                for (int t0 = 0; t0 < cnt; t0 += SPEC_PAGE_SIZE) {
+                    const int64_t page = __builtin_amdgcn_readlane(my_page, t0);
+                    const int n_t = cnt - t0 < SPEC_PAGE_SIZE ? cnt - t0 : SPEC_PAGE_SIZE;
+                    const float* vb = pool + ((((int64_t)layer_pool * kv.n_pages + page) * 2 + 1) * Hkv + g) * block + c;
+                    float v[SPEC_PAGE_SIZE];
+#pragma unroll
+                    for (int t = 0; t < SPEC_PAGE_SIZE; ++t) v[t] = vb[(int64_t)(t < n_t ? t : n_t - 1) * dh];
+#pragma unroll
+                    for (int t = 0; t < SPEC_PAGE_SIZE; ++t)
+                        if (t < n_t) o += sp[t0 + t] * v[t];
                 }
                 acc[a] = o;
             }
@@ -205,11 +282,35 @@ static size_t f32_carve(const spec_model_desc& d, int M, char* base, F32Ws* w)
 
 size_t f32_workspace_bytes(const spec_model_desc& d, int B, int k) { return f32_carve(d, B * (k + 1), nullptr, nullptr); }
 
-static void gemm(const float* a, const float* w, int M, int N, int K, float* y, int ldy, bool accum, hipStream_t s)
+// y = a w^T for up to three matrices over the same rows, side by side in y
+static void gemm(const float* a, std::initializer_list<std::pair<const float*, int>> ws, int M, int K, float* y, int ldy, bool accum, hipStream_t s)
 {
-    dim3 grid((unsigned)cdiv(N, 32), (unsigned)cdiv(M, 32));
-    if (accum) f32_gemm_kernel<true><<<grid, 256, 0, s>>>(a, w, M, N, K, y, ldy);
-    else f32_gemm_kernel<false><<<grid, 256, 0, s>>>(a, w, M, N, K, y, ldy);
+    F32Parts parts{};
+    int N = 0;
+    bool aligned = K % 4 == 0 && ((uintptr_t)a & 15) == 0;
+    for (auto& w : ws) {
+        N += w.second;
+        parts.w[parts.n] = w.first;
+        parts.end[parts.n++] = N;
+        aligned = aligned && ((uintptr_t)w.first & 15) == 0;
+    }
+    for (int i = parts.n; i < 3; ++i) { parts.w[i] = parts.w[parts.n - 1]; parts.end[i] = N; }
+    // f32_gemm_rows_kernel takes a trip to memory per 256 of K, but fetches a matrix again for every 8 rows; the tiled kernel takes a
+    // trip per 32 of K, and its tile is 32 rows.  Tiled / rows, us: N = 1024, K = 256: 15.2 / 3.8 at 16 rows, 18.4 / 12.1 at 512;
+    // N = 1024, K = 704: 38.8 / 5.1 and 45.7 / 20.9; N = 4096, K = 256: 15.2 / 4.2 and 41.1 / 37.6; N = K = 4096: 319 / 20 and
+    // 669 / 547.  The lead shrinks with the rows, and beyond 512 nothing was measured.
+    if (aligned && M <= 512) {
+        dim3 grid((unsigned)cdiv(N, 16), (unsigned)cdiv(M, 8));
+        if (accum) f32_gemm_rows_kernel<true><<<grid, 256, 0, s>>>(a, parts, M, N, K, y, ldy);
+        else f32_gemm_rows_kernel<false><<<grid, 256, 0, s>>>(a, parts, M, N, K, y, ldy);
+        return;
+    }
+    for (auto& w : ws) {
+        dim3 grid((unsigned)cdiv(w.second, 32), (unsigned)cdiv(M, 32));
+        if (accum) f32_gemm_kernel<true><<<grid, 256, 0, s>>>(a, w.first, M, w.second, K, y, ldy);
+        else f32_gemm_kernel<false><<<grid, 256, 0, s>>>(a, w.first, M, w.second, K, y, ldy);
+        y += w.second;
+    }
 }
 
 spec_status f32_forward(spec_model* mdl, spec_kv* kv, int B, int k, const int32_t* dev_seq_ids,
@@ -230,20 +331,17 @@ spec_status f32_forward(spec_model* mdl, spec_kv* kv, int B, int k, const int32_
         int lp = kv->alias_mod > 0 ? l % kv->alias_mod : l;
         auto W = [&](int i) { return (const float*)mdl->layer_w(l, i); };
         f32_rmsnorm_kernel<<<M, 256, 0, s>>>(w.x, W(0), D, d.rms_eps, w.h);
-        gemm(w.h, W(1), M, nq, D, w.qkv, nqkv, false, s);
-        gemm(w.h, W(2), M, nkv, D, w.qkv + nq, nqkv, false, s);
-        gemm(w.h, W(3), M, nkv, D, w.qkv + nq + nkv, nqkv, false, s);
+        gemm(w.h, {{W(1), nq}, {W(2), nkv}, {W(3), nkv}}, M, D, w.qkv, nqkv, false, s);
         f32_rope_kv_write_kernel<<<M, 256, 0, s>>>(w.qkv, T, dev_seq_ids, view, lp, Hq, Hkv, dh, d.rope_theta);
         f32_attention_kernel<<<dim3(M, Hq), 64, 0, s>>>(w.qkv, T, dev_seq_ids, view, lp, Hq, Hkv, dh, scale, w.attn);
-        gemm(w.attn, W(4), M, D, nq, w.x, D, true, s);
+        gemm(w.attn, {{W(4), D}}, M, nq, w.x, D, true, s);
         f32_rmsnorm_kernel<<<M, 256, 0, s>>>(w.x, W(5), D, d.rms_eps, w.h);
-        gemm(w.h, W(6), M, F, D, w.gu, 2 * F, false, s);
-        gemm(w.h, W(7), M, F, D, w.gu + F, 2 * F, false, s);
+        gemm(w.h, {{W(6), F}, {W(7), F}}, M, D, w.gu, 2 * F, false, s);
         f32_swiglu_kernel<<<(unsigned)cdiv((int64_t)M * F, 256), 256, 0, s>>>(w.gu, M, F, w.act);
-        gemm(w.act, W(8), M, D, F, w.x, D, true, s);
+        gemm(w.act, {{W(8), D}}, M, F, w.x, D, true, s);
     }
     f32_rmsnorm_kernel<<<M, 256, 0, s>>>(w.x, (const float*)mdl->final_norm(), D, d.rms_eps, w.h);
-    gemm(w.h, (const float*)mdl->head_w(), M, head_rows(d), D, dev_logits, head_rows(d), false, s);
+    gemm(w.h, {{(const float*)mdl->head_w(), head_rows(d)}}, M, D, dev_logits, head_rows(d), false, s);
     SPEC_LAUNCH_CHECK("fp32 forward");
     return SPEC_OK;
 }

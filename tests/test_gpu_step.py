@@ -669,3 +669,21 @@ def test_bf16_one_column_block_per_wavefront(B, k, f16_inputs, w8):
         sv.spec_tune_set("gemm_f16_inputs", before)
     print("M=%d, fp16 inputs %d, 8-bit matrices %s: logits max abs err %.3e" % (B * (k + 1), f16_inputs, w8, max_err))
     assert ok, (max_err, worst)
+
+
+@pytest.mark.parametrize("B,k,changes", [
+    (1, 0, {}),                                       # one row of an 8-row block
+    (3, 2, dict(vocab=1001)),                         # 9 rows, a last column group of one
+    (5, 1, dict(ffn_dim=706)),                        # a K that is no multiple of 4 (down projection): the tiled kernel
+    (64, 7, {}),                                      # 512 rows: the last the few-row kernel takes
+    (103, 4, dict(vocab=999, n_kv_heads=2)),          # 515 rows: the tiled kernel
+    (2, 7, dict(d_model=1028, n_q_heads=2, n_kv_heads=2)),          # K = 1028: five trips, the last with one lane; K = 128: half the lanes
+])
+def test_f32_projections_few_and_many_rows(B, k, changes):
+    """The two fp32 projection kernels at the edges of their tiles and of the rule between them; contexts around the page and
+    wavefront boundaries of the fp32 attention (fp32 sums of a few hundred terms: far below 1e-4 of logits of order one)."""
+    cfg = dict(si.MODELS["tiny_fp32"], **changes)
+    ctx = [[0, 1, 15, 16, 17, 63, 64, 65, 127, 130][b % 10] for b in range(B)]
+    ok, max_err, worst = _run_custom_bf16(ctx, k=k, seed=B + k, **cfg)
+    print("fp32 B=%d k=%d %s: logits max abs err %.3e" % (B, k, changes, max_err))
+    assert ok and max_err <= 1e-4, (max_err, worst)
