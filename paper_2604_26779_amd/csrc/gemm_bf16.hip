@@ -195,7 +195,7 @@ spec_status w8_pack_matrix(const unsigned char* const* dev_parts, const float* c
 // columns), so with WM = 2 every activation fragment read from LDS feeds two MFMAs and every weight
 // fragment is read by two wavefronts (the second read hits the CU's L1): half the LDS traffic per MFMA.
 // GROUPED (mixture of experts): blockIdx.z walks a device-side list of row tiles, tiles[0] = number of
-// tiles, then (group, first row block) pairs; group g multiplies by the matrix at Wp + g * w_group_stride
+// tiles, then (group, first row block and rows in use) pairs; group g multiplies by the matrix at Wp + g * w_group_stride
 // (all groups have the same shape).  Tiles past the list's end exit at once.
 // (Large row counts take the 192- and 256-row x 256-column tiles of gemm_big.hip.)
 // W8: the weights are E4M3 codes, two k-steps per 16-byte word (half the weight bytes and load instructions); a
@@ -242,7 +242,8 @@ __global__ __launch_bounds__(GEMM_THREADS, (MB >= 3 && WM == 1 && NBW_T == 2) ? 
         if (bz >= tiles[0]) return;
         Wp += (int64_t)tiles[1 + 2 * bz] * w_group_stride;
         if constexpr (W8) wscale += (int64_t)tiles[1 + 2 * bz] * w_group_stride * 4;   // a group's scales sit in its own region
-        mblk0 = tiles[2 + 2 * bz];
+        mblk0 = moe_tile_block(tiles[2 + 2 * bz]);
+        M = mblk0 * 32 + moe_tile_rows(tiles[2 + 2 * bz]);                 // padding rows are not stored
     }
 
     // slab s of column block j of this wavefront: wptr[j] + s * wslab

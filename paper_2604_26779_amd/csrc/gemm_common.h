@@ -35,6 +35,11 @@ __device__ inline u32x4_t widen_e4m3x8(unsigned int wa, unsigned int wb)
                        __builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(wb, 1.0f, true))};
 }
 
+// entry of the grouped GEMM's tile list: first 32-row block of the tile (24 bits) and how many of its rows are not padding
+__host__ __device__ inline int moe_tile_pack(int first_block, int rows) { return first_block | (rows << 24); }
+__device__ inline int moe_tile_block(int t) { return t & 0xffffff; }
+__device__ inline int moe_tile_rows(int t) { return t >> 24; }
+
 // Which tile a workgroup computes.  Workgroups go to the dies round robin in launch order, so the launch index is re-mapped:
 // die j takes a contiguous stretch of the tiles in the order (row tile fastest, then column tile, then k-split).  The workgroups
 // that share a weight tile then share an L2, and a die reads the activations of one or two k-splits instead of all of them.

@@ -6,6 +6,7 @@
 // Order of the rows inside an expert's tile list is the order of the (row, rank) pairs, so every buffer
 // and every sum is a pure function of the inputs (no atomics on results).
 #include "common.h"
+#include "gemm_common.h"
 #include "operand.h"
 
 namespace specv {
@@ -63,34 +64,41 @@ __global__ __launch_bounds__(64) void moe_route_kernel(const float* __restrict__
     }
 }
 
-// One workgroup: how many rows every expert received, where its (padded) rows start, and the tile list
+// One workgroup, thread e for expert e (E <= 256): how many rows every expert received, where its (padded) rows start, and the tile list
 // of the grouped GEMM.  row0 [E + 1] (row0[E] = all padded rows); tiles: [0] = count, then (expert, first
-// 32-row block) pairs.
+// 32-row block and rows that are not padding) pairs.
 __global__ __launch_bounds__(256) void moe_plan_kernel(const int32_t* __restrict__ ids, int n_pairs, int E,
                                                         int32_t* __restrict__ row0, int32_t* __restrict__ tiles)
 {
-    __shared__ int hist[256];
-    hist[threadIdx.x] = 0;
+    __shared__ int hist[256], upto[256];
+    const int e = threadIdx.x;
+    hist[e] = 0;
     __syncthreads();
-    for (int p = threadIdx.x; p < n_pairs; p += 256) {
-        int e = ids[p];
-        if (e >= 0 && e < E) atomicAdd(&hist[e], 1);
+    for (int p = e; p < n_pairs; p += 256) {
+        int x = ids[p];
+        if (x >= 0 && x < E) atomicAdd(&hist[x], 1);
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        int at = 0, nt = 0;
-        for (int e = 0; e < E; ++e) {
-            row0[e] = at;
-            int t = (hist[e] + MOE_TILE_ROWS - 1) / MOE_TILE_ROWS;
-            for (int j = 0; j < t; ++j) {
-                tiles[1 + 2 * nt] = e;
-                tiles[2 + 2 * nt] = (at + j * MOE_TILE_ROWS) / 32;
-                ++nt;
-            }
-            at += t * MOE_TILE_ROWS;
-        }
-        row0[E] = at;
-        tiles[0] = nt;
+    const int t = (hist[e] + MOE_TILE_ROWS - 1) / MOE_TILE_ROWS;
+    // tiles of the experts up to and including this one: sums over doubling distances
+    upto[e] = t;
+    __syncthreads();
+    for (int off = 1; off < 256; off <<= 1) {
+        const int add = e >= off ? upto[e - off] : 0;
+        __syncthreads();
+        upto[e] += add;
+        __syncthreads();
+    }
+    const int first = upto[e] - t;
+    if (e < E) row0[e] = first * MOE_TILE_ROWS;
+    for (int j = 0; j < t; ++j) {
+        tiles[1 + 2 * (first + j)] = e;
+        const int rows = hist[e] - j * MOE_TILE_ROWS;
+        tiles[2 + 2 * (first + j)] = moe_tile_pack((first + j) * (MOE_TILE_ROWS / 32), rows < MOE_TILE_ROWS ? rows : MOE_TILE_ROWS);
+    }
+    if (e == 255) {
+        row0[E] = upto[255] * MOE_TILE_ROWS;
+        tiles[0] = upto[255];
     }
 }
 
@@ -124,8 +132,10 @@ __global__ __launch_bounds__(256) void moe_permute_kernel(const int32_t* __restr
     for (int row = base + running + threadIdx.x; row < end; row += 256) src_row[row] = -1;
 }
 
-// Activations of the permuted rows in the GEMM's operand order (hi and lo words), zeros for padding.
-// One thread per 16-byte destination word: writes are contiguous, reads gather rows of one k-step.
+// Activations of the permuted rows in the GEMM's operand order (hi and lo words).  One thread per 16-byte destination word: writes
+// are contiguous, reads gather rows of one k-step.  Padding rows (three in four at 16 rows per expert) are left as they are, here and
+// in the outputs of the expert projections: a row of a product depends on its own row of the input only, and nothing reads
+// a padding row's results.
 // The source is always hi + lo (the router reads it too); with xf_dst = XF_F16 (expert projections that take fp16
 // activations, 64 threads per workgroup) a destination word is fp16(hi + lo) of the same eight values.
 __device__ inline unsigned int hilo_to_f16x2(unsigned int hi, unsigned int lo)
@@ -142,18 +152,15 @@ __global__ void moe_gather_kernel(const uint4* __restrict__ xp_src, int mb_pad_s
     if (mblk >= blocks) return;
     const int part = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int m = src_row[mblk * 32 + (lane & 31)];
-    uint4 v = make_uint4(0, 0, 0, 0);
+    if (m < 0) return;
     if (xf_dst == XF_F16) {
-        if (m >= 0) {
-            const int64_t at = (((int64_t)ks * mb_pad_src + (m >> 5)) * 2) * 64 + (m & 31) + (lane & 32);
-            const uint4 hi = xp_src[at], lo = xp_src[at + 64];
-            v = make_uint4(hilo_to_f16x2(hi.x, lo.x), hilo_to_f16x2(hi.y, lo.y), hilo_to_f16x2(hi.z, lo.z), hilo_to_f16x2(hi.w, lo.w));
-        }
-        xp_dst[((int64_t)ks * mb_pad_dst + mblk) * 64 + lane] = v;
+        const int64_t at = (((int64_t)ks * mb_pad_src + (m >> 5)) * 2) * 64 + (m & 31) + (lane & 32);
+        const uint4 hi = xp_src[at], lo = xp_src[at + 64];
+        xp_dst[((int64_t)ks * mb_pad_dst + mblk) * 64 + lane] =
+            make_uint4(hilo_to_f16x2(hi.x, lo.x), hilo_to_f16x2(hi.y, lo.y), hilo_to_f16x2(hi.z, lo.z), hilo_to_f16x2(hi.w, lo.w));
         return;
     }
-    if (m >= 0) v = xp_src[(((int64_t)ks * mb_pad_src + (m >> 5)) * 2 + part) * 64 + (m & 31) + (lane & 32)];
-    xp_dst[(((int64_t)ks * mb_pad_dst + mblk) * 2 + part) * 64 + lane] = v;
+    xp_dst[(((int64_t)ks * mb_pad_dst + mblk) * 2 + part) * 64 + lane] = xp_src[(((int64_t)ks * mb_pad_src + (m >> 5)) * 2 + part) * 64 + (m & 31) + (lane & 32)];
 }
 
 // x[m] += sum over the row's experts (in rank order) of weight * expert output; xp = RMSNorm(x[m]) * gain.
