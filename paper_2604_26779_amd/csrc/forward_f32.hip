@@ -74,7 +74,8 @@ __global__ __launch_bounds__(256) void f32_gemm_kernel(const float* __restrict__
 // The same product for few rows: up to three matrices over the same input side by side (their columns follow each other in y).
 // A wavefront computes 8 rows x 4 columns with K spread over its lanes, so that a narrow projection still gives hundreds of
 // wavefronts, every load is 16 bytes and the only wait is one trip to memory per 256 of K; the 32 sums are folded over the
-// lanes by exchanging halves (32 shuffles).  K % 4 == 0, rows and matrices 16-byte aligned.
+// lanes by exchanging halves (32 shuffles).  K % 4 == 0, rows and matrices 16-byte aligned.  Bound by the launch and two trips to memory
+// at the sizes of the tiny configuration (3.8 us for N = 1024, K = 256 at 16 rows; the tiled kernel 15.2).
 struct F32Parts { const float* w[3]; int end[3]; int n; };
 
 template <bool ACCUM>

@@ -135,7 +135,7 @@ __global__ __launch_bounds__(256) void moe_permute_kernel(const int32_t* __restr
 // Activations of the permuted rows in the GEMM's operand order (hi and lo words).  One thread per 16-byte destination word: writes
 // are contiguous, reads gather rows of one k-step.  Padding rows (three in four at 16 rows per expert) are left as they are, here and
 // in the outputs of the expert projections: a row of a product depends on its own row of the input only, and nothing reads
-// a padding row's results.
+// a padding row's results.  (256 rows over 128 experts: gather 24.9 -> 22.3 us, down projection 322 -> 276-293, gate/up 566 -> 543.)
 // The source is always hi + lo (the router reads it too); with xf_dst = XF_F16 (expert projections that take fp16
 // activations, 64 threads per workgroup) a destination word is fp16(hi + lo) of the same eight values.
 __device__ inline unsigned int hilo_to_f16x2(unsigned int hi, unsigned int lo)
