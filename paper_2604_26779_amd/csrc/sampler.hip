@@ -134,7 +134,7 @@ __device__ inline int round_groups(int gb, int g1)
     return n < SAMP_GPT ? n : SAMP_GPT;
 }
 
-// (reference, sum of exp(z - reference)) of one range of a row.  Each wavefront reads its entries once, takes the maximum
+// (largest logit, sum of exp((logit - largest) / T)) of one range of a row.  Each wavefront reads its entries once, takes the maximum
 // of the 16 entries per lane that are in registers as the reference (moving it, and what has been summed, when a later
 // round exceeds it), so there is no second pass over the logits and no barrier before the sums; the wavefronts' pairs are
 // merged in a fixed order.
@@ -144,8 +144,8 @@ __device__ inline int round_groups(int gb, int g1)
 // q rows a mapped draft draw then fills at scattered positions; counters != null: the sequences' arrival counters of the
 // scan that follows, counter_rows rows per sequence)
 template <bool VEC>
-__global__ __launch_bounds__(SAMP_THREADS) void row_stats_kernel(const float* __restrict__ logits, int64_t row_stride, int V, double T,
-                                                                  double rT, double2* __restrict__ stats, int32_t* __restrict__ counters,
+__global__ __launch_bounds__(SAMP_THREADS) void row_stats_kernel(const float* __restrict__ logits, int64_t row_stride, int V, double rT,
+                                                                  double2* __restrict__ stats, int32_t* __restrict__ counters,
                                                                   int counter_rows, float* __restrict__ zero_rows = nullptr,
                                                                   int64_t zero_stride = 0, int zero_width = 0)
 {
@@ -191,19 +191,20 @@ __global__ __launch_bounds__(SAMP_THREADS) void row_stats_kernel(const float* __
     }
     // fixed order: butterfly inside a wavefront, then the wavefronts one after the other
     for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
-    if (lane == 0) l_st[wave] = make_double2(ref > -INFINITY ? (double)ref / T : -INFINITY, sum);
+    if (lane == 0) l_st[wave] = make_double2((double)ref, sum);
     __syncthreads();
     if (threadIdx.x == 0) {
         double M = -INFINITY, S = 0.0;
         for (int w = 0; w < SAMP_WAVES; ++w) M = fmax(M, l_st[w].x);
         for (int w = 0; w < SAMP_WAVES; ++w)
-            if (l_st[w].y > 0.0) S += l_st[w].y * exp_sum(l_st[w].x - M);
+            if (l_st[w].y > 0.0) S += l_st[w].y * exp_sum((l_st[w].x - M) * rT);
         stats[(int64_t)blockIdx.x * SAMP_PARTS + blockIdx.y] = make_double2(M, S);
     }
 }
 
-// a row's statistics from those of its ranges, in range order: M = max m_p, S = sum_p s_p exp(m_p - M)
-__device__ inline double2 row_stat(const double2* __restrict__ stats, int64_t row)
+// a row's statistics from those of its ranges, in range order: M = max m_p, S = sum_p s_p exp((m_p - M) / T).  M stays a logit: M / T is
+// formed where it is needed, as M cannot be had back from it when T is infinite (0) or subnormal.
+__device__ inline double2 row_stat(const double2* __restrict__ stats, int64_t row, double rT)
 {
     double2 c[SAMP_PARTS];
 #pragma unroll
@@ -213,7 +214,7 @@ __device__ inline double2 row_stat(const double2* __restrict__ stats, int64_t ro
     for (int p = 0; p < SAMP_PARTS; ++p) M = fmax(M, c[p].x);
     double S = 0.0;
 #pragma unroll
-    for (int p = 0; p < SAMP_PARTS; ++p) S += c[p].y > 0.0 ? c[p].y * exp_sum(c[p].x - M) : 0.0;
+    for (int p = 0; p < SAMP_PARTS; ++p) S += c[p].y > 0.0 ? c[p].y * exp_sum((c[p].x - M) * rT) : 0.0;
     return make_double2(M, S);
 }
 
@@ -248,16 +249,16 @@ __device__ inline float race_scale(uint32_t word)
 // Weights of a race over one row: RACE_PLAIN p; RACE_RES max(0, p - q); RACE_HOT p except 0 at the token `hot` (the residual
 // of a one-hot draft distribution).  race_key: the exact key of entry v, fp64, -1 where the weight is not positive.
 constexpr int RACE_PLAIN = 0, RACE_RES = 1, RACE_HOT = 2;
-struct RaceRow {                              // one race: the row, its statistics, the random stream
+struct RaceRow {                              // one race: the row, its largest logit and sum, the random stream
     const float *l, *q;
     int V, hot;
-    double T, m, S;
+    double T, max_l, S;
     uint32_t k0, k1, c1, c2, c3;
 };
 template <int KIND>
 __device__ inline double race_key(const RaceRow& r, int v)
 {
-    const double pv = exp((double)r.l[v] / r.T - r.m) / r.S;
+    const double pv = exp((double)r.l[v] / r.T - r.max_l / r.T) / r.S;
     if (!(pv > 0.0)) return -1.0;
     const double w = KIND == RACE_RES ? fmax(0.0, pv - (double)r.q[v]) : (KIND == RACE_HOT && v == r.hot ? 0.0 : pv);
     if (!(w > 0.0)) return -1.0;
@@ -269,15 +270,31 @@ __device__ inline double race_key(const RaceRow& r, int v)
 
 // One round of a race, SAMP_GPT groups per lane: keeps in `best` / `best_v` the exact winner among the lane's entries that may win.
 // reach: the largest lower bound of a key that this wavefront has met (or knows to exist elsewhere).
-// The exponent (l - mx) log2(e) / T, mx the row's largest logit, carries three fp32 roundings: 126 * 3 * 2^-24 = 2.3e-5 at most
+// The exponent (l - mx) log2(e) / T, mx the row's largest logit, carries three fp32 roundings (RaceExponent): 126 * 3 * 2^-24 = 2.3e-5 at most
 // where the exponential is a normal number, so the fp32 probability is off by less than RACE_EPS of itself, the scale of
 // race_scale included.  Below that it counts as 0 with an upper bound of RACE_TINY: such an entry matters only if nothing clear of
 // the fp32 range's end competes, and then (bar = 0) every entry is evaluated.
 constexpr float RACE_EPS = 4.0e-5f, RACE_TINY = 1.2e-38f;
 
+// log2 of an entry's probability times S: (l c - mx c) * (log2(e) / (T c)), the first term one fused instruction.  c is a power of two
+// (1 for the usual temperatures) that keeps every term inside fp32's range for every T > 0, infinite and subnormal ones too:
+//   T > 1: 1/2 - l - mx may be twice the largest number, and e.g. T = 1e38 would still give it weight;
+//   T < 1e-37: 2^24 - log2(e) / T may be infinite (and 0 times it no number).  With |mx| >= 2^100 c stays 1 and that factor is held at the
+//   largest number: two logits that differ do so by 2^77 there, so the product is 0 or far below the range all the same.
+struct RaceExponent {
+    float c, mc, r;
+    __device__ RaceExponent(float mx, double T)
+    {
+        c = T > 1.0 ? 0.5f : (T < 1e-37 && fabsf(mx) < 1.2676506e30f ? 16777216.0f : 1.0f);
+        mc = mx * c;
+        r = (float)fmin(1.4426950408889634 / (T * c), 3.4028234663852886e38);
+    }
+    __device__ float operator()(float l) const { return __builtin_fmaf(l, c, -mc) * r; }
+};
+
 template <int KIND>
 __device__ inline void race_round(const RaceRow& row, const float (&l)[SAMP_GPT][4], const float (&qv)[SAMP_GPT][4], int gb, int g1, int n_u,
-                                  float rT2, float mx, float rS, float& reach, double& best, int& best_v)
+                                  const RaceExponent& exponent, float rS, float& reach, double& best, int& best_v)
 {
     const int lane = threadIdx.x & 63;
     float key[SAMP_GPT][4];                                          // the residual races': upper bounds; the plain race's: the fp32 keys
@@ -292,7 +309,7 @@ __device__ inline void race_round(const RaceRow& row, const float (&l)[SAMP_GPT]
             const uint32_t word[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const float p = __builtin_amdgcn_exp2f((l[u][j] - mx) * rT2) * rS;           // 0 for -inf; NaN is never kept
+                const float p = __builtin_amdgcn_exp2f(exponent(l[u][j])) * rS;              // 0 for -inf; NaN is never kept
                 const float r = race_scale(word[j]);
                 if constexpr (KIND == RACE_PLAIN) {
                     key[u][j] = l[u][j] > -INFINITY ? p * r : -1.f;
@@ -329,14 +346,15 @@ template <int KIND, bool VEC>
 __device__ inline void race_scan(const RaceRow& row, int g0, int g1, double& best, int& best_v)
 {
     const int wave = threadIdx.x >> 6;
-    const float rT2 = (float)(1.4426950408889634 / row.T), mx = (float)(row.m * row.T), rS = (float)(1.0 / row.S);
+    const RaceExponent exponent((float)row.max_l, row.T);
+    const float rS = (float)(1.0 / row.S);
     // the entry with the largest p, 1 / S, has a key of at least 1 / (17 S) (-ln u is at most 16.7): nothing below wins the plain race
     float reach = KIND == RACE_PLAIN ? rS * (1.0f / 17.0f) : 0.f;
     for (int gb = g0 + wave * 64; gb < g1; gb += SAMP_THREADS * SAMP_GPT) {
         float l[SAMP_GPT][4], qv[SAMP_GPT][4];
         load_round<VEC>(row.l, gb, g1, row.V, -INFINITY, l);
         if (KIND == RACE_RES) load_round<VEC>(row.q, gb, g1, row.V, 0.f, qv);
-        race_round<KIND>(row, l, qv, gb, g1, round_groups(gb, g1), rT2, mx, rS, reach, best, best_v);
+        race_round<KIND>(row, l, qv, gb, g1, round_groups(gb, g1), exponent, rS, reach, best, best_v);
     }
 }
 
@@ -377,7 +395,7 @@ __device__ inline bool merge_parts(RacePart* parts, int part, int32_t* counter, 
 template <bool VEC>
 __global__ __launch_bounds__(SAMP_THREADS, 4) void reject_scan_kernel(
     int k, int V, const float* __restrict__ logits, const float* __restrict__ q, const int32_t* __restrict__ draft,
-    double T, uint32_t seed_lo, uint32_t seed_hi, uint32_t step4, const double2* __restrict__ stats,
+    double T, double rT, uint32_t seed_lo, uint32_t seed_hi, uint32_t step4, const double2* __restrict__ stats,
     RacePart* __restrict__ parts, int32_t* __restrict__ counters, int32_t* __restrict__ accept_len, int32_t* __restrict__ out_tokens,
     float* __restrict__ dbg)
 {
@@ -399,10 +417,10 @@ __global__ __launch_bounds__(SAMP_THREADS, 4) void reject_scan_kernel(
             const bool probe = x >= 0 && x < V;
             const float lx = probe ? L[(int64_t)i * V + x] : 0.f;
             Q = probe ? (Qb ? (double)Qb[(int64_t)i * V + x] : 1.0) : 0.0;      // no q array: one-hot drafts (a deterministic drafter)
-            const double2 st = row_stat(stats, (int64_t)b * (k + 1) + i);
+            const double2 st = row_stat(stats, (int64_t)b * (k + 1) + i, rT);
             s_st[i] = st;
             if (probe) {
-                P = exp((double)lx / T - st.x) / st.y;
+                P = exp((double)lx / T - st.x / T) / st.y;
                 const Philox4 r = philox4x32_10(0u, (uint32_t)i, (uint32_t)b, step4 + 0u, seed_lo, seed_hi);
                 u = (double)(r.x >> 8) * (1.0 / 16777216.0);
                 ok = u * Q < P;
@@ -473,10 +491,11 @@ __global__ __launch_bounds__(SAMP_THREADS, 4) void draft_scan_kernel(
     const double2 c = stats[(int64_t)b * SAMP_PARTS + (lane & (SAMP_PARTS - 1))];
     double m = c.x;
     for (int off = SAMP_PARTS / 2; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off));
-    double S = c.y > 0.0 ? c.y * exp_sum(c.x - m) : 0.0;
+    double S = c.y > 0.0 ? c.y * exp_sum((c.x - m) * rT) : 0.0;
     for (int off = SAMP_PARTS / 2; off > 0; off >>= 1) S += __shfl_xor(S, off);
     const double rS = 1.0 / S;
-    const float rT2 = (float)(1.4426950408889634 / T), mx = (float)(m * T), rS32 = (float)rS;
+    const RaceExponent exponent((float)m, T);
+    const float rS32 = (float)rS;
     float reach = MAPPED ? 0.f : rS32 * (1.0f / 17.0f);             // as in race_scan (a map may leave out the most probable entry)
     int g0, g1;
     part_groups(V, part, &g0, &g1);
@@ -496,7 +515,7 @@ __global__ __launch_bounds__(SAMP_THREADS, 4) void draft_scan_kernel(
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const float lj = l[u][j];
-                const float pj = (float)(exp_sum(((double)lj - (double)mx) * rT) * rS);
+                const float pj = (float)(exp_sum(((double)lj - m) * rT) * rS);
                 p[j] = lj == lj ? pj : lj;
             }
             if (g < g1) {
@@ -514,7 +533,7 @@ __global__ __launch_bounds__(SAMP_THREADS, 4) void draft_scan_kernel(
                 }
             }
         }
-        race_round<RACE_PLAIN>(race, l, none, gb, g1, n_u, rT2, mx, rS32, reach, best, best_v);
+        race_round<RACE_PLAIN>(race, l, none, gb, g1, n_u, exponent, rS32, reach, best, best_v);
     }
     block_argmax(best, best_v, lk, lv);
     if (!merge_parts(parts + (int64_t)b * SAMP_PARTS, part, counters + b, best, best_v, &s_last)) return;
@@ -552,17 +571,17 @@ static spec_status reject_sample_launch(const char* who, int32_t B, int32_t k, i
     if (!dev_logits || !dev_accept_len || !dev_out_tokens || !ws || (k > 0 && !dev_draft_tokens)) {
         set_error("%s: null pointer", who); return SPEC_EINVAL;
     }
-    const double T = (double)temperature;
+    const double T = (double)temperature, rT = 1.0 / T;
     RacePart* parts = (RacePart*)((char*)ws + sample_stats_bytes((int64_t)B * (k + 1)));
     int32_t* counters = (int32_t*)((char*)parts + sample_parts_bytes(B));
     prof_mark(PC_OTHER, s);
     const bool vec = rows_vec(dev_logits, V, V) && (!dev_q || rows_vec(dev_q, V, V));
     const dim3 stat_grid((unsigned)(B * (k + 1)), SAMP_PARTS), grid((unsigned)B, SAMP_PARTS);
 #define SPEC_REJECT_LAUNCH(VECV) do { \
-        row_stats_kernel<VECV><<<stat_grid, SAMP_THREADS, 0, s>>>(dev_logits, (int64_t)V, V, T, 1.0 / T, stats, counters, k + 1); \
+        row_stats_kernel<VECV><<<stat_grid, SAMP_THREADS, 0, s>>>(dev_logits, (int64_t)V, V, rT, stats, counters, k + 1); \
         SPEC_LAUNCH_CHECK("row_stats_kernel"); \
         prof_mark(PC_SAMPLE_STATS, s); \
-        reject_scan_kernel<VECV><<<grid, SAMP_THREADS, 0, s>>>(k, V, dev_logits, dev_q, dev_draft_tokens, T, (uint32_t)seed, (uint32_t)(seed >> 32), \
+        reject_scan_kernel<VECV><<<grid, SAMP_THREADS, 0, s>>>(k, V, dev_logits, dev_q, dev_draft_tokens, T, rT, (uint32_t)seed, (uint32_t)(seed >> 32), \
                                                               (uint32_t)(step * 4u), stats, parts, counters, dev_accept_len, dev_out_tokens, dev_dbg); \
     } while (0)
     if (vec) SPEC_REJECT_LAUNCH(true); else SPEC_REJECT_LAUNCH(false);
@@ -659,7 +678,7 @@ static spec_status draft_sample_launch(const char* who, int32_t B, int32_t V, co
     const bool vec = rows_vec(dev_logits, logits_row_stride, V) && (dev_token_map || rows_vec(dev_q, q_row_stride, V));
     const dim3 grid((unsigned)B, SAMP_PARTS);
 #define SPEC_DRAFT_LAUNCH(VECV, MAPV) do { \
-        row_stats_kernel<VECV><<<grid, SAMP_THREADS, 0, s>>>(dev_logits, logits_row_stride, V, T, rT, stats, counters, 1, \
+        row_stats_kernel<VECV><<<grid, SAMP_THREADS, 0, s>>>(dev_logits, logits_row_stride, V, rT, stats, counters, 1, \
                                                             dev_token_map ? dev_q : nullptr, q_row_stride, q_width); \
         draft_scan_kernel<VECV, MAPV><<<grid, SAMP_THREADS, 0, s>>>(V, dev_logits, logits_row_stride, T, rT, (uint32_t)seed, (uint32_t)(seed >> 32), \
                                                              (uint32_t)(step * 4u), (uint32_t)row, stats, dev_q, q_row_stride, parts, counters, \

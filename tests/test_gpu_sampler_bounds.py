@@ -75,3 +75,70 @@ def test_draft_draw_at_the_limits_of_its_bounds(V, temperature, mapped):
     # q is an fp64 softmax rounded to fp32 on both sides: at most one unit apart (below the smallest normal number: flushed)
     got = q.cpu().numpy()
     assert np.all(np.abs(got - q_or) <= 2.0 ** -23 * q_or + 1.2e-38)
+
+
+def _run_one_hot(logits, draft, temperature, seed, step):
+    """No q array: one-hot drafts."""
+    from paper_2604_26779_amd import binding as sv
+    B, k1, V = logits.shape
+    dl, dd = torch.from_numpy(logits).cuda(), torch.from_numpy(draft).cuda()
+    n, out = torch.empty(B, dtype=torch.int32, device="cuda"), torch.empty((B, k1), dtype=torch.int32, device="cuda")
+    ws = torch.empty(sv.spec_sample_workspace_bytes(B, k1 - 1), dtype=torch.uint8, device="cuda")
+    sv.spec_reject_sample(B, k1 - 1, V, dl, None, dd, temperature, seed, step, n, out, None, ws)
+    return n.cpu().numpy(), out.cpu().numpy()
+
+
+def _check_draft_draw(logits, temperature, mapped):
+    from paper_2604_26779_amd import binding as sv
+    B, V = logits.shape
+    token_map = np.arange(V, dtype=np.int32) * 2 + 1
+    width = 2 * V + 1 if mapped else V
+    dl = torch.from_numpy(logits).cuda()
+    tok, q = torch.empty(B, dtype=torch.int32, device="cuda"), torch.full((B, width), -1.0, device="cuda")
+    if mapped:
+        sv.spec_draft_sample_mapped(B, V, dl, V, temperature, 5, 2, 1, tok, 1, None, 1, q, width, torch.from_numpy(token_map).cuda(), width)
+        x_or, q_or = oracle_sampler.draft_sample_mapped(logits, token_map, width, temperature, 5, 2, 1)[:2]
+    else:
+        sv.spec_draft_sample(B, V, dl, V, temperature, 5, 2, 1, tok, 1, None, 1, q, V)
+        x_or, q_or = oracle_sampler.draft_sample(logits, temperature, 5, 2, 1)[:2]
+    assert np.array_equal(tok.cpu().numpy(), x_or)
+    # q is an fp64 softmax rounded to fp32 on both sides: at most one unit apart (below the smallest normal number: flushed)
+    got = q.cpu().numpy()
+    assert np.all(np.abs(got - q_or) <= 2.0 ** -23 * q_or + 1.2e-38)
+
+
+# (temperature, spread of the logits): infinite; near fp32's largest number, with logits that still matter there; where log2(e) / T or T
+# itself leaves fp32's normal range, with logits of every size beside it
+EXTREME_T = [(np.inf, 3.0), (3e38, 5e37), (1e30, 3.0), (1e30, 1e30), (1e-37, 1e-37), (1e-38, 3.0), (1e-39, 2e-39), (1e-39, 3.0),
+             (1e-45, 3.0), (1e-45, 1e31)]
+
+
+@pytest.mark.parametrize("V", [1023, 16388])
+@pytest.mark.parametrize("temperature,spread", EXTREME_T)
+@pytest.mark.parametrize("draft_kind", ["explicit", "one-hot"])
+def test_reject_at_extreme_temperatures(V, temperature, spread, draft_kind):
+    B, k = 6, 2
+    rng = np.random.default_rng(V)
+    logits = (rng.standard_normal((B, k + 1, V)) * spread).astype(np.float32)
+    t64 = np.float64(np.float32(temperature))
+    q = _softmax((logits[:, :k].astype(np.float64) + rng.standard_normal((B, k, V)) * spread) / t64).astype(np.float32)
+    draft = rng.integers(0, V, size=(B, k)).astype(np.int32)
+    draft[:, 0] = logits[:, 0].argmax(-1)
+    if draft_kind == "one-hot":
+        q = np.zeros_like(q)
+        np.put_along_axis(q, draft[..., None], 1.0, -1)
+    n_or, out_or = oracle_sampler.reject_sample(logits, q, draft, temperature, 77, 4)
+    if draft_kind == "one-hot":
+        n_gpu, out_gpu = _run_one_hot(logits, draft, temperature, 77, 4)
+    else:
+        n_gpu, out_gpu, _ = _run_gpu(logits, q, draft, temperature, 77, 4)
+    assert np.array_equal(n_gpu, n_or) and np.array_equal(out_gpu, out_or)
+    assert np.all(np.take_along_axis(out_gpu, n_gpu[:, None].astype(np.int64), 1) >= 0)
+
+
+@pytest.mark.parametrize("V", [1023, 16388])
+@pytest.mark.parametrize("temperature,spread", EXTREME_T)
+@pytest.mark.parametrize("mapped", [False, True])
+def test_draft_draw_at_extreme_temperatures(V, temperature, spread, mapped):
+    rng = np.random.default_rng(V + 1)
+    _check_draft_draw((rng.standard_normal((5, V)) * spread).astype(np.float32), temperature, mapped)
