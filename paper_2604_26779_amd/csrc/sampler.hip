@@ -198,12 +198,15 @@ __global__ __launch_bounds__(SAMP_THREADS) void row_stats_kernel(const float* __
         for (int w = 0; w < SAMP_WAVES; ++w) M = fmax(M, l_st[w].x);
         for (int w = 0; w < SAMP_WAVES; ++w)
             if (l_st[w].y > 0.0) S += l_st[w].y * exp_sum((l_st[w].x - M) * rT);
+        if (M == INFINITY) S = 0.0;                                  // no distribution (see row_stat)
         stats[(int64_t)blockIdx.x * SAMP_PARTS + blockIdx.y] = make_double2(M, S);
     }
 }
 
 // a row's statistics from those of its ranges, in range order: M = max m_p, S = sum_p s_p exp((m_p - M) / T).  M stays a logit: M / T is
-// formed where it is needed, as M cannot be had back from it when T is infinite (0) or subnormal.
+// formed where it is needed, as M cannot be had back from it when T is infinite (0) or subnormal.  S = 0 says that the row has no
+// distribution: it is -inf throughout, or holds +inf (exp_sum gives such a row's terms the value of exp(-708), not NaN).  Its
+// probabilities are then NaN as 0 / 0 is: no accept test passes and no key is kept.
 __device__ inline double2 row_stat(const double2* __restrict__ stats, int64_t row, double rT)
 {
     double2 c[SAMP_PARTS];
@@ -215,7 +218,7 @@ __device__ inline double2 row_stat(const double2* __restrict__ stats, int64_t ro
     double S = 0.0;
 #pragma unroll
     for (int p = 0; p < SAMP_PARTS; ++p) S += c[p].y > 0.0 ? c[p].y * exp_sum((c[p].x - M) * rT) : 0.0;
-    return make_double2(M, S);
+    return make_double2(M, M == INFINITY ? 0.0 : S);
 }
 
 __device__ inline void argmax_merge(double& key, int& v, double key2, int v2)
@@ -493,7 +496,8 @@ __global__ __launch_bounds__(SAMP_THREADS, 4) void draft_scan_kernel(
     for (int off = SAMP_PARTS / 2; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off));
     double S = c.y > 0.0 ? c.y * exp_sum((c.x - m) * rT) : 0.0;
     for (int off = SAMP_PARTS / 2; off > 0; off >>= 1) S += __shfl_xor(S, off);
-    const double rS = 1.0 / S;
+    if (m == INFINITY) S = 0.0;
+    const double rS = S > 0.0 ? 1.0 / S : NAN;                      // without a distribution q is NaN, and the verifier rejects the -1 drawn from it
     const RaceExponent exponent((float)m, T);
     const float rS32 = (float)rS;
     float reach = MAPPED ? 0.f : rS32 * (1.0f / 17.0f);             // as in race_scan (a map may leave out the most probable entry)
@@ -514,9 +518,9 @@ __global__ __launch_bounds__(SAMP_THREADS, 4) void draft_scan_kernel(
             float p[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const float lj = l[u][j];
-                const float pj = (float)(exp_sum(((double)lj - m) * rT) * rS);
-                p[j] = lj == lj ? pj : lj;
+                const double x = ((double)l[u][j] - m) * rT;
+                const float pj = (float)(exp_sum(x) * rS);
+                p[j] = x == x ? pj : NAN;                           // a NaN logit (and -inf at an infinite T)
             }
             if (g < g1) {
                 if constexpr (VEC && !MAPPED) {

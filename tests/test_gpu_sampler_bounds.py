@@ -142,3 +142,60 @@ def test_reject_at_extreme_temperatures(V, temperature, spread, draft_kind):
 def test_draft_draw_at_extreme_temperatures(V, temperature, spread, mapped):
     rng = np.random.default_rng(V + 1)
     _check_draft_draw((rng.standard_normal((5, V)) * spread).astype(np.float32), temperature, mapped)
+
+
+@pytest.mark.parametrize("V", [3, 1023, 16388, 70000])
+@pytest.mark.parametrize("temperature", [0.7, np.inf])
+@pytest.mark.parametrize("row", ["+inf", "all -inf"])
+@pytest.mark.parametrize("mapped", [False, True])
+def test_draft_row_without_a_distribution_gives_nan_and_is_rejected(V, temperature, row, mapped):
+    """A draft that overflowed: token -1 and a q of NaN, not numbers that look like probabilities; the verifier then rejects the -1 and
+    emits from the target's own distribution (for NaN the residual is identically zero)."""
+    from paper_2604_26779_amd import binding as sv
+    B = 3
+    rng = np.random.default_rng(V)
+    logits = (rng.standard_normal((B, V)) * 3).astype(np.float32)
+    good = logits.copy()
+    logits[1] = -np.inf if row == "all -inf" else logits[1]
+    if row == "+inf":
+        logits[1, rng.integers(0, V)] = np.inf
+    dl = torch.from_numpy(logits).cuda()
+    tok, q = torch.empty(B, dtype=torch.int32, device="cuda"), torch.full((B, V), -1.0, device="cuda")
+    if mapped:
+        sv.spec_draft_sample_mapped(B, V, dl, V, temperature, 5, 2, 1, tok, 1, None, 1, q, V, torch.arange(V, dtype=torch.int32, device="cuda"), V)
+    else:
+        sv.spec_draft_sample(B, V, dl, V, temperature, 5, 2, 1, tok, 1, None, 1, q, V)
+    got = q.cpu().numpy()
+    assert tok[1].item() == -1 and np.all(np.isnan(got[1]))
+    x_or, q_or = oracle_sampler.draft_sample(good, temperature, 5, 2, 1)
+    for b in (0, 2):
+        assert tok[b].item() == x_or[b] and np.all(np.abs(got[b] - q_or[b]) <= 2.0 ** -23 * q_or[b] + 1.2e-38)
+    target = (rng.standard_normal((B, 2, V)) * 3).astype(np.float32)
+    draft = tok.cpu().numpy().reshape(B, 1)
+    n_gpu, out_gpu, _ = _run_gpu(target, got.reshape(B, 1, V), draft, temperature, 77, 4)
+    n_or, out_or = oracle_sampler.reject_sample(target, got.reshape(B, 1, V), np.maximum(draft, 0), temperature, 77, 4)
+    assert n_gpu[1] == 0 and np.array_equal(n_gpu, n_or) and np.array_equal(out_gpu, out_or)
+
+
+@pytest.mark.parametrize("V", [3, 1023, 16388])
+@pytest.mark.parametrize("mask", [-np.inf, np.finfo(np.float32).min])
+@pytest.mark.parametrize("kept", [1, 2, 700])
+def test_masked_rows(V, mask, kept):
+    """Rows masked with -inf or with the type's lowest value but for a few entries, one of them wholly -inf in some ranges of the scan;
+    a target row that is -inf throughout, or holds +inf, emits -1 as the oracle does."""
+    B, k = 5, 2
+    rng = np.random.default_rng(V + kept)
+    logits = np.full((B, k + 1, V), mask, dtype=np.float32)
+    for b in range(B):
+        for i in range(k + 1):
+            at = rng.permutation(V)[:kept]
+            logits[b, i, at] = rng.standard_normal(len(at)) * 3
+    for b, x in ((3, np.inf), (4, -np.inf)):
+        logits[b, 0, :] = -np.inf
+        logits[b, 0, V // 2] = x
+    draft = logits[:, :k].argmax(-1).astype(np.int32)
+    q = np.full((B, k, V), 1.0 / V, dtype=np.float32)
+    n_or, out_or = oracle_sampler.reject_sample(logits, q, draft, 0.7, 77, 4)
+    n_gpu, out_gpu, _ = _run_gpu(logits, q, draft, 0.7, 77, 4)
+    assert np.array_equal(n_gpu, n_or) and np.array_equal(out_gpu, out_or)
+    assert np.all(out_gpu[3:, 0] == -1)
