@@ -127,6 +127,12 @@ __device__ inline void load_round(const float* __restrict__ row, int gb, int g1,
 // whether every row of an array can be read in 16-byte words
 static bool rows_vec(const void* rows, int64_t stride, int V) { return ((uintptr_t)rows & 15) == 0 && (stride & 3) == 0 && (V & 3) == 0; }
 
+// a value that every lane holds alike, in scalar registers: the scans have none of the vector ones to spare
+__device__ inline double uniform(double x)
+{
+    return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(x)), __builtin_amdgcn_readfirstlane(__double2loint(x)));
+}
+
 // groups per lane that the round starting at group gb holds (the same for a wavefront)
 __device__ inline int round_groups(int gb, int g1)
 {
@@ -252,6 +258,7 @@ __device__ inline float race_scale(uint32_t word)
 // Weights of a race over one row: RACE_PLAIN p; RACE_RES max(0, p - q); RACE_HOT p except 0 at the token `hot` (the residual
 // of a one-hot draft distribution).  race_key: the exact key of entry v, fp64, -1 where the weight is not positive.
 constexpr int RACE_PLAIN = 0, RACE_RES = 1, RACE_HOT = 2;
+constexpr double RACE_SOME = -0.5;            // in the place of a best key: nothing was found, but an entry below `reach` may have a positive weight
 struct RaceRow {                              // one race: the row, its largest logit and sum, the random stream
     const float *l, *q;
     int V, hot;
@@ -272,12 +279,16 @@ __device__ inline double race_key(const RaceRow& r, int v)
 }
 
 // One round of a race, SAMP_GPT groups per lane: keeps in `best` / `best_v` the exact winner among the lane's entries that may win.
-// reach: the largest lower bound of a key that this wavefront has met (or knows to exist elsewhere).
+// reach: the largest lower bound of a key that this wavefront has met, or that is known or supposed of the row.  A race starts from a
+// bound of the whole row: without one a wavefront that holds only keys below the fp32 range's end would evaluate all of them, and with
+// peaked logits (a largest logit of 25 over a spread of 2 at T = 0.2) that is nearly every wavefront.  Draw of 256 rows, V = 128256, such
+// logits, no bound / a bound: rejected explicit draft 474 / 220 us a call, one-hot 459 / 203, mapped draw of 32000 138 / 87.
 // The exponent (l - mx) log2(e) / T, mx the row's largest logit, carries three fp32 roundings (RaceExponent): 126 * 3 * 2^-24 = 2.3e-5 at most
 // where the exponential is a normal number, so the fp32 probability is off by less than RACE_EPS of itself, the scale of
 // race_scale included.  Below that it counts as 0 with an upper bound of RACE_TINY: such an entry matters only if nothing clear of
-// the fp32 range's end competes, and then (bar = 0) every entry is evaluated.
-constexpr float RACE_EPS = 4.0e-5f, RACE_TINY = 1.2e-38f;
+// the fp32 range's end competes (RACE_FLOOR, some way above RACE_TINY times the largest scale, 1.7e7); without such a key every
+// entry that may have a positive weight is evaluated (bar = 0).
+constexpr float RACE_EPS = 4.0e-5f, RACE_TINY = 1.2e-38f, RACE_FLOOR = 1.0e-30f;
 
 // log2 of an entry's probability times S: (l c - mx c) * (log2(e) / (T c)), the first term one fused instruction.  c is a power of two
 // (1 for the usual temperatures) that keeps every term inside fp32's range for every T > 0, infinite and subnormal ones too:
@@ -300,6 +311,7 @@ __device__ inline void race_round(const RaceRow& row, const float (&l)[SAMP_GPT]
                                   const RaceExponent& exponent, float rS, float& reach, double& best, int& best_v)
 {
     const int lane = threadIdx.x & 63;
+    const float reach0 = reach;
     float key[SAMP_GPT][4];                                          // the residual races': upper bounds; the plain race's: the fp32 keys
     float lo_max = 0.f;
 #pragma unroll
@@ -328,7 +340,7 @@ __device__ inline void race_round(const RaceRow& row, const float (&l)[SAMP_GPT]
     }
     for (int off = 32; off > 0; off >>= 1) lo_max = fmaxf(lo_max, __shfl_xor(lo_max, off));
     reach = fmaxf(reach, lo_max);
-    const float bar = reach > 1.0e-30f ? reach * (1.0f - (KIND == RACE_PLAIN ? 3.0f : 1.0f) * RACE_EPS) : 0.f;
+    const float bar = reach >= RACE_FLOOR ? reach * (1.0f - (KIND == RACE_PLAIN ? 3.0f : 1.0f) * RACE_EPS) : 0.f;
     unsigned int may_win = 0;
 #pragma unroll
     for (int u = 0; u < SAMP_GPT; ++u)
@@ -342,17 +354,24 @@ __device__ inline void race_round(const RaceRow& row, const float (&l)[SAMP_GPT]
         const double k = race_key<KIND>(row, v);
         argmax_merge(best, best_v, k, k > 0.0 ? v : -1);
     }
+    if (KIND != RACE_PLAIN && reach == reach0) {
+        bool some = false;
+#pragma unroll
+        for (int u = 0; u < SAMP_GPT; ++u)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) some |= key[u][j] >= 0.f;
+        if (some) best = fmax(best, RACE_SOME);
+    }
 }
 
-// Exponential race over the groups [g0, g1) of one row, all SAMP_THREADS threads; every lane's best entry.
+// Exponential race over the groups [g0, g1) of one row, all SAMP_THREADS threads; every lane's best entry.  No key below `reach` is
+// certain to be found: the caller looks again with a lower one where the row's best turns out to lie below.
 template <int KIND, bool VEC>
-__device__ inline void race_scan(const RaceRow& row, int g0, int g1, double& best, int& best_v)
+__device__ inline void race_scan(const RaceRow& row, int g0, int g1, float reach, double& best, int& best_v)
 {
     const int wave = threadIdx.x >> 6;
     const RaceExponent exponent((float)row.max_l, row.T);
     const float rS = (float)(1.0 / row.S);
-    // the entry with the largest p, 1 / S, has a key of at least 1 / (17 S) (-ln u is at most 16.7): nothing below wins the plain race
-    float reach = KIND == RACE_PLAIN ? rS * (1.0f / 17.0f) : 0.f;
     for (int gb = g0 + wave * 64; gb < g1; gb += SAMP_THREADS * SAMP_GPT) {
         float l[SAMP_GPT][4], qv[SAMP_GPT][4];
         load_round<VEC>(row.l, gb, g1, row.V, -INFINITY, l);
@@ -360,6 +379,9 @@ __device__ inline void race_scan(const RaceRow& row, int g0, int g1, double& bes
         race_round<KIND>(row, l, qv, gb, g1, round_groups(gb, g1), exponent, rS, reach, best, best_v);
     }
 }
+
+// a key that the plain race over a row of sum S surely holds
+__device__ inline float race_known(double S) { return (float)(1.0 / S) * (1.0f / 17.0f); }
 
 // what a range's workgroup hands to the merge: its best (key, token) of the race
 struct RacePart { double key; int64_t v; };
@@ -443,28 +465,32 @@ __global__ __launch_bounds__(SAMP_THREADS, 4) void reject_scan_kernel(
         if (i == 0) s_n = n;
     }
     __syncthreads();
-    const int n = s_n;
-    const double2 st = s_st[n];
+    const int n = __builtin_amdgcn_readfirstlane(s_n);
+    const double2 st = make_double2(uniform(s_st[n].x), uniform(s_st[n].y));
     const float* lrow = L + (int64_t)n * V;
     int g0, g1;
     part_groups(V, part, &g0, &g1);
     double best = -1.0;
     int best_v = -1;
-    RaceRow row = {lrow, Qb ? Qb + (int64_t)n * V : nullptr, V, -1, T, st.x, st.y, seed_lo, seed_hi, (uint32_t)n, (uint32_t)b, step4 + 1u};
-    if (n < k && Qb) {
-        race_scan<RACE_RES, VEC>(row, g0, g1, best, best_v);
-    } else if (n < k) {
-        row.hot = draft[(int64_t)b * k + n];
-        race_scan<RACE_HOT, VEC>(row, g0, g1, best, best_v);
-    } else {
-        race_scan<RACE_PLAIN, VEC>(row, g0, g1, best, best_v);
-    }
-    block_argmax(best, best_v, lk, lv);
-    if (!merge_parts(parts + (int64_t)b * SAMP_PARTS, part, counters + b, best, best_v, &s_last)) return;
-    if (n < k && best_v < 0) {
-        // the residual is identically zero: the token comes from the plain race over the whole row
-        race_scan<RACE_PLAIN, VEC>(row, 0, (V + 3) >> 2, best, best_v);
+    RaceRow row = {lrow, Qb ? Qb + (int64_t)n * V : nullptr, V, n < k && !Qb ? draft[(int64_t)b * k + n] : -1, T, st.x, st.y,
+                   seed_lo, seed_hi, (uint32_t)n, (uint32_t)b, step4 + 1u};
+    // The plain race: the entry with the largest p, 1 / S, has a key of at least 1 / (17 S) (-ln u is at most 16.7).  The residual races
+    // have no such entry, but a draft is rejected where q exceeds p by at least 2^-24 q, and a q of sum 1 leaves as much residual elsewhere:
+    // keys above RACE_FLOOR are to be expected.  Where there are none the workgroup that finishes the sequence looks again at
+    // everything positive (a q that left nothing but such weights: 393 us a call of 64 rows, 75 otherwise), and if there is nothing (a
+    // residual identically zero) the token comes from the plain race.
+    int kind = n == k ? RACE_PLAIN : Qb ? RACE_RES : RACE_HOT;
+    float known = kind == RACE_PLAIN ? race_known(st.y) : RACE_FLOOR;
+    for (bool whole = false;; whole = true) {
+        if (whole) { g0 = 0; g1 = (V + 3) >> 2; }
+        if (kind == RACE_RES) race_scan<RACE_RES, VEC>(row, g0, g1, known, best, best_v);
+        else if (kind == RACE_HOT) race_scan<RACE_HOT, VEC>(row, g0, g1, known, best, best_v);
+        else race_scan<RACE_PLAIN, VEC>(row, g0, g1, known, best, best_v);
         block_argmax(best, best_v, lk, lv);
+        if (!whole && !merge_parts(parts + (int64_t)b * SAMP_PARTS, part, counters + b, best, best_v, &s_last)) return;
+        if (kind == RACE_PLAIN || (best_v >= 0 && best >= (double)known)) break;
+        if (known > 0.f && best >= RACE_SOME) known = 0.f;
+        else { kind = RACE_PLAIN; known = race_known(st.y); }
     }
     if (threadIdx.x == 0) accept_len[b] = n;
     for (int i = threadIdx.x; i <= k; i += SAMP_THREADS) out_tokens[(int64_t)b * (k + 1) + i] = i < n ? draft[(int64_t)b * k + i] : (i == n ? best_v : -1);
@@ -496,51 +522,59 @@ __global__ __launch_bounds__(SAMP_THREADS, 4) void draft_scan_kernel(
     for (int off = SAMP_PARTS / 2; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off));
     double S = c.y > 0.0 ? c.y * exp_sum((c.x - m) * rT) : 0.0;
     for (int off = SAMP_PARTS / 2; off > 0; off >>= 1) S += __shfl_xor(S, off);
-    if (m == INFINITY) S = 0.0;
+    m = uniform(m);
+    S = m == INFINITY ? 0.0 : uniform(S);
     const double rS = S > 0.0 ? 1.0 / S : NAN;                      // without a distribution q is NaN, and the verifier rejects the -1 drawn from it
     const RaceExponent exponent((float)m, T);
     const float rS32 = (float)rS;
-    float reach = MAPPED ? 0.f : rS32 * (1.0f / 17.0f);             // as in race_scan (a map may leave out the most probable entry)
+    float reach = race_known(S);
+    const float known = reach;
     int g0, g1;
     part_groups(V, part, &g0, &g1);
     double best = -1.0;
     int best_v = -1;
     const float none[SAMP_GPT][4] = {};
     const RaceRow race = {lrow, nullptr, V, -1, T, m, S, seed_lo, seed_hi, row, (uint32_t)b, step4 + 2u};
-    for (int gb = g0 + wave * 64; gb < g1; gb += SAMP_THREADS * SAMP_GPT) {
-        float l[SAMP_GPT][4];
-        const int n_u = round_groups(gb, g1);
-        load_round<VEC>(lrow, gb, g1, V, -INFINITY, l);
+    for (bool whole = false;; whole = true) {
+        if (MAPPED && whole) { g0 = 0; g1 = (V + 3) >> 2; reach = 0.f; }
+        for (int gb = g0 + wave * 64; gb < g1; gb += SAMP_THREADS * SAMP_GPT) {
+            float l[SAMP_GPT][4];
+            const int n_u = round_groups(gb, g1);
+            load_round<VEC>(lrow, gb, g1, V, -INFINITY, l);
 #pragma unroll
-        for (int u = 0; u < SAMP_GPT; ++u) {
-            if (u >= n_u) break;
-            const int g = gb + u * SAMP_THREADS + lane;
-            float p[4];
+            for (int u = 0; u < SAMP_GPT; ++u) {
+                if (u >= n_u) break;
+                const int g = gb + u * SAMP_THREADS + lane;
+                float p[4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const double x = ((double)l[u][j] - m) * rT;
-                const float pj = (float)(exp_sum(x) * rS);
-                p[j] = x == x ? pj : NAN;                           // a NaN logit (and -inf at an infinite T)
-            }
-            if (g < g1) {
-                if constexpr (VEC && !MAPPED) {
-                    *(float4*)(qrow + 4 * (int64_t)g) = make_float4(p[0], p[1], p[2], p[3]);
-                } else {
+                for (int j = 0; j < 4; ++j) {
+                    const double x = ((double)l[u][j] - m) * rT;
+                    const float pj = (float)(exp_sum(x) * rS);
+                    p[j] = x == x ? pj : NAN;                           // a NaN logit (and -inf at an infinite T)
+                }
+                if (g < g1) {
+                    if constexpr (VEC && !MAPPED) {
+                        *(float4*)(qrow + 4 * (int64_t)g) = make_float4(p[0], p[1], p[2], p[3]);
+                    } else {
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const int v = 4 * g + j;
-                        if (v >= V) continue;
-                        const int at = MAPPED ? token_map[v] : v;                               // (a mapped row was cleared by the statistics kernel)
-                        if (MAPPED && (unsigned)at >= (unsigned)q_width) l[u][j] = -INFINITY;    // outside the target's vocabulary: never written, never drawn
-                        else qrow[at] = p[j];
+                        for (int j = 0; j < 4; ++j) {
+                            const int v = 4 * g + j;
+                            if (v >= V) continue;
+                            const int at = MAPPED ? token_map[v] : v;                               // (a mapped row was cleared by the statistics kernel)
+                            if (MAPPED && (unsigned)at >= (unsigned)q_width) l[u][j] = -INFINITY;    // outside the target's vocabulary: never written, never drawn
+                            else qrow[at] = p[j];
+                        }
                     }
                 }
             }
+            race_round<RACE_PLAIN>(race, l, none, gb, g1, n_u, exponent, rS32, reach, best, best_v);
         }
-        race_round<RACE_PLAIN>(race, l, none, gb, g1, n_u, exponent, rS32, reach, best, best_v);
+        block_argmax(best, best_v, lk, lv);
+        if (!whole && !merge_parts(parts + (int64_t)b * SAMP_PARTS, part, counters + b, best, best_v, &s_last)) return;
+        // a map may leave out the most probable entry, and then there may be no key of that size: once more, over the whole row (q is written
+        // again with the same values)
+        if (!MAPPED || whole || best >= (double)known) break;
     }
-    block_argmax(best, best_v, lk, lv);
-    if (!merge_parts(parts + (int64_t)b * SAMP_PARTS, part, counters + b, best, best_v, &s_last)) return;
     if (threadIdx.x == 0) {
         if (MAPPED && best_v >= 0) best_v = token_map[best_v];
         if (tok_a) tok_a[(int64_t)b * stride_a] = best_v;

@@ -199,3 +199,61 @@ def test_masked_rows(V, mask, kept):
     n_gpu, out_gpu, _ = _run_gpu(logits, q, draft, 0.7, 77, 4)
     assert np.array_equal(n_gpu, n_or) and np.array_equal(out_gpu, out_or)
     assert np.all(out_gpu[3:, 0] == -1)
+
+
+@pytest.mark.parametrize("V", [1023, 16388, 70000])
+@pytest.mark.parametrize("draft_kind", ["elsewhere", "top", "one-hot", "tiny residual", "tiny residual in one range"])
+def test_reject_races_of_peaked_rows(V, draft_kind):
+    """A few entries far above the rest, whose weights lie below fp32's range, and residuals of nothing but such weights: the race's
+    supposed lower bound holds, or does not and everything is looked at again."""
+    B, k, temperature = 6, 2, 0.2
+    rng = np.random.default_rng(V)
+    logits = (rng.standard_normal((B, k + 1, V)) * 2).astype(np.float32)
+    top = rng.integers(0, V, size=(B, k + 1))
+    np.put_along_axis(logits, top[..., None], 25.0, -1)
+    p = _softmax(logits[:, :k].astype(np.float64) / temperature)
+    draft = rng.integers(0, V, size=(B, k)).astype(np.int32)
+    q = np.zeros((B, k, V), dtype=np.float32)
+    if draft_kind == "elsewhere" or draft_kind == "one-hot":
+        np.put_along_axis(q, draft[..., None], 1.0, -1)
+    elif draft_kind == "top":                      # rejected at the top entry: what is left is of the order of 1e-35 and below
+        draft = top[:, :k].astype(np.int32)
+        np.put_along_axis(q, draft[..., None], np.float32(3e8), -1)
+    else:                                          # q covers everything but entries of tiny weight
+        q = (1.5 * p + 1e-20).astype(np.float32)
+        if draft_kind == "tiny residual":
+            q[p < 1e-31] = 0.0
+        else:
+            q[..., V - 300:][p[..., V - 300:] < 1e-31] = 0.0
+        draft = top[:, :k].astype(np.int32)
+        np.put_along_axis(q, draft[..., None], np.float32(3e8), -1)
+    n_or, out_or = oracle_sampler.reject_sample(logits, q, draft, temperature, 77, 4)
+    if draft_kind == "one-hot":
+        n_gpu, out_gpu = _run_one_hot(logits, draft, temperature, 77, 4)
+    else:
+        n_gpu, out_gpu, _ = _run_gpu(logits, q, draft, temperature, 77, 4)
+    assert np.array_equal(n_gpu, n_or) and np.array_equal(out_gpu, out_or)
+
+
+@pytest.mark.parametrize("V", [1023, 16388, 70000])
+@pytest.mark.parametrize("top", [25.0, 60.0])
+def test_draft_draw_whose_map_leaves_out_the_top(V, top):
+    """The most probable entry maps outside the target's vocabulary: the draw is decided among keys far below the bound it gives."""
+    from paper_2604_26779_amd import binding as sv
+    B, temperature = 4, 0.2
+    rng = np.random.default_rng(V)
+    logits = (rng.standard_normal((B, V)) * 2).astype(np.float32)
+    logits[:, V // 3] = top
+    token_map = np.arange(V, dtype=np.int32)
+    token_map[V // 3] = V + 5
+    tok, q = torch.empty(B, dtype=torch.int32, device="cuda"), torch.full((B, V), -1.0, device="cuda")
+    sv.spec_draft_sample_mapped(B, V, torch.from_numpy(logits).cuda(), V, temperature, 5, 2, 1, tok, 1, None, 1, q, V,
+                                torch.from_numpy(token_map).cuda(), V)
+    p = _softmax(logits.astype(np.float64) / temperature)
+    for b in range(B):
+        key = np.array([p[b, v] / -np.log(oracle_sampler.uniform_draft(5, 2, b, 1, v)) for v in range(V)])
+        key[V // 3] = -1.0
+        assert tok[b].item() == int(key.argmax())
+    want = p.copy()
+    want[:, V // 3] = 0.0
+    assert np.all(np.abs(q.cpu().numpy() - want) <= 2.0 ** -23 * want + 1.2e-38)
