@@ -28,7 +28,7 @@ static std::map<std::string, int>& tune_table()
     // launch parameters with their defaults; see gemm_bf16.hip / attn_bf16.hip for their meaning
     static std::map<std::string, int> t = {
         {"gemm_wg_target", 256},   // split K while a GEMM launches fewer workgroups than this
-        {"fuse_swiglu", 1},        // 1: silu(gate) * up in the gate/up projection's epilogue (unsplit K, even row blocks)
+        {"fuse_swiglu", 1},        // 1: silu(gate) * up in the gate/up projection's epilogue, where K is unsplit
         {"attn_row_blocks", 0},    // most 16-row blocks per attention workgroup (1..4; 0 = up to 4, groups as equal as possible)
         {"gemm_max_mb", 4},        // 32-row blocks per GEMM tile (1..4): smaller tiles = more workgroups, weights read once per tile
         {"gemm_split_rows", 2},     // GEMMs of up to this many 128-row tiles (97..256 rows at 2) run as 64-row x 256-column tiles instead (0 = never)
@@ -39,7 +39,7 @@ static std::map<std::string, int>& tune_table()
         {"moe_wide_tiles", 1},      // grouped expert GEMMs: 64 x 256 tiles, wavefronts 1 x 4 (0: 64 x 128, wavefronts 2 x 2)
         {"gemm_big_min_blocks", 5}, // from this many 32-row blocks on, a GEMM may take 192/256-row x 256-column tiles (0 = never)
         {"gemm_min_ksteps", 32},   // never split below this many 16-wide k-steps per workgroup
-        {"splits_qkv", 0}, {"splits_o", 0}, {"splits_gu", 0}, {"splits_down", 0}, {"splits_head", 0},   // 0 = auto
+        {"splits_qkv", 0}, {"splits_o", 0}, {"splits_gu", 0}, {"splits_down", 0}, {"splits_head", 0},   // 0 = auto (splits_gu: a gate/up projection of an even row-block count never splits K while fuse_swiglu is on)
         {"attn_chunk_pages", 0},   // KV pages per attention workgroup (a multiple of 4 up to 256; 0 = chosen on the device from the batch's contexts)
         {"attn_rounds", 1},        // the attention's work list is cut to fill the chip's resident workgroups this many times over (B=32, contexts 1k..8k: 3.41 ms of attention per step at 1, 3.54 at 2, 3.60 at 3)
         {"attn_min_pages", 16},    // shortest chunk the device-side choice may take (pages)

@@ -589,20 +589,21 @@ int gemm_pick_splits(const PackedW& W, int M, int forced)
     return (int)cdiv(W.k_steps, kps);
 }
 
-// out must hold splits * M * ldo floats; with swiglu (gate/up projection, splits == 1, an even number
-// of row blocks) out is instead the hi + lo operand buffer of silu(gate) * up, [N/2] channels wide.
-// Returns SPEC_EUNSUPPORTED (nothing launched) if swiglu is asked for a shape it cannot fuse.
+// Whether the gate/up projection forms silu(gate) * up in its epilogue.
 bool gemm_can_fuse_swiglu(const PackedW& W, int M, int splits)
 {
     if (splits != 1) return false;
     const GemmShape g = gemm_shape(W, M, true);
-    // odd row-block counts (a tile with one column block per wavefront): where K would not be split anyway - with few column
-    // tiles the split projection and its pass over the slices keep more of the chip busy.  (At 4 rows of the 8B shape the fused
-    // launch takes the 37.5 us of the plain one and saves the 4.6 us pass per layer.)
-    if (g.mb % 2 != 0 && !g.wide) return gemm_pick_splits(W, M, 0) == 1;
+    // odd row-block counts (a tile with one column block per wavefront): where K would not be split anyway, by the tile count or by
+    // splits_gu - with few column tiles the split projection and its pass over the slices keep more of the chip busy.  (At 4 rows of
+    // the 8B shape the fused launch takes the 37.5 us of the plain one and saves the 4.6 us pass per layer.)
+    if (g.mb % 2 != 0 && !g.wide) return gemm_pick_splits(W, M, tune("splits_gu")) == 1;
     return true;
 }
 
+// out must hold splits * M * ldo floats; with swiglu (gate/up projection, splits == 1) out is instead the operand buffer of
+// silu(gate) * up, [N/2] channels wide, in the format the matrix takes (hi + lo or fp16).
+// Returns SPEC_EUNSUPPORTED (nothing launched) if swiglu is asked for a shape it cannot fuse.
 spec_status launch_gemm_bf16(const PackedW& W, const bf16_t* Xp, int M, float* out, int ldo, int splits, bool swiglu, hipStream_t s)
 {
     const GemmShape g = gemm_shape(W, M, swiglu);

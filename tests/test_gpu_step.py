@@ -687,3 +687,43 @@ def test_f32_projections_few_and_many_rows(B, k, changes):
     ok, max_err, worst = _run_custom_bf16(ctx, k=k, seed=B + k, **cfg)
     print("fp32 B=%d k=%d %s: logits max abs err %.3e" % (B, k, changes, max_err))
     assert ok and max_err <= 1e-4, (max_err, worst)
+
+
+def _with_tune(want, fn):
+    from paper_2604_26779_amd import binding as sv
+    before = {n: sv.spec_tune_get(n) for n in want}
+    try:
+        for n, v in want.items():
+            sv.spec_tune_set(n, v)
+        return fn()
+    finally:
+        for n, v in before.items():
+            sv.spec_tune_set(n, v)
+
+
+@pytest.mark.parametrize("f16_inputs", [12, 0])
+@pytest.mark.parametrize("B,k", [(1, 0), (8, 3), (16, 3), (12, 7)])
+@pytest.mark.parametrize("how", ["fuse_swiglu off", "K split by the tile count", "K split by splits_gu"])
+def test_bf16_separate_swiglu_pass(B, k, f16_inputs, how):
+    """The SwiGLU as a pass of its own, over one slice of the gate/up projection or the sum of two: M = 1, 32, 64 and 96 rows."""
+    want = {"fuse_swiglu off": {"fuse_swiglu": 0}, "K split by the tile count": {"gemm_min_ksteps": 16},
+            "K split by splits_gu": {"gemm_min_ksteps": 16, "gemm_wg_target": 1, "splits_gu": 2}}[how]
+    rng = np.random.default_rng(B * 10 + k)
+    ctx = [int(c) for c in rng.integers(3, 120, size=B)]
+    ok, max_err, worst = _with_tune(dict(want, gemm_f16_inputs=f16_inputs), lambda: _run_custom_bf16(ctx, k=k, seed=B + k, vocab=1000))
+    print("M=%d, fp16 inputs %d, %s: logits max abs err %.3e" % (B * (k + 1), f16_inputs, how, max_err))
+    assert ok, (max_err, worst)
+
+
+@pytest.mark.parametrize("B,k", [(1, 0), (8, 3), (12, 7)])
+def test_splits_gu_is_honoured_at_odd_row_block_counts(B, k):
+    """M = 1, 32 and 96 rows: splits_gu = 2 takes two slices of the gate/up projection (the workspace holds them), also where the tile
+    count alone would not split K."""
+    from paper_2604_26779_amd import binding as sv
+    from paper_2604_26779_amd.session import VerifySession
+    cfg = si.MODELS["small_bf16"]
+    sess = VerifySession(cfg, si.make_weights(cfg, seed=1, device="cuda"), max_seqs=B, max_ctx_len=64, n_pages=64)
+    base = {"gemm_min_ksteps": 16, "gemm_wg_target": 1, "splits_qkv": 1, "splits_o": 1, "splits_down": 1}
+    size = {n: _with_tune(dict(base, splits_gu=n), lambda: sv.spec_verify_workspace_bytes(sess.model, sess.kv, B, k)) for n in (1, 2)}
+    sess.close()
+    assert abs(size[2] - size[1] - B * (k + 1) * 2 * cfg["ffn_dim"] * 4) < 256
