@@ -257,6 +257,7 @@ static spec_status launch_one(const PackedW& W, const bf16_t* Xp, int M, int mb_
     if (raised != hipSuccess) { set_error("gemm: cannot reserve %d bytes of LDS: %s", lds_bytes, hipGetErrorString(raised)); return SPEC_EHIP; }
     kern<<<grid, GEMM_THREADS, lds_bytes, s>>>((const u32x4_t*)W.data, (const u32x4_t*)Xp, out, W.n_blocks, W.k_steps, kps, mb_pad, M, W.N, ldo,
                                                (int64_t)M * ldo, W.scale);
+    SPEC_LAUNCH_CHECK("gemm_big_kernel");
     return SPEC_OK;
 }
 

@@ -126,3 +126,19 @@ def test_argument_checks_of_the_rollout_side_calls(sv):
     assert sv.spec_model_weight_count(dict(fused, fuse_taps=3)) == 1 + 9 + 1 + 3 + 1
     # a head over a subset of the vocabulary is a matrix of its own
     assert sv.spec_model_weight_count(dict(fused, fuse_taps=3, tied_head=0, head_vocab=6)) == 1 + 9 + 1 + 1 + 3 + 1
+
+
+def test_every_launch_is_checked_where_it_is_made():
+    """A function that launches kernels and returns a status reads the launch status before it returns: a refused launch is reported as
+    such, by name, and not by a later call."""
+    csrc = os.path.join(ROOT, "paper_2604_26779_amd", "csrc")
+    seen, unchecked = 0, []
+    for src in sorted(f for f in os.listdir(csrc) if f.endswith(".hip")):
+        text = open(os.path.join(csrc, src)).read()
+        for m in re.finditer(r'^(?:extern "C" |static )?spec_status (\w+)\([^;{]*\)\n\{\n(.*?)^\}', text, flags=re.S | re.M):
+            name, body = m.groups()
+            if "<<<" in body:
+                seen += 1
+                if "SPEC_LAUNCH_CHECK" not in body[body.rindex("<<<"):]:
+                    unchecked.append("%s: %s" % (src, name))
+    assert seen >= 20 and not unchecked, unchecked
