@@ -18,6 +18,7 @@
 
 #include "common.h"
 #include "gemm_common.h"
+#include "lds_limit.h"
 #include "operand.h"
 
 namespace specv {
@@ -253,7 +254,8 @@ static spec_status launch_one(const PackedW& W, const bf16_t* Xp, int M, int mb_
 {
     auto kern = gemm_big_kernel<MB, EPI, W8, XF>;
     constexpr int lds_bytes = GemmBig<MB, EPI, W8, XF>::LDS_BYTES;        // beyond the 64 KiB a kernel gets by default
-    static const hipError_t raised = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+    static LdsLimit limit;
+    const hipError_t raised = limit.raise((const void*)kern, lds_bytes);
     if (raised != hipSuccess) { set_error("gemm: cannot reserve %d bytes of LDS: %s", lds_bytes, hipGetErrorString(raised)); return SPEC_EHIP; }
     kern<<<grid, GEMM_THREADS, lds_bytes, s>>>((const u32x4_t*)W.data, (const u32x4_t*)Xp, out, W.n_blocks, W.k_steps, kps, mb_pad, M, W.N, ldo,
                                                (int64_t)M * ldo, W.scale);

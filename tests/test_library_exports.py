@@ -142,3 +142,37 @@ def test_every_launch_is_checked_where_it_is_made():
                 if "SPEC_LAUNCH_CHECK" not in body[body.rindex("<<<"):]:
                     unchecked.append("%s: %s" % (src, name))
     assert seen >= 20 and not unchecked, unchecked
+
+
+LDS_LIMIT_PROGRAM = r"""
+#include "lds_limit.h"
+static int gpu = 0, calls = 0, fail = 0;
+extern "C" hipError_t hipGetDevice(int* d) { *d = gpu; return hipSuccess; }
+extern "C" hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { ++calls; return fail ? hipErrorInvalidValue : hipSuccess; }
+int main()
+{
+    static specv::LdsLimit a, b;
+    auto made = [&](specv::LdsLimit& l, int on) { gpu = on; const int before = calls; const bool ok = l.raise(nullptr, 1) == hipSuccess; return ok ? calls - before : -1; };
+    if (made(a, 0) != 1 || made(a, 0) != 0) return 1;         // once on one GPU
+    if (made(a, 1) != 1 || made(a, 1) != 0 || made(a, 0) != 0) return 2;         // and once on another
+    if (made(b, 0) != 1) return 3;                            // of each kernel
+    fail = 1;
+    if (made(a, 2) != -1) return 4;
+    fail = 0;
+    if (made(a, 2) != 1 || made(a, 2) != 0) return 5;         // again after a failure
+    return made(a, 64) == 1 && made(a, 64) == 1 ? 0 : 6;
+}
+"""
+
+
+def test_lds_limit_is_raised_on_every_gpu(tmp_path):
+    """The limit of a kernel's dynamic LDS holds on one GPU only: with a stand-in for the runtime, it is raised once on each, and every
+    kernel that asks for it goes through that."""
+    import subprocess
+    csrc = os.path.join(ROOT, "paper_2604_26779_amd", "csrc")
+    src, exe = tmp_path / "lds.cpp", tmp_path / "lds"
+    src.write_text(LDS_LIMIT_PROGRAM)
+    subprocess.check_call(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I" + csrc, str(src), "-o", str(exe)])
+    assert subprocess.call([str(exe)]) == 0
+    callers = [f for f in os.listdir(csrc) if "hipFuncSetAttribute" in open(os.path.join(csrc, f)).read()]
+    assert callers == ["lds_limit.h"]
