@@ -227,8 +227,9 @@ __global__ __launch_bounds__(64) void f32_attention_kernel(const float* __restri
         __syncthreads();
         int cnt = visible - p0 < 64 ? visible - p0 : 64;
         for (int a = 0; a < 4; ++a) {
-            int c = lane + 64 * a;
-            if (c < dh) {
+            if (64 * a < dh) {
+                // every lane stays on, as the page ids are handed round between them: those beyond the last channel repeat it (not stored)
+                const int c = lane + 64 * a < dh ? lane + 64 * a : dh - 1;
                 float o = acc[a] * corr;
                 // a page of positions at a time (p0 is a multiple of the page size), its loads in flight together: the
                 // slots past the last visible position re-read that one and are left out of the sum

@@ -727,3 +727,14 @@ def test_splits_gu_is_honoured_at_odd_row_block_counts(B, k):
     size = {n: _with_tune(dict(base, splits_gu=n), lambda: sv.spec_verify_workspace_bytes(sess.model, sess.kv, B, k)) for n in (1, 2)}
     sess.close()
     assert abs(size[2] - size[1] - B * (k + 1) * 2 * cfg["ffn_dim"] * 4) < 256
+
+
+@pytest.mark.parametrize("head_dim", [2, 16, 62, 66, 80, 192, 200, 256])
+def test_f32_attention_head_dims(head_dim):
+    """Head dimensions that are no multiple of the wavefront, and both limits, over contexts of several pages and pieces of 64 positions
+    (fp32 sums of a few hundred terms: far below 1e-4 of logits of order one)."""
+    cfg = dict(si.MODELS["tiny_fp32"], head_dim=head_dim)
+    ctx = [0, 1, 15, 16, 17, 47, 63, 64, 65, 127, 130, 200]
+    ok, max_err, worst = _run_custom_bf16(ctx, k=3, seed=head_dim, **cfg)
+    print("fp32 head_dim %d: logits max abs err %.3e" % (head_dim, max_err))
+    assert ok and max_err <= 1e-4, (max_err, worst)
