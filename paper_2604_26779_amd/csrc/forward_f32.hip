@@ -284,6 +284,23 @@ static size_t f32_carve(const spec_model_desc& d, int M, char* base, F32Ws* w)
 
 size_t f32_workspace_bytes(const spec_model_desc& d, int B, int k) { return f32_carve(d, B * (k + 1), nullptr, nullptr); }
 
+// f32_gemm_rows_kernel takes a trip to memory per 256 of K, but fetches a matrix again for every 8 rows; the tiled kernel takes a trip per
+// 32 of K (3.6 us each), and its tile is 32 rows.  Tiled / rows, us:
+//   matrices that stay in the 256 MB memory-side cache: N = 1024, K = 256: 15.2 / 3.8 at 16 rows, 18.4 / 12.1 at 512; N = 1024, K = 704:
+//   38.8 / 5.1 and 45.7 / 20.9; N = 4096, K = 256: 15.2 / 4.2 and 41.1 / 37.6; N = K = 4096: 319 / 20 and 669 / 547; two of 16384 x 2048 (256
+//   MB): 716 / 626 at 128 rows, 2509 / 2353 at 512.  The lead shrinks with the rows, and beyond 512 nothing was measured;
+//   beyond the cache every 8 rows fetch the matrices from HBM: up to 24 rows that is still the faster (98304 x 1024: 286 / 174 at 16 rows,
+//   335 / 349 at 32, 1129 / 1384 at 128; 131072 x 4096: 1389 / 869, 1532 / 1725, 5707 / 6804).  With more, it is so while the tiled kernel has too few
+//   tiles to hide its trips, that is up to some number of outputs per matrix: N = 4096, K = 28672: 3286 / 2970 at 256 rows, 3938 / 4494
+//   at 384; N = 8192, K = 16384: 1912 / 1653 at 128, 2361 / 2484 at 192; two of 11008 x 4096: 1026 / 860 at 96, 1949 / 2253 at 256; two of 28672 x
+//   4096: 1216 / 770 at 32, 1381 / 1526 at 64.  (70000 x 1024, 273 MB, is even from 64 rows on.)
+static bool rows_kernel_is_ahead(int M, int N, int K, int n_matrices)
+{
+    if (M > 512) return false;
+    if ((int64_t)N * K * 4 <= (int64_t)288 << 20) return true;
+    return M <= 24 || (int64_t)M * N <= (int64_t)n_matrices * 1300000;
+}
+
 // y = a w^T for up to three matrices over the same rows, side by side in y
 static void gemm(const float* a, std::initializer_list<std::pair<const float*, int>> ws, int M, int K, float* y, int ldy, bool accum, hipStream_t s)
 {
@@ -297,11 +314,7 @@ static void gemm(const float* a, std::initializer_list<std::pair<const float*, i
         aligned = aligned && ((uintptr_t)w.first & 15) == 0;
     }
     for (int i = parts.n; i < 3; ++i) { parts.w[i] = parts.w[parts.n - 1]; parts.end[i] = N; }
-    // f32_gemm_rows_kernel takes a trip to memory per 256 of K, but fetches a matrix again for every 8 rows; the tiled kernel takes a
-    // trip per 32 of K, and its tile is 32 rows.  Tiled / rows, us: N = 1024, K = 256: 15.2 / 3.8 at 16 rows, 18.4 / 12.1 at 512;
-    // N = 1024, K = 704: 38.8 / 5.1 and 45.7 / 20.9; N = 4096, K = 256: 15.2 / 4.2 and 41.1 / 37.6; N = K = 4096: 319 / 20 and
-    // 669 / 547.  The lead shrinks with the rows, and beyond 512 nothing was measured.
-    if (aligned && M <= 512) {
+    if (aligned && rows_kernel_is_ahead(M, N, K, parts.n)) {
         dim3 grid((unsigned)cdiv(N, 16), (unsigned)cdiv(M, 8));
         if (accum) f32_gemm_rows_kernel<true><<<grid, 256, 0, s>>>(a, parts, M, N, K, y, ldy);
         else f32_gemm_rows_kernel<false><<<grid, 256, 0, s>>>(a, parts, M, N, K, y, ldy);

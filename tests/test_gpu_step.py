@@ -738,3 +738,12 @@ def test_f32_attention_head_dims(head_dim):
     ok, max_err, worst = _run_custom_bf16(ctx, k=3, seed=head_dim, **cfg)
     print("fp32 head_dim %d: logits max abs err %.3e" % (head_dim, max_err))
     assert ok and max_err <= 1e-4, (max_err, worst)
+
+
+@pytest.mark.parametrize("B,k", [(8, 2), (9, 2)])
+def test_f32_projection_beyond_the_memory_side_cache(B, k):
+    """An output head of 320 MB: 24 rows take the few-row kernel, 27 the tiled one (sums of 1024 terms of logits of order one)."""
+    cfg = dict(si.MODELS["tiny_fp32"], d_model=1024, vocab=81001, n_layers=1)
+    ok, max_err, worst = _run_custom_bf16([[0, 15, 16, 65, 130][b % 5] for b in range(B)], k=k, seed=B, **cfg)
+    print("fp32 head beyond the cache, M=%d: logits max abs err %.3e" % (B * (k + 1), max_err))
+    assert ok and max_err <= 1e-4, (max_err, worst)
