@@ -259,16 +259,16 @@ __device__ inline float race_scale(uint32_t word)
 // of a one-hot draft distribution).  race_key: the exact key of entry v, fp64, -1 where the weight is not positive.
 constexpr int RACE_PLAIN = 0, RACE_RES = 1, RACE_HOT = 2;
 constexpr double RACE_SOME = -0.5;            // in the place of a best key: nothing was found, but an entry below `reach` may have a positive weight
-struct RaceRow {                              // one race: the row, its largest logit and sum, the random stream
+struct RaceRow {                              // one race: the row, its largest logit / T and sum, the random stream
     const float *l, *q;
     int V, hot;
-    double T, max_l, S;
+    double T, m, S;
     uint32_t k0, k1, c1, c2, c3;
 };
 template <int KIND>
 __device__ inline double race_key(const RaceRow& r, int v)
 {
-    const double pv = exp((double)r.l[v] / r.T - r.max_l / r.T) / r.S;
+    const double pv = exp((double)r.l[v] / r.T - r.m) / r.S;
     if (!(pv > 0.0)) return -1.0;
     const double w = KIND == RACE_RES ? fmax(0.0, pv - (double)r.q[v]) : (KIND == RACE_HOT && v == r.hot ? 0.0 : pv);
     if (!(w > 0.0)) return -1.0;
@@ -282,7 +282,7 @@ __device__ inline double race_key(const RaceRow& r, int v)
 // reach: the largest lower bound of a key that this wavefront has met, or that is known or supposed of the row.  A race starts from a
 // bound of the whole row: without one a wavefront that holds only keys below the fp32 range's end would evaluate all of them, and with
 // peaked logits (a largest logit of 25 over a spread of 2 at T = 0.2) that is nearly every wavefront.  Draw of 256 rows, V = 128256, such
-// logits, no bound / a bound: rejected explicit draft 474 / 220 us a call, one-hot 459 / 203, mapped draw of 32000 138 / 87.
+// logits, no bound / a bound: rejected explicit draft 455 / 216 us a call, one-hot 438 / 194, mapped draw of 32000 137 / 86.
 // The exponent (l - mx) log2(e) / T, mx the row's largest logit, carries three fp32 roundings (RaceExponent): 126 * 3 * 2^-24 = 2.3e-5 at most
 // where the exponential is a normal number, so the fp32 probability is off by less than RACE_EPS of itself, the scale of
 // race_scale included.  Below that it counts as 0 with an upper bound of RACE_TINY: such an entry matters only if nothing clear of
@@ -297,11 +297,12 @@ constexpr float RACE_EPS = 4.0e-5f, RACE_TINY = 1.2e-38f, RACE_FLOOR = 1.0e-30f;
 //   largest number: two logits that differ do so by 2^77 there, so the product is 0 or far below the range all the same.
 struct RaceExponent {
     float c, mc, r;
-    __device__ RaceExponent(float mx, double T)
+    __device__ RaceExponent(float mx, double rT)
     {
-        c = T > 1.0 ? 0.5f : (T < 1e-37 && fabsf(mx) < 1.2676506e30f ? 16777216.0f : 1.0f);
+        const int e = rT < 1.0 ? -1 : (rT > 1e37 && fabsf(mx) < 1.2676506e30f ? 24 : 0);
+        c = ldexpf(1.0f, e);
         mc = mx * c;
-        r = (float)fmin(1.4426950408889634 / (T * c), 3.4028234663852886e38);
+        r = (float)fmin(ldexp(1.4426950408889634 * rT, -e), 3.4028234663852886e38);
     }
     __device__ float operator()(float l) const { return __builtin_fmaf(l, c, -mc) * r; }
 };
@@ -367,11 +368,9 @@ __device__ inline void race_round(const RaceRow& row, const float (&l)[SAMP_GPT]
 // Exponential race over the groups [g0, g1) of one row, all SAMP_THREADS threads; every lane's best entry.  No key below `reach` is
 // certain to be found: the caller looks again with a lower one where the row's best turns out to lie below.
 template <int KIND, bool VEC>
-__device__ inline void race_scan(const RaceRow& row, int g0, int g1, float reach, double& best, int& best_v)
+__device__ inline void race_scan(const RaceRow& row, const RaceExponent& exponent, float rS, int g0, int g1, float reach, double& best, int& best_v)
 {
     const int wave = threadIdx.x >> 6;
-    const RaceExponent exponent((float)row.max_l, row.T);
-    const float rS = (float)(1.0 / row.S);
     for (int gb = g0 + wave * 64; gb < g1; gb += SAMP_THREADS * SAMP_GPT) {
         float l[SAMP_GPT][4], qv[SAMP_GPT][4];
         load_round<VEC>(row.l, gb, g1, row.V, -INFINITY, l);
@@ -380,8 +379,9 @@ __device__ inline void race_scan(const RaceRow& row, int g0, int g1, float reach
     }
 }
 
-// a key that the plain race over a row of sum S surely holds
-__device__ inline float race_known(double S) { return (float)(1.0 / S) * (1.0f / 17.0f); }
+// a key that the plain race over a row of sum S surely holds: the entry with the largest p, 1 / S, has one of at least 1 / (17 S), as
+// -ln u is at most 16.7
+__device__ inline float race_known(float rS) { return rS * (1.0f / 17.0f); }
 
 // what a range's workgroup hands to the merge: its best (key, token) of the race
 struct RacePart { double key; int64_t v; };
@@ -429,6 +429,7 @@ __global__ __launch_bounds__(SAMP_THREADS, 4) void reject_scan_kernel(
     const float* Qb = q ? q + (int64_t)b * k * V : nullptr;
     __shared__ int s_n, s_last;
     __shared__ double2 s_st[SPEC_MAX_DRAFT + 1];
+    __shared__ double s_m[SPEC_MAX_DRAFT + 1];                        // largest logit / T
     __shared__ double lk[SAMP_WAVES];
     __shared__ int lv[SAMP_WAVES];
 
@@ -443,9 +444,11 @@ __global__ __launch_bounds__(SAMP_THREADS, 4) void reject_scan_kernel(
             const float lx = probe ? L[(int64_t)i * V + x] : 0.f;
             Q = probe ? (Qb ? (double)Qb[(int64_t)i * V + x] : 1.0) : 0.0;      // no q array: one-hot drafts (a deterministic drafter)
             const double2 st = row_stat(stats, (int64_t)b * (k + 1) + i, rT);
+            const double m = st.x / T;
             s_st[i] = st;
+            s_m[i] = m;
             if (probe) {
-                P = exp((double)lx / T - st.x / T) / st.y;
+                P = exp((double)lx / T - m) / st.y;
                 const Philox4 r = philox4x32_10(0u, (uint32_t)i, (uint32_t)b, step4 + 0u, seed_lo, seed_hi);
                 u = (double)(r.x >> 8) * (1.0 / 16777216.0);
                 ok = u * Q < P;
@@ -472,25 +475,30 @@ __global__ __launch_bounds__(SAMP_THREADS, 4) void reject_scan_kernel(
     part_groups(V, part, &g0, &g1);
     double best = -1.0;
     int best_v = -1;
-    RaceRow row = {lrow, Qb ? Qb + (int64_t)n * V : nullptr, V, n < k && !Qb ? draft[(int64_t)b * k + n] : -1, T, st.x, st.y,
+    RaceRow row = {lrow, Qb ? Qb + (int64_t)n * V : nullptr, V, n < k && !Qb ? draft[(int64_t)b * k + n] : -1, T, uniform(s_m[n]), st.y,
                    seed_lo, seed_hi, (uint32_t)n, (uint32_t)b, step4 + 1u};
-    // The plain race: the entry with the largest p, 1 / S, has a key of at least 1 / (17 S) (-ln u is at most 16.7).  The residual races
-    // have no such entry, but a draft is rejected where q exceeds p by at least 2^-24 q, and a q of sum 1 leaves as much residual elsewhere:
-    // keys above RACE_FLOOR are to be expected.  Where there are none the workgroup that finishes the sequence looks again at
-    // everything positive (a q that left nothing but such weights: 393 us a call of 64 rows, 75 otherwise), and if there is nothing (a
-    // residual identically zero) the token comes from the plain race.
-    int kind = n == k ? RACE_PLAIN : Qb ? RACE_RES : RACE_HOT;
-    float known = kind == RACE_PLAIN ? race_known(st.y) : RACE_FLOOR;
-    for (bool whole = false;; whole = true) {
-        if (whole) { g0 = 0; g1 = (V + 3) >> 2; }
-        if (kind == RACE_RES) race_scan<RACE_RES, VEC>(row, g0, g1, known, best, best_v);
-        else if (kind == RACE_HOT) race_scan<RACE_HOT, VEC>(row, g0, g1, known, best, best_v);
-        else race_scan<RACE_PLAIN, VEC>(row, g0, g1, known, best, best_v);
+    const RaceExponent exponent((float)st.x, rT);
+    const float rS = __builtin_amdgcn_rcpf((float)st.y);
+    // The residual races have no entry that is sure to have a large key, but a draft is rejected where q exceeds p by at least 2^-24 q, and
+    // a q of sum 1 leaves as much residual elsewhere: keys above RACE_FLOOR are to be expected.
+    if (n < k && Qb) race_scan<RACE_RES, VEC>(row, exponent, rS, g0, g1, RACE_FLOOR, best, best_v);
+    else if (n < k) race_scan<RACE_HOT, VEC>(row, exponent, rS, g0, g1, RACE_FLOOR, best, best_v);
+    else race_scan<RACE_PLAIN, VEC>(row, exponent, rS, g0, g1, race_known(rS), best, best_v);
+    block_argmax(best, best_v, lk, lv);
+    if (!merge_parts(parts + (int64_t)b * SAMP_PARTS, part, counters + b, best, best_v, &s_last)) return;
+    if (n < k && best >= RACE_SOME && best < (double)RACE_FLOOR) {
+        // there are none, but smaller ones: every entry of the row in fp64 (a q that left nothing but such weights: 395 us a call of
+        // 64 rows, 75 otherwise)
+        for (int v = threadIdx.x; v < V; v += SAMP_THREADS) {
+            const double key = Qb ? race_key<RACE_RES>(row, v) : race_key<RACE_HOT>(row, v);
+            argmax_merge(best, best_v, key, key > 0.0 ? v : -1);
+        }
         block_argmax(best, best_v, lk, lv);
-        if (!whole && !merge_parts(parts + (int64_t)b * SAMP_PARTS, part, counters + b, best, best_v, &s_last)) return;
-        if (kind == RACE_PLAIN || (best_v >= 0 && best >= (double)known)) break;
-        if (known > 0.f && best >= RACE_SOME) known = 0.f;
-        else { kind = RACE_PLAIN; known = race_known(st.y); }
+    }
+    if (n < k && best_v < 0) {
+        // the residual is identically zero: the token comes from the plain race over the whole row
+        race_scan<RACE_PLAIN, VEC>(row, exponent, rS, 0, (V + 3) >> 2, race_known(rS), best, best_v);
+        block_argmax(best, best_v, lk, lv);
     }
     if (threadIdx.x == 0) accept_len[b] = n;
     for (int i = threadIdx.x; i <= k; i += SAMP_THREADS) out_tokens[(int64_t)b * (k + 1) + i] = i < n ? draft[(int64_t)b * k + i] : (i == n ? best_v : -1);
@@ -525,55 +533,58 @@ __global__ __launch_bounds__(SAMP_THREADS, 4) void draft_scan_kernel(
     m = uniform(m);
     S = m == INFINITY ? 0.0 : uniform(S);
     const double rS = S > 0.0 ? 1.0 / S : NAN;                      // without a distribution q is NaN, and the verifier rejects the -1 drawn from it
-    const RaceExponent exponent((float)m, T);
+    const RaceExponent exponent((float)m, rT);
     const float rS32 = (float)rS;
-    float reach = race_known(S);
+    float reach = race_known(rS32);
     const float known = reach;
     int g0, g1;
     part_groups(V, part, &g0, &g1);
     double best = -1.0;
     int best_v = -1;
     const float none[SAMP_GPT][4] = {};
-    const RaceRow race = {lrow, nullptr, V, -1, T, m, S, seed_lo, seed_hi, row, (uint32_t)b, step4 + 2u};
-    for (bool whole = false;; whole = true) {
-        if (MAPPED && whole) { g0 = 0; g1 = (V + 3) >> 2; reach = 0.f; }
-        for (int gb = g0 + wave * 64; gb < g1; gb += SAMP_THREADS * SAMP_GPT) {
-            float l[SAMP_GPT][4];
-            const int n_u = round_groups(gb, g1);
-            load_round<VEC>(lrow, gb, g1, V, -INFINITY, l);
+    const RaceRow race = {lrow, nullptr, V, -1, T, m / T, S, seed_lo, seed_hi, row, (uint32_t)b, step4 + 2u};
+    for (int gb = g0 + wave * 64; gb < g1; gb += SAMP_THREADS * SAMP_GPT) {
+        float l[SAMP_GPT][4];
+        const int n_u = round_groups(gb, g1);
+        load_round<VEC>(lrow, gb, g1, V, -INFINITY, l);
 #pragma unroll
-            for (int u = 0; u < SAMP_GPT; ++u) {
-                if (u >= n_u) break;
-                const int g = gb + u * SAMP_THREADS + lane;
-                float p[4];
+        for (int u = 0; u < SAMP_GPT; ++u) {
+            if (u >= n_u) break;
+            const int g = gb + u * SAMP_THREADS + lane;
+            float p[4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const double x = ((double)l[u][j] - m) * rT;
-                    const float pj = (float)(exp_sum(x) * rS);
-                    p[j] = x == x ? pj : NAN;                           // a NaN logit (and -inf at an infinite T)
-                }
-                if (g < g1) {
-                    if constexpr (VEC && !MAPPED) {
-                        *(float4*)(qrow + 4 * (int64_t)g) = make_float4(p[0], p[1], p[2], p[3]);
-                    } else {
+            for (int j = 0; j < 4; ++j) {
+                const double x = ((double)l[u][j] - m) * rT;
+                const float pj = (float)(exp_sum(x) * rS);
+                p[j] = x == x ? pj : NAN;                           // a NaN logit (and -inf at an infinite T)
+            }
+            if (g < g1) {
+                if constexpr (VEC && !MAPPED) {
+                    *(float4*)(qrow + 4 * (int64_t)g) = make_float4(p[0], p[1], p[2], p[3]);
+                } else {
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) {
-                            const int v = 4 * g + j;
-                            if (v >= V) continue;
-                            const int at = MAPPED ? token_map[v] : v;                               // (a mapped row was cleared by the statistics kernel)
-                            if (MAPPED && (unsigned)at >= (unsigned)q_width) l[u][j] = -INFINITY;    // outside the target's vocabulary: never written, never drawn
-                            else qrow[at] = p[j];
-                        }
+                    for (int j = 0; j < 4; ++j) {
+                        const int v = 4 * g + j;
+                        if (v >= V) continue;
+                        const int at = MAPPED ? token_map[v] : v;                               // (a mapped row was cleared by the statistics kernel)
+                        if (MAPPED && (unsigned)at >= (unsigned)q_width) l[u][j] = -INFINITY;    // outside the target's vocabulary: never written, never drawn
+                        else qrow[at] = p[j];
                     }
                 }
             }
-            race_round<RACE_PLAIN>(race, l, none, gb, g1, n_u, exponent, rS32, reach, best, best_v);
+        }
+        race_round<RACE_PLAIN>(race, l, none, gb, g1, n_u, exponent, rS32, reach, best, best_v);
+    }
+    block_argmax(best, best_v, lk, lv);
+    if (!merge_parts(parts + (int64_t)b * SAMP_PARTS, part, counters + b, best, best_v, &s_last)) return;
+    if (MAPPED && S > 0.0 && best < (double)known) {
+        // a map may leave out the most probable entry, and then there may be no key of that size: every entry of the row in fp64
+        for (int v = threadIdx.x; v < V; v += SAMP_THREADS) {
+            if ((unsigned)token_map[v] >= (unsigned)q_width) continue;
+            const double key = race_key<RACE_PLAIN>(race, v);
+            argmax_merge(best, best_v, key, key > 0.0 ? v : -1);
         }
         block_argmax(best, best_v, lk, lv);
-        if (!whole && !merge_parts(parts + (int64_t)b * SAMP_PARTS, part, counters + b, best, best_v, &s_last)) return;
-        // a map may leave out the most probable entry, and then there may be no key of that size: once more, over the whole row (q is written
-        // again with the same values)
-        if (!MAPPED || whole || best >= (double)known) break;
     }
     if (threadIdx.x == 0) {
         if (MAPPED && best_v >= 0) best_v = token_map[best_v];
