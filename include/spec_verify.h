@@ -271,7 +271,7 @@ spec_status spec_reject_sample(int32_t B, int32_t k, int32_t V, const float* dev
  * spec_reject_sample for callers that cannot allocate device memory or carry a workspace along: code recorded under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, arithmetic, random
  * streams and outputs as spec_reject_sample, minus the workspace: the row statistics and per-range race results live
- * in a buffer that is part of the loaded library (1.5 MiB of device memory per GPU, held until the process ends).
+ * in a buffer that is part of the loaded library (1.02 MiB of device memory per GPU, held until the process ends).
  * The call allocates and frees nothing.  Limit: B * (k + 1) <= 4096 logits rows, SPEC_EINVAL beyond (use
  * spec_reject_sample then).
  * All calls on one GPU share that buffer: calls whose work may overlap on one GPU (different streams, or graphs

@@ -389,7 +389,8 @@ __global__ __launch_bounds__(GEMM_THREADS, (MB >= 3 && WM == 1 && NBW_T == 2) ? 
     if constexpr (EPI == GEMM_EPI_SWIGLU && WM == 1 && NBW == 1) {
         // 128-column tile of the 1 x 4 arrangement with one column block per wavefront: wavefronts 0 and 2 hold the gates,
         // 1 and 3 the ups of 2 x 32 hidden channels (the column blocks of a pair are both inside the matrix or both outside).  The raw accumulators go through LDS one row block at a time, and
-        // silu(gate) * up is formed on the way out.
+        // silu(gate) * up is formed on the way out.  Odd row-block counts use expf as swiglu_pack_kernel does, which they take where K
+        // is split: fused or not, the result is the same bits.  (Even ones are never split while the fusion is on.)
         float* tile = (float*)lds;                              // [32 rows][129]
         uint4* xo = (uint4*)out;
 #pragma unroll

@@ -5,7 +5,7 @@
 // 16-wide k-step (twice the MB part for hi + lo operands) for MB * 64 MFMA cycles, as long as nothing is fetched twice.  So both
 // operands go from memory straight into LDS (global_load ... lds) exactly once per workgroup, and the four wavefronts (2 x 2,
 // MB/2 x 4 accumulator blocks of 32 x 32 each) read their fragments from there.
-//   * A slab is two k-steps.  NBUF slabs sit in LDS (112-144 KiB, one workgroup per CU): while one is multiplied, the others
+//   * A slab is two k-steps.  NBUF slabs sit in LDS (80-144 KiB, one workgroup per CU): while one is multiplied, the others
 //     are in flight, so a transfer has two or three slabs' worth of MFMAs (1 000 or 2 000 cycles each) to arrive.
 //   * LDS reads run one k-step ahead of the MFMAs that use them, across the slab boundary too: the barrier between slabs sits
 //     before the last k-step's MFMAs, when every wavefront has its last fragments in registers and the next slab has arrived.

@@ -48,15 +48,17 @@ __device__ inline void part_groups(int V, int part, int* g0, int* g1)
     *g1 = (part + 1) * per < groups ? (part + 1) * per : groups;
 }
 
-// Everything a decision hangs on is fp64, as the definition has it: z = logit / T (a division, not a product with
-// 1 / T), e = exp(z - max), p = e / sum, the accept test u * q < p, the race keys w / (-ln u).  With fp32 keys two
-// candidates closer than 1e-6 relative could swap, and a residual p - q that cancels to a few ulps was noise; in fp64
-// the choice differs from an fp64 reference's only where its own keys agree to 15 digits.
+// Everything a decision hangs on is fp64, as the definition has it: z = logit / T, e = exp(z - max), p = e / sum, the accept
+// test u * q < p, the race keys w / (-ln u).  In the accept tests and the keys z is a division; in the sums and in the q that is
+// written out z - max is (logit - largest) * (1 / T), whose first factor is exact and whose error, 2^-52 of itself, is that of the
+// two divisions.  With fp32 keys two candidates closer than 1e-6 relative could swap, and a residual p - q that cancels to a few
+// ulps was noise; in fp64 the choice differs from an fp64 reference's only where its own keys agree to 15 digits.
 //
 // What keeps that cheap (both kernels should be bound by reading the logits):
 //   * the sums need an fp64 exponential per entry: exp_sum below, 18 fp64 instructions, no branch, no special cases;
 //   * a race needs its keys in fp64 only where they can win: every entry's key is first bounded in fp32 from above and
-//     below, and the few entries of a wavefront whose upper bound reaches the best lower bound are then evaluated in fp64.
+//     below, and the entries whose upper bound reaches the best lower bound known to the wavefront are then evaluated in fp64.
+//     Those are few unless the weights cancel: a residual that is rounding noise everywhere (q = p) leaves every entry.
 // Measured (V = 128256): figures at the kernels.
 
 // a * b + c with c in scalar registers.  Left to itself the compiler takes the two-address form and copies the constant into
@@ -286,8 +288,7 @@ __device__ inline double race_key(const RaceRow& r, int v)
 // The exponent (l - mx) log2(e) / T, mx the row's largest logit, carries three fp32 roundings (RaceExponent): 126 * 3 * 2^-24 = 2.3e-5 at most
 // where the exponential is a normal number, so the fp32 probability is off by less than RACE_EPS of itself, the scale of
 // race_scale included.  Below that it counts as 0 with an upper bound of RACE_TINY: such an entry matters only if nothing clear of
-// the fp32 range's end competes (RACE_FLOOR, some way above RACE_TINY times the largest scale, 1.7e7); without such a key every
-// entry that may have a positive weight is evaluated (bar = 0).
+// the fp32 range's end competes (RACE_FLOOR, some way above RACE_TINY times the largest scale, 1.7e7), and `reach` is never below that.
 constexpr float RACE_EPS = 4.0e-5f, RACE_TINY = 1.2e-38f, RACE_FLOOR = 1.0e-30f;
 
 // log2 of an entry's probability times S: (l c - mx c) * (log2(e) / (T c)), the first term one fused instruction.  c is a power of two
@@ -341,7 +342,7 @@ __device__ inline void race_round(const RaceRow& row, const float (&l)[SAMP_GPT]
     }
     for (int off = 32; off > 0; off >>= 1) lo_max = fmaxf(lo_max, __shfl_xor(lo_max, off));
     reach = fmaxf(reach, lo_max);
-    const float bar = reach >= RACE_FLOOR ? reach * (1.0f - (KIND == RACE_PLAIN ? 3.0f : 1.0f) * RACE_EPS) : 0.f;
+    const float bar = reach * (1.0f - (KIND == RACE_PLAIN ? 3.0f : 1.0f) * RACE_EPS);
     unsigned int may_win = 0;
 #pragma unroll
     for (int u = 0; u < SAMP_GPT; ++u)
@@ -365,8 +366,8 @@ __device__ inline void race_round(const RaceRow& row, const float (&l)[SAMP_GPT]
     }
 }
 
-// Exponential race over the groups [g0, g1) of one row, all SAMP_THREADS threads; every lane's best entry.  No key below `reach` is
-// certain to be found: the caller looks again with a lower one where the row's best turns out to lie below.
+// Exponential race over the groups [g0, g1) of one row, all SAMP_THREADS threads; every lane's best entry.  No key below `reach` (at
+// least RACE_FLOOR) is certain to be found: where the row's best turns out to lie below, the caller looks at all entries.
 template <int KIND, bool VEC>
 __device__ inline void race_scan(const RaceRow& row, const RaceExponent& exponent, float rS, int g0, int g1, float reach, double& best, int& best_v)
 {
