@@ -147,7 +147,7 @@ __device__ inline int round_groups(int gb, int g1)
 // round exceeds it), so there is no second pass over the logits and no barrier before the sums; the wavefronts' pairs are
 // merged in a fixed order.
 // Bound by its vector instructions (32 per entry, most of them fp64 at the fp32 rate) with the reads beside them: 1024 rows take
-// 152 us = 3.5 TB/s, 355 us as two passes with the library's exponential and a barrier between them; 384 rows 48 us, 122 before.
+// 128-130 us = 4.1 TB/s, 355 us as two passes with the library's exponential and a barrier between them; 384 rows 51-55 us, 122 before.
 // (zero_rows != null: the workgroup also clears its eighth of row blockIdx.x of that array, zero_width entries wide - the
 // q rows a mapped draft draw then fills at scattered positions; counters != null: the sequences' arrival counters of the
 // scan that follows, counter_rows rows per sequence)
@@ -416,7 +416,7 @@ __device__ inline bool merge_parts(RacePart* parts, int part, int32_t* counter, 
 }
 
 // Bound by its vector instructions: a Philox block per 4 entries, a logarithm, an exponential and a reciprocal in fp32 per entry
-// (58 instructions, about 70 us of issue at B = 256, k = 3, V = 128256 where the two rows' reads would take 45).  Measured there: 86 us, 345 us with
+// (58 instructions, about 70 us of issue at B = 256, k = 3, V = 128256 where the two rows' reads would take 45).  Measured there: 76-84 us, 345 us with
 // every key in fp64, the accept tests one after the other and the merge in a launch of its own.
 template <bool VEC>
 __global__ __launch_bounds__(SAMP_THREADS, 4) void reject_scan_kernel(
@@ -509,8 +509,8 @@ __global__ __launch_bounds__(SAMP_THREADS, 4) void reject_scan_kernel(
 // written out for the verifier (rounded to fp32 from the fp64 value), and x = argmax_v q_v / (-ln u_v) on random
 // stream 2.  row_stats_kernel gives the ranges' statistics; draft_scan_kernel (workgroup = sequence, range) merges them,
 // writes its range of q and finds its range's best key; the workgroup that finishes a sequence last picks the token.
-// Bound as reject_scan_kernel, with an fp64 exponential more per entry: 98 us at B = 256, V = 128256.  With its statistics the draw
-// takes 119 us there (317 before) and 39 us at B = 64 (87 before).
+// Bound as reject_scan_kernel, with an fp64 exponential more per entry.  With its statistics the draw takes 125-130 us at B = 256,
+// V = 128256 (335 before) and 40-42 us at B = 64 (87 before).
 template <bool VEC, bool MAPPED>
 __global__ __launch_bounds__(SAMP_THREADS, 4) void draft_scan_kernel(
     int V, const float* __restrict__ logits, int64_t logits_stride, double T, double rT, uint32_t seed_lo, uint32_t seed_hi,
