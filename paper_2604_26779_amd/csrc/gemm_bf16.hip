@@ -12,7 +12,7 @@
 //     (spread evenly over the HBM channels) instead of thousands of streams a power of two apart.
 //   * the activations are written by the producing kernel in the same operand order, as hi + lo
 //     bf16 pairs ([k-step][32-row block][hi|lo][lane][8], see operand.h), staged through LDS in
-//     slabs of KS k-steps (double buffered, one barrier per slab) and shared by the 4 wavefronts
+//     slabs of KS k-steps (two or three in flight, one barrier per slab) and shared by the 4 wavefronts
 //     of the workgroup; each weight fragment feeds two MFMAs per row block (hi and lo).
 //   * v_mfma_f32_32x32x16_bf16: A = activation fragment (rows m), B = weight fragment
 //     (columns n), so a lane ends up with one output column and 16 rows: stores are
@@ -28,8 +28,12 @@
 
 namespace specv {
 
-constexpr int GEMM_WD = 4;          // slabs of weight fragments each wavefront keeps in flight
-constexpr int GEMM_KUNIT = GEMM_KS * GEMM_WD;       // k-steps per split are a multiple of this
+constexpr int GEMM_WD = 2;          // slabs of weight fragments each wavefront keeps in flight: the LDS slabs behind them allow no more
+constexpr int GEMM_KUNIT = GEMM_KS * 4;             // K is a multiple of 16 times this
+
+// how many slabs ahead the activations of a tile of mb row blocks are requested.  Two, but one for the large slabs of two hi + lo row blocks and more
+// (QKV / output projection of the 8B shape at 64 rows 14.2 / 10.9 us with two, 14.0 / 10.7 with one; at 4 rows 10.9 / 8.1 and 11.2 / 8.2)
+constexpr int gemm_slabs_ahead(int mb, int xf) { return mb == 1 || xf == XF_F16 ? 2 : 1; }
 
 // from gemm_big.hip
 spec_status launch_gemm_big(const PackedW& W, const bf16_t* Xp, int M, int mb, int mb_pad, float* out, int ldo, int kps, bool swiglu,
@@ -204,7 +208,19 @@ spec_status w8_pack_matrix(const unsigned char* const* dev_parts, const float* c
 // XF: the activations' operand format (operand.h): XF_HILO = hi + lo bf16 pairs against bf16 weights, two MFMAs per
 // weight fragment and row block; XF_F16 = one fp16 value against fp16 weights, one MFMA.  The fused SwiGLU epilogue
 // writes its output in the same format (gate/up and down projection take the same one).
-template <int MB, int WM, int WD, int EPI, bool GROUPED = false, int NBW_T = WM, bool W8 = false, int XF = XF_HILO>
+// The activation slabs are requested LA slabs ahead (LA + 1 of them in LDS), so that waiting for one - vector loads return in order - does
+// not also wait for the weights requested just before it.  What bounds a launch is how much of the weight stream is in flight, so every
+// wait in the loop counts (load_to_lds says why that takes buffer loads), and nothing is fetched twice.  8B shape, us with every wait draining the
+// queue and the last slab of the weights re-read past the end / now: QKV, output, gate/up and down projection at 4 rows 12.2, 8.9, 36.6, 19.9 /
+// 10.6, 7.8, 35.0, 19.0; at 64 rows 14.3, 10.8, 40.0, 21.3 / 13.7, 10.1, 37.2, 20.3; at 96 rows 18.5, 14.3, 44.5, 24.5 / 16.2, 11.8, 42.3, 22.2; at 128
+// rows 20.0, 15.3, 48.1, 26.7 / 19.1, 14.5, 46.5, 25.5.  With 8-bit weights at 4 rows 10.0, 7.1, 27.5, 14.3 / 8.5, 6.1, 21.6, 11.7, at 128 rows 17.8, 13.7, 40.7,
+// 23.2 / 16.5, 12.9, 35.0, 21.1; only a head of 1002 tiles, four workgroups on a CU, loses 3-5 % with 8-bit weights and up to 64 rows.
+// EPI: PLAIN, SWIGLU (fused), or for an output that is not split along K - in the first place the head's logits, tens of megabytes that
+// nobody reads before the launch ends - STREAM: stored past the L2s, it does not push out what the workgroups share there (head of 128256
+// rows at 64, 74 and 128 rows: 171 -> 164, 198 -> 177, 184 -> 172 us; slices of a split output are small and gain nothing).  STREAM_SHARED: the
+// same with several row tiles, whose workgroups also share the weights: ordinary instead of nontemporal loads (32000 rows at 160
+// and 256 rows: 104 -> 91, 116 -> 93 us; with one row tile, or split, the nontemporal ones are ahead, 164 against 181 us at 64 rows).
+template <int MB, int WM, int EPI, bool GROUPED = false, int NBW_T = WM, bool W8 = false, int XF = XF_HILO, int WD = GEMM_WD>
 __global__ __launch_bounds__(GEMM_THREADS, (MB >= 3 && WM == 1 && NBW_T == 2) ? 1 : 2) void gemm_bf16_kernel(
     const u32x4_t* __restrict__ Wp, const u32x4_t* __restrict__ Xp, float* __restrict__ out, int n_blocks, int k_steps,
     int ksteps_per_split, int mb_pad, int M, int N, int ldo, int64_t split_stride,
@@ -218,12 +234,14 @@ __global__ __launch_bounds__(GEMM_THREADS, (MB >= 3 && WM == 1 && NBW_T == 2) ? 
     constexpr int SLAB = KS * MB * 64 * XF;             // u32x4_t per slab (XF operand words per lane and k-step)
     constexpr int XPT = SLAB / GEMM_THREADS;            // u32x4_t per thread per slab
     static_assert(SLAB % GEMM_THREADS == 0, "a slab must divide over the threads");
+    constexpr int LA = gemm_slabs_ahead(MB, XF), NX = LA + 1;
+    static_assert(LA <= WD && (WD == 2 || WD == 4), "the waits below count the weight loads behind an activation slab");
     // the fused SwiGLU epilogue re-uses the slabs as an fp32 transpose tile, which may be the larger of the two
     constexpr int EPI_WORDS = EPI != GEMM_EPI_SWIGLU ? 0 : (WM == 1 ? 32 * 129 : MB * 32 * 65) / 4 + 1;
-    constexpr int LDS_WORDS = 2 * SLAB > EPI_WORDS ? 2 * SLAB : EPI_WORDS;
+    constexpr int LDS_WORDS = NX * SLAB > EPI_WORDS ? NX * SLAB : EPI_WORDS;
     __shared__ u32x4_t lds[LDS_WORDS];
 
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int mh = wave % WM, np = wave / WM;
     int bx = blockIdx.x, by = blockIdx.y, bz = blockIdx.z;
     if constexpr (!GROUPED) {
@@ -246,11 +264,11 @@ __global__ __launch_bounds__(GEMM_THREADS, (MB >= 3 && WM == 1 && NBW_T == 2) ? 
         M = mblk0 * 32 + moe_tile_rows(tiles[2 + 2 * bz]);                 // padding rows are not stored
     }
 
-    // slab s of column block j of this wavefront: wptr[j] + s * wslab
+    // slab s of column block j of this wavefront: wptr[j] + s * wslab (+ the lane), all scalar
     const u32x4_t* wptr[NBW];
 #pragma unroll
     for (int j = 0; j < NBW; ++j)
-        wptr[j] = Wp + (((int64_t)(ks0 / KS) * n_blocks + (nb0 + j < n_blocks ? nb0 + j : 0)) * KSW) * 64 + lane;
+        wptr[j] = Wp + (((int64_t)(ks0 / KS) * n_blocks + (nb0 + j < n_blocks ? nb0 + j : 0)) * KSW) * 64;
     const int64_t wslab = (int64_t)n_blocks * KSW * 64;
     float wsc[NBW];                                     // 8-bit weights: this lane's column scales
 #pragma unroll
@@ -268,34 +286,35 @@ __global__ __launch_bounds__(GEMM_THREADS, (MB >= 3 && WM == 1 && NBW_T == 2) ? 
     // the weight stream runs WD slabs ahead of the MFMAs: a register ring, each entry refilled
     // right after its last use
     u32x4_t w[WD][KSW][NBW];
+    auto load_w = [](const u32x4_t* p) {
+        if constexpr (EPI == GEMM_EPI_STREAM_SHARED) return *p;
+        else return __builtin_nontemporal_load(p);
+    };
 
-    // The activation slabs go from global memory straight into LDS (global_load ... lds: no staging registers, no LDS store
-    // instructions).  Each instruction moves 64 x 16 bytes: per-lane global addresses, LDS address = the wavefront-uniform
-    // base given here + 16 * lane.
+    // The activation slabs go from memory straight into LDS.  The offsets are scalar, and the base moves with the slab, so none grows with K.
     auto stage_x = [&](int slab, int tobuf) {
+        const u32x4_t* src = xbase + (int64_t)slab * KS * mb_pad * (64 * XF);
 #pragma unroll
         for (int j = 0; j < XPT; ++j) {
-            int idx = threadIdx.x + GEMM_THREADS * j;
-            int kl = idx / (MB * 64 * XF), rem = idx % (MB * 64 * XF);
-            const u32x4_t* src = xbase + ((int64_t)(slab * KS + kl) * mb_pad) * (64 * XF) + rem;
-            u32x4_t* dst = lds + tobuf * SLAB + (idx - lane);
-            __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)src,
-                                             (void __attribute__((address_space(3)))*)dst, 16, 0, 0);
+            const int c = wave + 4 * j, kl = c / (MB * XF), rem = c % (MB * XF);       // 1 KiB chunk c of the slab
+            load_to_lds(src, (kl * mb_pad * XF + rem) * 1024, lds + tobuf * SLAB + c * 64);
         }
     };
     int buf = 0;
     // No branch may sit between the loads and their use: the compiler can only count outstanding
     // loads (s_waitcnt vmcnt(n)) along straight-line code, and falls back to draining the whole
-    // queue otherwise.  So every slab issues its prefetches unconditionally; past the end they
-    // re-read the last slab (cache hits, results unused).
+    // queue otherwise.  So every slab issues its prefetches unconditionally; past the end they read
+    // activations that are in the caches (results unused; the last slab of the weights would come from HBM once more).
     auto slab_body = [&](auto slot_c, int s) {
         constexpr int SLOT = decltype(slot_c)::value;
-        const int s_w = s + WD < n_slabs ? s + WD : n_slabs - 1;
-        const int s_x = s + 1 < n_slabs ? s + 1 : n_slabs - 1;
-        // the next slab's activations are the oldest loads of this slab: what is waited for at its end
-        stage_x(s_x, buf ^ 1);
+        const int s_x = s + LA < n_slabs ? s + LA : n_slabs - 1;
+        // the oldest loads of this slab, into the buffer that the last slab has freed
+        stage_x(s_x, buf > 0 ? buf - 1 : NX - 1);
         // keep these loads HERE: left alone, the scheduler sinks them to the end of the slab, next to the LDS
         // stores that consume them, and the whole round trip to L2 is then paid once per slab
+        const u32x4_t* w_src[NBW];
+#pragma unroll
+        for (int j = 0; j < NBW; ++j) w_src[j] = s + WD < n_slabs ? wptr[j] + (int64_t)(s + WD) * wslab : xbase;
         __builtin_amdgcn_sched_barrier(0);
         // LDS reads run one k-step ahead of the MFMAs that use them (two register sets): with one or two
         // wavefronts per SIMD nothing else would hide the LDS latency.  The scheduling barriers keep that order.
@@ -338,52 +357,61 @@ __global__ __launch_bounds__(GEMM_THREADS, (MB >= 3 && WM == 1 && NBW_T == 2) ? 
             if (!W8 || (kk & 1)) {                       // (8-bit: a word serves two k-steps and is refilled after the second)
 #pragma unroll
                 for (int j = 0; j < NBW; ++j)
-                    w[SLOT][W8 ? kk >> 1 : kk][j] = __builtin_nontemporal_load(wptr[j] + (int64_t)s_w * wslab + (W8 ? kk >> 1 : kk) * 64);
+                    w[SLOT][W8 ? kk >> 1 : kk][j] = load_w(w_src[j] + (W8 ? kk >> 1 : kk) * 64 + lane);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
         // ... and the weight loads of this slab stay above the LDS stores, so that waiting for the (older)
         // activation loads does not drain the weight stream
         __builtin_amdgcn_sched_barrier(0);
-        // Wait for the transfers into LDS only: the slab's own weight reloads (KSW * NBW of them) were issued later
-        // and stay in flight (__syncthreads would drain the whole queue).  No wavefront reads the other buffer
-        // before this barrier, and all have finished reading this one when they pass the next.
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm(KSW * NBW));
+        // Wait for the next slab's transfers into LDS only: the weight reloads (KSW * NBW a slab) and the transfers that were issued
+        // after them stay in flight (__syncthreads would drain the whole queue).  No wavefront reads the next buffer
+        // before this barrier, and all have finished reading this one when they pass it.
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(KSW * NBW + (LA - 1) * (KSW * NBW + XPT)));
         __builtin_amdgcn_s_barrier();
-        buf ^= 1;
+        buf = buf + 1 < NX ? buf + 1 : 0;
     };
 
-    // n_slabs is a multiple of WD (K % (16 * GEMM_KUNIT) == 0 and split sizes are rounded to it)
+    // n_slabs is a multiple of WD (K % (16 * GEMM_KUNIT) == 0, split sizes are rounded to two slabs, and a ring of four is taken
+    // where they are multiples of four)
     if (n_slabs > 0) {
         if constexpr (W8) {
-            // Fetched with the first weight loads and known to have arrived (the wait below, then the empty asm that
-            // ties the values to this point) on every path into the epilogue: a load the compiler may still count as
+            // Fetched before anything else and known to have arrived (the first wait below, then the empty asm behind the loop that
+            // ties the values to that point) on every path into the epilogue: a load the compiler may still count as
             // outstanding there makes it wait with vmcnt(0) before each of the 64 stores, which serialises them.
 #pragma unroll
             for (int j = 0; j < NBW; ++j)
                 if (nb0 + j < n_blocks) wsc[j] = wscale[(nb0 + j) * 32 + (lane & 31)];
         }
 #pragma unroll
-        for (int d = 0; d < WD; ++d) {
-            const int sd = d < n_slabs ? d : n_slabs - 1;
+        for (int d = 0; d < LA; ++d) stage_x(d, d);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int d = 0; d < WD; ++d)
 #pragma unroll
             for (int i = 0; i < KSW; ++i)
 #pragma unroll
-                for (int j = 0; j < NBW; ++j) w[d][i][j] = __builtin_nontemporal_load(wptr[j] + (int64_t)sd * wslab + i * 64);
-        }
-        stage_x(0, 0);
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+                for (int j = 0; j < NBW; ++j) w[d][i][j] = load_w(wptr[j] + (int64_t)d * wslab + i * 64 + lane);
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm((LA - 1) * XPT + KSW * NBW * WD));
         __builtin_amdgcn_s_barrier();
+        // The loop runs at least once and has no remainder: every load is then used on the only way on from it.  Otherwise the compiler
+        // drops those that nobody reads, or moves them behind a wait that counts them.
+        int s = 0;
+        do {
+            slab_body(std::integral_constant<int, 0>{}, s);
+            slab_body(std::integral_constant<int, 1>{}, s + 1);
+            if constexpr (WD == 4) {
+                slab_body(std::integral_constant<int, 2>{}, s + 2);
+                slab_body(std::integral_constant<int, 3>{}, s + 3);
+            }
+            s += WD;
+        } while (s < n_slabs);
         if constexpr (W8) {
 #pragma unroll
             for (int j = 0; j < NBW; ++j) asm volatile("" : "+v"(wsc[j]));
         }
-        for (int s = 0; s < n_slabs; s += WD) {
-            slab_body(std::integral_constant<int, 0>{}, s);
-            if constexpr (WD > 1) slab_body(std::integral_constant<int, 1>{}, s + 1);
-            if constexpr (WD > 2) slab_body(std::integral_constant<int, 2>{}, s + 2);
-            if constexpr (WD > 3) slab_body(std::integral_constant<int, 3>{}, s + 3);
-        }
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(KSW * NBW));       // no transfer into LDS is left when the epilogue re-uses it or the workgroup ends
     }
 
     if constexpr (EPI == GEMM_EPI_SWIGLU && WM == 1 && NBW == 1) {
@@ -491,7 +519,10 @@ __global__ __launch_bounds__(GEMM_THREADS, (MB >= 3 && WM == 1 && NBW_T == 2) ? 
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 int m = (mblk0 + mh * MBW + i) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                if (m < M) o[(int64_t)m * ldo + n] = W8 ? acc[i][j][r] * sc : acc[i][j][r];
+                if (m >= M) continue;
+                const float v = W8 ? acc[i][j][r] * sc : acc[i][j][r];
+                if constexpr (EPI >= GEMM_EPI_STREAM) __builtin_nontemporal_store(v, o + (int64_t)m * ldo + n);
+                else o[(int64_t)m * ldo + n] = v;
             }
     }
 }
@@ -537,9 +568,7 @@ static GemmShape gemm_shape(const PackedW& W, int M, bool fused_swiglu)
     }
     g.mb = big ? 4 : gemm_mb(M);
     g.tile_nb = 4;
-    // k-steps per split come in units of one pass of the weight ring: 2 slabs for the 2x2 arrangement (even row-block
-    // counts), 4 for the others
-    g.kunit = g.mb % 2 == 0 ? GEMM_KS * 2 : GEMM_KUNIT;
+    g.kunit = GEMM_KS * 2;                              // k-steps per split: whole pairs of slabs
     g.m_tiles = pad / g.mb; g.n_tiles = (int)cdiv(W.n_blocks, 4);
     // One tile of 64 or 128 rows, plain epilogue, K unsplit because the columns alone give enough workgroups (the LM head): 256-column
     // tiles with the wavefronts 1 x 4 - no weight fragment fetched twice, the activation slab serves twice the columns.
@@ -615,48 +644,46 @@ spec_status launch_gemm_bf16(const PackedW& W, const bf16_t* Xp, int M, float* o
     const u32x4_t* wp = (const u32x4_t*)W.data;
     const u32x4_t* xp = (const u32x4_t*)Xp;
     if (swiglu && !gemm_can_fuse_swiglu(W, M, splits)) { set_error("gemm: SwiGLU cannot be fused for this shape"); return SPEC_EUNSUPPORTED; }
-#define SPEC_GEMM_LAUNCH_W(MBV, WMV, WDV, E, W8V, XFV) gemm_bf16_kernel<MBV, WMV, WDV, E, false, (MBV % 2 == 0 && WMV == 1) ? 2 : WMV, W8V, XFV><<<grid, GEMM_THREADS, 0, s>>>(wp, xp, out, W.n_blocks, W.k_steps, kps, mb_pad, M, W.N, ldo, stride, nullptr, 0, W.scale)
-#define SPEC_GEMM_LAUNCH_1BW(MBV, E, W8V, XFV) gemm_bf16_kernel<MBV, 1, 2, E, false, 1, W8V, XFV><<<grid, GEMM_THREADS, 0, s>>>(wp, xp, out, W.n_blocks, W.k_steps, kps, mb_pad, M, W.N, ldo, stride, nullptr, 0, W.scale)
-#define SPEC_GEMM_LAUNCH_96W(E, W8V, XFV) gemm_bf16_kernel<3, 1, 2, E, false, 2, W8V, XFV><<<grid, GEMM_THREADS, 0, s>>>(wp, xp, out, W.n_blocks, W.k_steps, kps, mb_pad, M, W.N, ldo, stride, nullptr, 0, W.scale)
+    const int epi = swiglu ? GEMM_EPI_SWIGLU : (grid.y > 1 ? GEMM_EPI_PLAIN : (grid.z > 1 ? GEMM_EPI_STREAM_SHARED : GEMM_EPI_STREAM));
+#define SPEC_GEMM_CALL(...) gemm_bf16_kernel<__VA_ARGS__><<<grid, GEMM_THREADS, 0, s>>>(wp, xp, out, W.n_blocks, W.k_steps, kps, mb_pad, M, W.N, ldo, stride, nullptr, 0, W.scale)
+    // MB row blocks, WM wavefronts along the rows, NBW column blocks per wavefront.  One column block and 8-bit weights, half the bytes a slab: a weight ring
+    // of four slabs where the split allows it (gate/up of the 8B shape at 4 and 128 rows 26.3 -> 22.9, 39.6 -> 36 us)
+#define SPEC_GEMM_TILE(MB, WM, NBW, E, W8, XF) do { \
+        if (W8 && NBW == 1 && kps % (4 * GEMM_KS) == 0) SPEC_GEMM_CALL(MB, WM, E, false, NBW, W8, XF, W8 && NBW == 1 ? 4 : 2); \
+        else SPEC_GEMM_CALL(MB, WM, E, false, NBW, W8, XF, 2); } while (0)
     // the four combinations of 8-bit or 16-bit weights and hi + lo or fp16 activations
-#define SPEC_GEMM_BY_TYPE(CALL, ...) do { \
-        if (W.w8) { if (W.f16) CALL(__VA_ARGS__, true, XF_F16); else CALL(__VA_ARGS__, true, XF_HILO); } \
-        else { if (W.f16) CALL(__VA_ARGS__, false, XF_F16); else CALL(__VA_ARGS__, false, XF_HILO); } } while (0)
-#define SPEC_GEMM_LAUNCH_96(E) SPEC_GEMM_BY_TYPE(SPEC_GEMM_LAUNCH_96W, E)
-#define SPEC_GEMM_LAUNCH(MBV, WMV, WDV, E) SPEC_GEMM_BY_TYPE(SPEC_GEMM_LAUNCH_W, MBV, WMV, WDV, E)
+#define SPEC_GEMM_BY_TYPE(MB, WM, NBW, E) do { \
+        if (W.w8) { if (W.f16) SPEC_GEMM_TILE(MB, WM, NBW, E, true, XF_F16); else SPEC_GEMM_TILE(MB, WM, NBW, E, true, XF_HILO); } \
+        else { if (W.f16) SPEC_GEMM_TILE(MB, WM, NBW, E, false, XF_F16); else SPEC_GEMM_TILE(MB, WM, NBW, E, false, XF_HILO); } } while (0)
+#define SPEC_GEMM_F16(MB, WM, NBW, E) do { if (W.w8) SPEC_GEMM_TILE(MB, WM, NBW, E, true, XF_F16); else SPEC_GEMM_TILE(MB, WM, NBW, E, false, XF_F16); } while (0)
+#define SPEC_GEMM_BY_EPI(BY_TYPE, MB, WM, NBW, SHARED) do { \
+        if (epi == GEMM_EPI_SWIGLU) BY_TYPE(MB, WM, NBW, GEMM_EPI_SWIGLU); \
+        else if (epi == GEMM_EPI_PLAIN) BY_TYPE(MB, WM, NBW, GEMM_EPI_PLAIN); \
+        else if (epi == GEMM_EPI_STREAM_SHARED) BY_TYPE(MB, WM, NBW, SHARED); \
+        else BY_TYPE(MB, WM, NBW, GEMM_EPI_STREAM); } while (0)
     switch (mb) {
-        case 1: if (swiglu) SPEC_GEMM_LAUNCH(1, 1, GEMM_WD, GEMM_EPI_SWIGLU); else SPEC_GEMM_LAUNCH(1, 1, GEMM_WD, GEMM_EPI_PLAIN); break;
+        case 1: SPEC_GEMM_BY_EPI(SPEC_GEMM_BY_TYPE, 1, 1, 1, GEMM_EPI_STREAM); break;
         case 2:
-            if (g.one_block) { if (swiglu) SPEC_GEMM_BY_TYPE(SPEC_GEMM_LAUNCH_1BW, 2, GEMM_EPI_SWIGLU); else SPEC_GEMM_BY_TYPE(SPEC_GEMM_LAUNCH_1BW, 2, GEMM_EPI_PLAIN); }
-            else if (g.wide && swiglu) SPEC_GEMM_LAUNCH(2, 1, 2, GEMM_EPI_SWIGLU);
-            else if (g.wide) SPEC_GEMM_LAUNCH(2, 1, 2, GEMM_EPI_PLAIN);
-            else if (swiglu) SPEC_GEMM_LAUNCH(2, 2, 2, GEMM_EPI_SWIGLU);
-            else SPEC_GEMM_LAUNCH(2, 2, 2, GEMM_EPI_PLAIN);
+            if (g.one_block) SPEC_GEMM_BY_EPI(SPEC_GEMM_BY_TYPE, 2, 1, 1, GEMM_EPI_STREAM);
+            else if (g.wide) SPEC_GEMM_BY_EPI(SPEC_GEMM_BY_TYPE, 2, 1, 2, GEMM_EPI_STREAM_SHARED);
+            else SPEC_GEMM_BY_EPI(SPEC_GEMM_BY_TYPE, 2, 2, 2, GEMM_EPI_STREAM);
             break;
         case 3:
-            if (g.wide && swiglu) SPEC_GEMM_LAUNCH_96(GEMM_EPI_SWIGLU);
-            else if (g.wide) SPEC_GEMM_LAUNCH_96(GEMM_EPI_PLAIN);
-            else if (swiglu) SPEC_GEMM_LAUNCH(3, 1, GEMM_WD, GEMM_EPI_SWIGLU);
-            else SPEC_GEMM_LAUNCH(3, 1, GEMM_WD, GEMM_EPI_PLAIN);
+            if (g.wide) SPEC_GEMM_BY_EPI(SPEC_GEMM_BY_TYPE, 3, 1, 2, GEMM_EPI_STREAM);
+            else SPEC_GEMM_BY_EPI(SPEC_GEMM_BY_TYPE, 3, 1, 1, GEMM_EPI_STREAM);
             break;
         case 6: case 8: return launch_gemm_big(W, Xp, M, mb, mb_pad, out, ldo, kps, swiglu, grid, s);
         default:
-            if (g.one_block) {                               // fp16 activations only
-                if (W.w8) { if (swiglu) SPEC_GEMM_LAUNCH_1BW(4, GEMM_EPI_SWIGLU, true, XF_F16); else SPEC_GEMM_LAUNCH_1BW(4, GEMM_EPI_PLAIN, true, XF_F16); }
-                else { if (swiglu) SPEC_GEMM_LAUNCH_1BW(4, GEMM_EPI_SWIGLU, false, XF_F16); else SPEC_GEMM_LAUNCH_1BW(4, GEMM_EPI_PLAIN, false, XF_F16); }
-            }
-            else if (g.wide && swiglu) SPEC_GEMM_LAUNCH(4, 1, 2, GEMM_EPI_SWIGLU);
-            else if (g.wide) SPEC_GEMM_LAUNCH(4, 1, 2, GEMM_EPI_PLAIN);
-            else if (swiglu) SPEC_GEMM_LAUNCH(4, 2, 2, GEMM_EPI_SWIGLU);
-            else SPEC_GEMM_LAUNCH(4, 2, 2, GEMM_EPI_PLAIN);
+            if (g.one_block) SPEC_GEMM_BY_EPI(SPEC_GEMM_F16, 4, 1, 1, GEMM_EPI_STREAM);
+            else if (g.wide) SPEC_GEMM_BY_EPI(SPEC_GEMM_BY_TYPE, 4, 1, 2, GEMM_EPI_STREAM);
+            else SPEC_GEMM_BY_EPI(SPEC_GEMM_BY_TYPE, 4, 2, 2, GEMM_EPI_STREAM);
             break;
     }
+#undef SPEC_GEMM_BY_EPI
+#undef SPEC_GEMM_F16
 #undef SPEC_GEMM_BY_TYPE
-#undef SPEC_GEMM_LAUNCH_96
-#undef SPEC_GEMM_LAUNCH_96W
-#undef SPEC_GEMM_LAUNCH_1BW
-#undef SPEC_GEMM_LAUNCH
-#undef SPEC_GEMM_LAUNCH_W
+#undef SPEC_GEMM_TILE
+#undef SPEC_GEMM_CALL
     SPEC_LAUNCH_CHECK("gemm_bf16_kernel");
     return SPEC_OK;
 }
@@ -679,7 +706,7 @@ spec_status launch_gemm_bf16_grouped(const PackedW& W0, int64_t group_stride, co
     // which is what the expert GEMMs - few rows, all weights touched - are bound by).
     const bool wide = tune("moe_wide_tiles") != 0 && W0.n_blocks % 8 == 0;
     if (wide) grid.x = (unsigned)cdiv(W0.n_blocks, 8);
-#define SPEC_GROUPED_LAUNCH(WMV, E, W8V, XFV) gemm_bf16_kernel<2, WMV, 2, E, true, 2, W8V, XFV><<<grid, GEMM_THREADS, 0, s>>>( \
+#define SPEC_GROUPED_LAUNCH(WMV, E, W8V, XFV) gemm_bf16_kernel<2, WMV, E, true, 2, W8V, XFV><<<grid, GEMM_THREADS, 0, s>>>( \
         wp, xp, out, W0.n_blocks, W0.k_steps, W0.k_steps, rows_pad / 32, rows_pad, W0.N, ldo, 0, tiles, stride16, W0.scale)
 #define SPEC_GROUPED_BY_TYPE(WMV, E) do { \
         if (W0.w8) { if (W0.f16) SPEC_GROUPED_LAUNCH(WMV, E, true, XF_F16); else SPEC_GROUPED_LAUNCH(WMV, E, true, XF_HILO); } \

@@ -14,7 +14,19 @@ typedef unsigned int u32x2v_t __attribute__((ext_vector_type(2)));
 constexpr int GEMM_KS = 4;          // k-steps (of 16) per slab of the tiled weights
 constexpr int GEMM_XCDS = 8;        // accelerator dies, each with its own L2; workgroup i of a launch runs on die i % 8
 constexpr int GEMM_THREADS = 256;
-constexpr int GEMM_EPI_PLAIN = 0, GEMM_EPI_SWIGLU = 1;
+constexpr int GEMM_EPI_PLAIN = 0, GEMM_EPI_SWIGLU = 1, GEMM_EPI_STREAM = 2, GEMM_EPI_STREAM_SHARED = 3;
+
+// 64 x 16 bytes from memory straight into LDS (no staging registers, no LDS store instructions): lane i's 16 bytes at base + offset + 16 i go
+// to dst + 16 i.  base, offset and dst are the wavefront's; offset < 2^31.
+// A buffer load, not global_load ... lds: the compiler takes the latter for a flat access that may touch either memory and, while one is
+// outstanding, turns each of its counted waits into vmcnt(0) lgkmcnt(0) - every LDS read and every weight fragment would be waited
+// for together with all that was requested after it.
+__device__ inline void load_to_lds(const u32x4_t* base, int offset, u32x4_t* dst)
+{
+    constexpr int RAW = 0x00020000;                     // word 3 of the descriptor: 32-bit data format, no stride, no swizzle
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, 0xffffffffu, RAW);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (void __attribute__((address_space(3)))*)dst, 16, (threadIdx.x & 63) * 16, offset, 0, 0);
+}
 
 // s_waitcnt operand: at most n vector-memory operations outstanding, the other counters not waited for
 constexpr int vmcnt_imm(int n) { return (n & 15) | 0x70 | 0xF00 | ((n >> 4) << 14); }
@@ -50,7 +62,8 @@ __device__ inline GemmTile gemm_tile_of_workgroup()
     const int total = nx * ny * nz, lin = blockIdx.x + nx * (blockIdx.y + ny * blockIdx.z);
     const int xcd = lin % GEMM_XCDS, slot = lin / GEMM_XCDS;
     const int v = xcd * (total / GEMM_XCDS) + (xcd < total % GEMM_XCDS ? xcd : total % GEMM_XCDS) + slot;
-    return GemmTile{(v / nz) % nx, v / (nz * nx), v % nz};
+    // (the divisions run in the vector unit; without the hint the compiler keeps what follows from them there too)
+    return GemmTile{__builtin_amdgcn_readfirstlane((v / nz) % nx), __builtin_amdgcn_readfirstlane(v / (nz * nx)), __builtin_amdgcn_readfirstlane(v % nz)};
 }
 
 }  // namespace specv

@@ -747,3 +747,18 @@ def test_f32_projection_beyond_the_memory_side_cache(B, k):
     ok, max_err, worst = _run_custom_bf16([[0, 15, 16, 65, 130][b % 5] for b in range(B)], k=k, seed=B, **cfg)
     print("fp32 head beyond the cache, M=%d: logits max abs err %.3e" % (B * (k + 1), max_err))
     assert ok and max_err <= 1e-4, (max_err, worst)
+
+
+@pytest.mark.parametrize("w8", [False, True])
+@pytest.mark.parametrize("splits", [1, 2, 4, 10])
+@pytest.mark.parametrize("B,k", [(1, 3), (9, 4), (12, 7), (32, 3), (43, 4)])
+def test_bf16_short_k_splits(B, k, splits, w8):
+    """Splits down to one pass of the weight ring (two slabs of four k-steps), and of two, three and more slab pairs (with 8-bit weights a ring
+    of four slabs where they allow it): K = 512 and 1280 over tiles of one to four row blocks, two and four row tiles of 64 rows, and the head with
+    one row tile and with several."""
+    rng = np.random.default_rng(B * 10 + k)
+    ctx = [int(c) for c in rng.integers(3, 120, size=B)]
+    want = {"gemm_min_ksteps": 8, "splits_qkv": splits, "splits_o": splits, "splits_down": splits}
+    ok, max_err, worst = _with_tune(want, lambda: _run_custom_bf16(ctx, k=k, seed=B + k, vocab=1000, **(dict(w_dtype="fp8_e4m3") if w8 else {})))
+    print("M=%d, %d splits, 8-bit matrices %s: logits max abs err %.3e" % (B * (k + 1), splits, w8, max_err))
+    assert ok, (max_err, worst)
