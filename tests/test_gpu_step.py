@@ -762,3 +762,21 @@ def test_bf16_short_k_splits(B, k, splits, w8):
     ok, max_err, worst = _with_tune(want, lambda: _run_custom_bf16(ctx, k=k, seed=B + k, vocab=1000, **(dict(w_dtype="fp8_e4m3") if w8 else {})))
     print("M=%d, %d splits, 8-bit matrices %s: logits max abs err %.3e" % (B * (k + 1), splits, w8, max_err))
     assert ok, (max_err, worst)
+
+
+@pytest.mark.parametrize("B,k,changes", [
+    (8, 3, {}),                                                                  # the norm, rotary and SwiGLU inside the projections, split attention
+    (8, 7, dict(n_kv_heads=2, head_dim=128, vocab=1003)),                        # two positions of the cache side by side per load, grouped heads
+    (8, 2, dict(n_q_heads=3, n_kv_heads=1, head_dim=20, ffn_dim=711, d_model=260)),   # lanes without channels, an odd number of gate columns, K = 711: tiled
+    (8, 3, dict(head_dim=18, n_q_heads=2, n_kv_heads=2)),                        # head_dim % 4 != 0: separate rotary, one wavefront per head
+    (33, 1, dict(d_model=1028)),                                                 # 66 rows, products beyond the size that is fused: separate norms
+    (40, 6, {}),                                                                 # 280 rows x 4 heads: one wavefront per head
+])
+def test_f32_fused_projections_and_split_attention(B, k, changes):
+    """The fp32 forward with its small kernels fused and apart, over contexts at the edges of pages, of the pieces of 64 positions and of the four
+    wavefronts' turns (fp32 sums of a few hundred terms: far below 1e-4 of logits of order one)."""
+    cfg = dict(si.MODELS["tiny_fp32"], **changes)
+    ctx = [[0, 62, 63, 64, 252, 255, 257, 700][b % 8] for b in range(B)]
+    ok, max_err, worst = _run_custom_bf16(ctx, k=k, seed=B + k, **cfg)
+    print("fp32 B=%d k=%d %s: logits max abs err %.3e" % (B, k, changes, max_err))
+    assert ok and max_err <= 1e-4, (max_err, worst)
