@@ -4,7 +4,7 @@
 // ride on ONE pass over that head's cached keys and values: that sharing is what makes verifying
 // k drafts cost about one decode step.  The pass is split along the context so that short and
 // long sequences fill the machine evenly:
-//   attn_plan_kernel    : once per forward pass (the contexts do not change between layers): the work list.  Every
+//   attn_plan           : once per forward pass (the contexts do not change between layers): the work list.  Every
 //                         sequence's pages are cut into chunks of (nearly) equal length, the length chosen on the
 //                         device, from the contexts the batch actually has, as the shortest for which the whole list
 //                         still fits the number of workgroups the chip holds in the rounds asked for - so a small
@@ -28,6 +28,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "attn_plan.h"
 #include "common.h"
 #include "operand.h"
 
@@ -39,9 +40,6 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
 
-constexpr int ATT_CP_MAX = 256;              // longest chunk (pages per workgroup): a wavefront's page ids sit in one register
-constexpr int KV_ERR_BOUND = 8;              // error bit: more work items than the launch was sized for
-constexpr int ATT_WAVES = 4;
 constexpr int ATT_DEPTH = 3;                 // pages in flight per wavefront
 constexpr int DH = 128;
 constexpr int BLOCK_U4 = SPEC_PAGE_SIZE * DH * 2 / 16;   // 256 16-byte words per K or V block
@@ -67,94 +65,6 @@ __device__ inline float quad_sum(float x)
     u = __float_as_uint(x);
     auto b = __builtin_amdgcn_permlane32_swap(u, u, false, false);
     return __uint_as_float(b[0]) + __uint_as_float(b[1]);
-}
-
-// One work item: pages [page0, page_end) of batch entry b (sequence seq, cached length ctx, `total` keys visible to the
-// last row; b = -1: unused slot of the list).  32 bytes, read with two 16-byte loads.
-struct AttnItem { int32_t b, seq, page0, page_end, ctx, total, chunk, pad; };
-
-// The work list of one forward pass.  One workgroup of 256.  pages(b) = pages holding the keys batch entry b may see
-// (0 for a dropped entry).  Chunk length L: the smallest multiple of 4 in [min_pages, 256] with sum_b ceil(pages(b) / L)
-// <= budget (256 if none; `forced` > 0 fixes L instead); entry b then has n = ceil(pages / L) items of
-// ceil(pages / n) pages rounded up to a multiple of 4 (the 4 wavefronts take every 4th page).  Items are listed in batch
-// order; entry_items[b] = (first item, number of items).  Slots of the list beyond the last item get b = -1.  More
-// items than max_items (contexts beyond the bound the launch was sized for) set KV_ERR_BOUND and are dropped.
-__global__ __launch_bounds__(256) void attn_plan_kernel(int B, int T, KvView kv, int budget, int min_pages, int forced, int max_items,
-                                                        AttnItem* __restrict__ items, int2* __restrict__ entry_items)
-{
-    __shared__ int s_cnt[256];
-    __shared__ int s_len, s_carry;
-    auto pages_of = [&](int b, int* seq_o, int* ctx_o, int* total_o) {
-        const int seq = kv.entry_seq[b];
-        int ctx = 0, total = 0;
-        if (seq >= 0) {
-            ctx = kv.ctx_len[seq];
-            total = ctx + T;
-            const int cap = kv.n_held[seq] * SPEC_PAGE_SIZE;
-            if (total > cap) total = cap;
-        }
-        if (seq_o) { *seq_o = seq; *ctx_o = ctx; *total_o = total; }
-        return (total + SPEC_PAGE_SIZE - 1) / SPEC_PAGE_SIZE;
-    };
-    {
-        // candidate j: chunks of 4 (j + 1) pages; thread t counts candidate t % 64 over the entries t / 64, t / 64 + 4, ...
-        const int j = threadIdx.x & 63, len = 4 * (j + 1);
-        int cnt = 0;
-        for (int b = threadIdx.x >> 6; b < B; b += 4) cnt += (pages_of(b, nullptr, nullptr, nullptr) + len - 1) / len;
-        s_cnt[threadIdx.x] = cnt;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            int best = ATT_CP_MAX;
-            for (int c = 63; c >= 0; --c) {
-                const int l = 4 * (c + 1);
-                if (l >= min_pages && s_cnt[c] + s_cnt[c + 64] + s_cnt[c + 128] + s_cnt[c + 192] <= budget) best = l;
-            }
-            s_len = forced > 0 ? forced : best;
-            s_carry = 0;
-        }
-        __syncthreads();
-    }
-    const int L = s_len;
-    for (int base = 0; base < B; base += 256) {
-        const int b = base + threadIdx.x;
-        int seq = -1, ctx = 0, total = 0;
-        const int p = b < B ? pages_of(b, &seq, &ctx, &total) : 0;
-        const int n = (p + L - 1) / L;
-        // exclusive scan of n over the workgroup
-        s_cnt[threadIdx.x] = n;
-        __syncthreads();
-        for (int off = 1; off < 256; off <<= 1) {
-            const int add = (int)threadIdx.x >= off ? s_cnt[threadIdx.x - off] : 0;
-            __syncthreads();
-            s_cnt[threadIdx.x] += add;
-            __syncthreads();
-        }
-        const int first = s_carry + s_cnt[threadIdx.x] - n, group_total = s_cnt[255];
-        __syncthreads();
-        if (b < B) {
-            const int len = n > 0 ? ((p + n - 1) / n + ATT_WAVES - 1) / ATT_WAVES * ATT_WAVES : 0;
-            int wrote = 0;
-            for (int c = 0; c < n; ++c) {
-                const int it = first + c;
-                if (it >= max_items) break;
-                AttnItem a;
-                a.b = b; a.seq = seq; a.page0 = c * len; a.page_end = (c + 1) * len < p ? (c + 1) * len : p;
-                a.ctx = ctx; a.total = total; a.chunk = c; a.pad = 0;
-                items[it] = a;
-                ++wrote;
-            }
-            entry_items[b] = make_int2(first < max_items ? first : 0, wrote);
-            if (wrote < n) atomicOr(kv.error, KV_ERR_BOUND);
-        }
-        if (threadIdx.x == 0) s_carry += group_total;
-        __syncthreads();
-    }
-    const int n_items = s_carry < max_items ? s_carry : max_items;
-    for (int it = n_items + threadIdx.x; it < max_items; it += 256) {
-        AttnItem a;
-        a.b = -1; a.seq = -1; a.page0 = 0; a.page_end = 0; a.ctx = 0; a.total = 0; a.chunk = 0; a.pad = 0;
-        items[it] = a;
-    }
 }
 
 // part_o : [item * Hkv + kv head][rows][128] fp32, part_ml : [..][rows][2] (reference point in log2 domain, sum relative
@@ -516,12 +426,12 @@ __global__ void attn_reduce_kernel(const float* __restrict__ part_o, const float
 
 // How R query rows per kv head are laid over workgroups: RG groups of NRB row blocks, NRB <= 4 and as equal as
 // possible (tuning parameter attn_row_blocks = 1..4 caps NRB instead).  How the contexts are cut into work items is
-// decided on the device (attn_plan_kernel); the host only gives the budget - the workgroups the chip holds at once
+// decided on the device (attn_plan); the host only gives the budget - the workgroups the chip holds at once
 // times attn_rounds, per kv head and row group - and sizes the list: at most max(budget, B * ceil(longest context /
 // 256 pages)) items, the host's bound on the longest context standing in for all of them.  attn_chunk_pages (a multiple
 // of 4, at most 256) fixes the chunk length instead.
 struct AttnPlan { int RB, RG, budget, forced, max_items; };
-static AttnPlan attn_plan(int R, int B, int Hkv, int pages_bound)
+static AttnPlan attn_layout(int R, int B, int Hkv, int pages_bound)
 {
     const int blocks = (int)cdiv(R, 16);
     const int forced_rb = tune("attn_row_blocks");
@@ -546,7 +456,7 @@ static AttnPlan attn_plan(int R, int B, int Hkv, int pages_bound)
 
 // the most work items a forward pass over B entries of at most pages_bound pages may have: sizes the item list and the
 // partial-result buffers
-int attn_max_items(int R, int B, int Hkv, int pages_bound) { return attn_plan(R, B, Hkv, pages_bound).max_items; }
+int attn_max_items(int R, int B, int Hkv, int pages_bound) { return attn_layout(R, B, Hkv, pages_bound).max_items; }
 
 // rows of a partial tile for R query rows per kv head: enough for every layout above (the workspace is sized before
 // the tuning parameters are final)
@@ -560,15 +470,13 @@ int attn_rows_padded(int R)
 
 size_t attn_item_bytes() { return sizeof(AttnItem); }
 
-// once per forward pass, after the page reservation: the work list of all its attention launches
-spec_status launch_attention_plan(int B, int T, int G, int Hkv, const KvView& kv, int pages_bound, void* items, void* entry_items, hipStream_t s)
+// what the kernel that builds the work list of a forward pass has to know (after the page reservation, before the first attention)
+AttnPlanArgs attention_plan_args(int B, int T, int G, int Hkv, int pages_bound, void* items, void* entry_items)
 {
-    const AttnPlan pl = attn_plan(T * G, B, Hkv, pages_bound);
+    const AttnPlan pl = attn_layout(T * G, B, Hkv, pages_bound);
     int min_pages = tune("attn_min_pages");
     if (min_pages < ATT_WAVES) min_pages = ATT_WAVES;
-    attn_plan_kernel<<<1, 256, 0, s>>>(B, T, kv, pl.budget, min_pages, pl.forced, pl.max_items, (AttnItem*)items, (int2*)entry_items);
-    SPEC_LAUNCH_CHECK("attn_plan_kernel");
-    return SPEC_OK;
+    return AttnPlanArgs{pl.budget, min_pages, pl.forced, pl.max_items, (AttnItem*)items, (int2*)entry_items};
 }
 
 spec_status launch_attention_bf16(const float* q, int B, int T, int G, int Hq, int Hkv, const KvView& kv, int layer_pool, int layer,
@@ -578,7 +486,7 @@ spec_status launch_attention_bf16(const float* q, int B, int T, int G, int Hq, i
     int R = T * G;
     if (R > 256) { set_error("attention: (k+1) * (query heads per kv head) = %d rows exceeds 256", R); return SPEC_EUNSUPPORTED; }
     const int rows = attn_rows_padded(R);
-    const AttnPlan pl = attn_plan(R, B, Hkv, pages_bound);
+    const AttnPlan pl = attn_layout(R, B, Hkv, pages_bound);
     const int RG = pl.RG;
     float scale_log2 = 1.4426950408889634f / sqrtf((float)DH);
     int IP = 1;                                   // items folded into blockIdx.x so that it spans a multiple of 8

@@ -11,11 +11,12 @@
 //   part  = xp_f W_d^T ; x += sum part ; xp_h = RMSNorm(x) * g_next     residual_rmsnorm_kernel
 //   (gate/up normally ends in the fused SwiGLU epilogue of the GEMM instead of swiglu_pack_kernel)
 // logits = xp_h W_head^T (fp32, written in place by the GEMM).
-// Around that: a draft model's input fusion (fuse_input_kernel; with multi-layer features pack_rows_kernel and the
+// Around that: a draft model's input fusion (fuse_input_kernel; with multi-layer features pack_rows and the
 // w_fc GEMM before it), the hidden-state and feature outputs (a copy of x after the last layer, tap_copy_kernel after
 // the tapped ones), and the mixture-of-experts feed-forward (moe.hip) in place of the dense one.
 #include <algorithm>
 
+#include "attn_plan.h"
 #include "common.h"
 #include "operand.h"
 
@@ -29,7 +30,7 @@ bool gemm_can_fuse_swiglu(const PackedW& W, int M, int splits);
 int attn_max_items(int R, int B, int Hkv, int pages_bound);
 size_t attn_item_bytes();
 int attn_rows_padded(int R);
-spec_status launch_attention_plan(int B, int T, int G, int Hkv, const KvView& kv, int pages_bound, void* items, void* entry_items, hipStream_t s);
+AttnPlanArgs attention_plan_args(int B, int T, int G, int Hkv, int pages_bound, void* items, void* entry_items);
 int moe_rows_bound(int M, int top_k, int E);
 spec_status launch_gemm_bf16_grouped(const PackedW& W0, int64_t group_stride, const bf16_t* Xp, int rows_pad, int max_tiles,
                                      const int32_t* tiles, float* out, int ldo, bool swiglu, hipStream_t s);
@@ -59,13 +60,12 @@ __device__ inline float block_sum(float v, float* lds16)
 // one workgroup per row (256 or 512 threads, 8 elements per thread and pass); d % 8 == 0
 constexpr int RES_ADD = 0, RES_EMBED = 1, RES_SET = 2;
 template <int MODE>
-__global__ __launch_bounds__(512) void residual_rmsnorm_kernel(
-    float* __restrict__ x, const float* __restrict__ part, int splits, int64_t split_stride, const int32_t* __restrict__ tokens,
+__device__ inline void residual_rmsnorm(
+    int m, float* __restrict__ x, const float* __restrict__ part, int splits, int64_t split_stride, const int32_t* __restrict__ tokens,
     const unsigned short* __restrict__ embed, int vocab, const unsigned short* __restrict__ gain, int d, float eps, int mb_pad,
     int xf, uint4* __restrict__ xp)
 {
     __shared__ float lds16[16];
-    const int m = blockIdx.x;
     const int stride = blockDim.x * 8;
     float* xr = x + (int64_t)m * d;
     float ss = 0.f;
@@ -123,6 +123,14 @@ __global__ __launch_bounds__(512) void residual_rmsnorm_kernel(
                       b.z * r * from_bf16(g.w & 0xffff), b.w * r * from_bf16(g.w >> 16)};
         xp_store8_rt(xp, xf, m, c, mb_pad, v);
     }
+}
+
+template <int MODE>
+__global__ __launch_bounds__(512) void residual_rmsnorm_kernel(
+    float* __restrict__ x, const float* __restrict__ part, int splits, int64_t split_stride, const unsigned short* __restrict__ gain, int d,
+    float eps, int mb_pad, int xf, uint4* __restrict__ xp)
+{
+    residual_rmsnorm<MODE>(blockIdx.x, x, part, splits, split_stride, nullptr, nullptr, 0, gain, d, eps, mb_pad, xf, xp);
 }
 
 // Input of a draft model that also takes hidden states: the operand of the fusion projection,
@@ -184,10 +192,9 @@ __global__ __launch_bounds__(512) void fuse_input_kernel(
 // and where the row's key and value go: row_slot[m] = page * SPEC_PAGE_SIZE + position in the page, or -1 (the batch entry
 // was dropped, or its sequence holds no page for that position).  The per-layer kernels then need no walk through the
 // bookkeeping (batch entry -> sequence -> length -> page list), three dependent loads each.
-__global__ void rope_table_kernel(int M, int T, KvView kv, int half, double theta, float2* __restrict__ table,
+__device__ inline void rope_table(int idx, int M, int T, const KvView& kv, int half, double theta, float2* __restrict__ table,
                                   int32_t* __restrict__ row_slot)
 {
-    int idx = blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= M * half) return;
     int m = idx / half, j = idx % half;
     const int seq = kv.entry_seq[m / T];
@@ -329,15 +336,48 @@ __global__ void swiglu_pack_kernel(const float* __restrict__ part, int splits, i
 }
 
 // fp32 rows [M, K] -> the hi + lo operand of a projection, unchanged in value (the multi-layer features before w_fc)
-__global__ __launch_bounds__(256) void pack_rows_kernel(const float* __restrict__ src, int M, int K, int mb_pad, uint4* __restrict__ xp)
+__device__ inline void pack_rows(int64_t i, const float* __restrict__ src, int M, int K, int mb_pad, uint4* __restrict__ xp)
 {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int per_row = K / 8;
     if (i >= (int64_t)M * per_row) return;
     const int m = (int)(i / per_row), c = (int)(i % per_row) * 8;
     const float4 a = *(const float4*)(src + (int64_t)m * K + c), b = *(const float4*)(src + (int64_t)m * K + c + 4);
     const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
     xp_store8(xp, m, c, mb_pad, v);
+}
+
+// What a forward pass starts with, all of it ready once the pages are reserved, in one launch (three of 3-23 us each, one after the other, before):
+// workgroup 0 the attention's work list, the next `rope_groups` the rotary table and the rows' cache slots, the others the first operand: FIRST_EMBED
+// a row of the embedding and its norm each, FIRST_FEATURES a piece of the multi-layer features before w_fc, FIRST_NONE nothing.
+constexpr int FIRST_NONE = 0, FIRST_EMBED = 1, FIRST_FEATURES = 2;
+struct BeginArgs {
+    int B, T, M, rope_groups;
+    KvView kv;
+    AttnPlanArgs plan;
+    int half;
+    double theta;
+    float2* rope;
+    int32_t* row_slot;
+    // FIRST_EMBED
+    float* x;
+    const int32_t* tokens;
+    const unsigned short *embed, *gain;
+    int vocab, d;
+    float eps;
+    // FIRST_FEATURES
+    const float* features;
+    int K;
+    int mb_pad, xf;
+    uint4* xp;
+};
+template <int FIRST>
+__global__ __launch_bounds__(512) void begin_kernel(BeginArgs a)
+{
+    const int g = blockIdx.x;
+    if (g == 0) attn_plan(a.B, a.T, a.kv, a.plan);
+    else if (g <= a.rope_groups) rope_table((g - 1) * blockDim.x + threadIdx.x, a.M, a.T, a.kv, a.half, a.theta, a.rope, a.row_slot);
+    else if (FIRST == FIRST_EMBED) residual_rmsnorm<RES_EMBED>(g - 1 - a.rope_groups, a.x, nullptr, 0, 0, a.tokens, a.embed, a.vocab, a.gain, a.d, a.eps, a.mb_pad, a.xf, a.xp);
+    else if (FIRST == FIRST_FEATURES) pack_rows((int64_t)(g - 1 - a.rope_groups) * blockDim.x + threadIdx.x, a.features, a.M, a.K, a.mb_pad, a.xp);
 }
 
 // the residual stream [M, d] into columns col0 .. col0+d-1 of the feature rows [M, width]
@@ -465,8 +505,14 @@ spec_status bf16_forward(spec_model* mdl, spec_kv* kv, int B, int k, const int32
     auto xf_of = [](const PackedW& W) { return W.f16 ? XF_F16 : XF_HILO; };
     if (!mdl->moe() && mdl->wgu[0].f16 != mdl->wd[0].f16) { set_error("bf16 forward: gate/up and down projection must take the same activation format"); return SPEC_ESTATE; }
 
-    rope_table_kernel<<<(unsigned)cdiv((int64_t)M * 64, 256), 256, 0, s>>>(M, T, view, 64, (double)d.rope_theta, rope, row_slot);
-    if ((st = launch_attention_plan(B, T, G, Hkv, view, live_pages, att_items, att_entry_items, s)) != SPEC_OK) return st;
+    BeginArgs begin{};
+    begin.B = B; begin.T = T; begin.M = M;
+    begin.rope_groups = (int)cdiv((int64_t)M * 64, norm_threads);
+    begin.kv = view;
+    begin.plan = attention_plan_args(B, T, G, Hkv, live_pages, att_items, att_entry_items);
+    begin.half = 64; begin.theta = (double)d.rope_theta; begin.rope = rope; begin.row_slot = row_slot;
+    begin.x = x; begin.tokens = dev_tokens; begin.embed = (const unsigned short*)mdl->embed(); begin.gain = (const unsigned short*)mdl->layer_w(0, 0);
+    begin.vocab = d.vocab; begin.d = D; begin.eps = d.rms_eps; begin.mb_pad = p.mb_pad;
     if (d.fuse_hidden) {
         // hidden-state input: x = w_fuse . [RMSNorm(embed) ; RMSNorm(hidden_in)] (the feed-forward operand buffer is free here)
         const float* hidden = io.dev_hidden_in;
@@ -474,20 +520,23 @@ spec_status bf16_forward(spec_model* mdl, spec_kv* kv, int B, int k, const int32
         if (io.dev_features_in) {
             // multi-layer features: hidden = w_fc . features, left as K-split partial sums for the kernel below
             const int Kf = d.fuse_taps * D;
-            pack_rows_kernel<<<(unsigned)cdiv((int64_t)M * (Kf / 8), 256), 256, 0, s>>>(io.dev_features_in, M, Kf, p.mb_pad, (uint4*)xp_f);
+            begin.features = io.dev_features_in; begin.K = Kf; begin.xp = (uint4*)xp_f;
+            begin_kernel<FIRST_FEATURES><<<(unsigned)(1 + begin.rope_groups + cdiv((int64_t)M * (Kf / 8), norm_threads)), norm_threads, 0, s>>>(begin);
             if ((st = launch_gemm_bf16(mdl->wfc, xp_f, M, part, D, p.s_fc, false, s)) != SPEC_OK) return st;
             hidden = part;
             h_splits = p.s_fc;
+        } else {
+            begin_kernel<FIRST_NONE><<<(unsigned)(1 + begin.rope_groups), norm_threads, 0, s>>>(begin);
         }
         fuse_input_kernel<<<M, norm_threads, 0, s>>>(dev_tokens, (const unsigned short*)mdl->embed(), d.vocab, hidden, h_splits, (int64_t)M * D,
                                                      (const unsigned short*)mdl->fuse_w(1), (const unsigned short*)mdl->fuse_w(2), D, d.rms_eps,
                                                      p.mb_pad, (uint4*)xp_f);
         if ((st = launch_gemm_bf16(mdl->wfuse, xp_f, M, part, D, p.s_fuse, false, s)) != SPEC_OK) return st;
-        residual_rmsnorm_kernel<RES_SET><<<M, norm_threads, 0, s>>>(x, part, p.s_fuse, (int64_t)M * D, nullptr, nullptr, 0,
-                                                                   (const unsigned short*)mdl->layer_w(0, 0), D, d.rms_eps, p.mb_pad, xf_of(mdl->wqkv[0]), (uint4*)xp_h);
+        residual_rmsnorm_kernel<RES_SET><<<M, norm_threads, 0, s>>>(x, part, p.s_fuse, (int64_t)M * D, (const unsigned short*)mdl->layer_w(0, 0), D, d.rms_eps,
+                                                                   p.mb_pad, xf_of(mdl->wqkv[0]), (uint4*)xp_h);
     } else {
-        residual_rmsnorm_kernel<RES_EMBED><<<M, norm_threads, 0, s>>>(x, nullptr, 0, 0, dev_tokens, (const unsigned short*)mdl->embed(), d.vocab,
-                                                        (const unsigned short*)mdl->layer_w(0, 0), D, d.rms_eps, p.mb_pad, xf_of(mdl->wqkv[0]), (uint4*)xp_h);
+        begin.xf = xf_of(mdl->wqkv[0]); begin.xp = (uint4*)xp_h;
+        begin_kernel<FIRST_EMBED><<<(unsigned)(1 + begin.rope_groups + M), norm_threads, 0, s>>>(begin);
     }
     prof_mark(PC_EMBED_NORM, s);
     // the residual stream after `done` layers into every feature column block that asks for it
@@ -509,7 +558,7 @@ spec_status bf16_forward(spec_model* mdl, spec_kv* kv, int B, int k, const int32
         if ((st = launch_gemm_bf16(mdl->wo[l], xp_a, M, part, D, p.s_o, false, s)) != SPEC_OK) return st;
         prof_mark(PC_GEMM_O, s);
         // (mixture of experts: the router reads this buffer and stays hi + lo; the gather below converts for the experts)
-        residual_rmsnorm_kernel<RES_ADD><<<M, norm_threads, 0, s>>>(x, part, p.s_o, (int64_t)M * D, nullptr, nullptr, 0,
+        residual_rmsnorm_kernel<RES_ADD><<<M, norm_threads, 0, s>>>(x, part, p.s_o, (int64_t)M * D,
                                                          (const unsigned short*)mdl->layer_w(l, 5), D, d.rms_eps, p.mb_pad,
                                                          mdl->moe() ? xf_of(mdl->router[l]) : xf_of(mdl->wgu[l]), (uint4*)xp_h);
         prof_mark(PC_RESID_NORM, s);
@@ -553,7 +602,7 @@ spec_status bf16_forward(spec_model* mdl, spec_kv* kv, int B, int k, const int32
         }
         if ((st = launch_gemm_bf16(mdl->wd[l], xp_f, M, part, D, p.s_down, false, s)) != SPEC_OK) return st;
         prof_mark(PC_GEMM_DOWN, s);
-        residual_rmsnorm_kernel<RES_ADD><<<M, norm_threads, 0, s>>>(x, part, p.s_down, (int64_t)M * D, nullptr, nullptr, 0,
+        residual_rmsnorm_kernel<RES_ADD><<<M, norm_threads, 0, s>>>(x, part, p.s_down, (int64_t)M * D,
                                                          (const unsigned short*)next_gain, D, d.rms_eps, p.mb_pad, next_xf, (uint4*)xp_h);
         prof_mark(PC_RESID_NORM, s);
         write_taps(l + 1);

@@ -780,3 +780,13 @@ def test_f32_fused_projections_and_split_attention(B, k, changes):
     ok, max_err, worst = _run_custom_bf16(ctx, k=k, seed=B + k, **cfg)
     print("fp32 B=%d k=%d %s: logits max abs err %.3e" % (B, k, changes, max_err))
     assert ok and max_err <= 1e-4, (max_err, worst)
+
+
+@pytest.mark.parametrize("B,k", [(63, 0), (257, 1), (1030, 0)])
+def test_bf16_work_list_of_many_entries(B, k):
+    """The work list of the attention over more entries than the workgroup has threads, and than it keeps page counts of; empty caches among them."""
+    ctx = [(7 * b) % 41 for b in range(B)]
+    ctx[B // 2] = 900
+    ok, max_err, worst = _run_custom_bf16(ctx, k=k, seed=B + k, vocab=500, n_layers=1)
+    print("B=%d k=%d: logits max abs err %.3e" % (B, k, max_err))
+    assert ok, (max_err, worst)
