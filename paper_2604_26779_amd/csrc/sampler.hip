@@ -55,7 +55,7 @@ __device__ inline void part_groups(int V, int part, int* g0, int* g1)
 // ulps was noise; in fp64 the choice differs from an fp64 reference's only where its own keys agree to 15 digits.
 //
 // What keeps that cheap (both kernels should be bound by reading the logits):
-//   * the sums need an fp64 exponential per entry: exp_sum below, 18 fp64 instructions, no branch, no special cases;
+//   * the sums need an fp64 exponential per entry: exp_sum below, 17 fp64 instructions, no branch, no special cases;
 //   * a race needs its keys in fp64 only where they can win: every entry's key is first bounded in fp32 from above and
 //     below, and the entries whose upper bound reaches the best lower bound known to the wavefront are then evaluated in fp64.
 //     Those are few unless the weights cancel: a residual that is rounding noise everywhere (q = p) leaves every entry.
@@ -70,7 +70,8 @@ __device__ inline double fma_const(double a, double b, double c)
     return d;
 }
 
-// exp(x) for x <= 0, without a branch: x = n ln 2 + r, |r| <= ln 2 / 2, Taylor to r^12 (remainder 1.7e-16), 2^n through the
+// exp(x) for x <= 0, without a branch: x = n ln 2 + r, |r| <= ln 2 / 2, 1 + r + r^2 / 2 + r^3 p(r) with p of degree 8 interpolating
+// (e^r - 1 - r - r^2 / 2) / r^3 at the Chebyshev nodes of that range (error 3.4e-17 of e^r; Taylor to r^12, one term more, 2.3e-16), 2^n through the
 // exponent bits.  The rounding of ln 2 to a double adds n 2.3e-17: an ulp at n = 10, and a term of a sum that small weighs 2^-n.
 // Arguments below -708 (and NaN) count as -708: 3e-308, nothing beside the largest term of 1.
 __device__ inline double exp_sum(double x)
@@ -80,51 +81,68 @@ __device__ inline double exp_sum(double x)
     const double t = __builtin_fma(x, 1.4426950408889634074, magic);
     const double n = t - magic;
     const double r = __builtin_fma(n, -0.6931471805599453094, x);
-    double p = fma_const(r, 1.0 / 479001600.0, 1.0 / 39916800.0);
-    p = fma_const(p, r, 1.0 / 3628800.0);
-    p = fma_const(p, r, 1.0 / 362880.0);
-    p = fma_const(p, r, 1.0 / 40320.0);
-    p = fma_const(p, r, 1.0 / 5040.0);
-    p = fma_const(p, r, 1.0 / 720.0);
-    p = fma_const(p, r, 1.0 / 120.0);
-    p = fma_const(p, r, 1.0 / 24.0);
-    p = fma_const(p, r, 1.0 / 6.0);
+    double p = fma_const(r, 0x1.af2360e209be0p-26, 0x1.28803926c8ebbp-22);
+    p = fma_const(p, r, 0x1.71de17e7960e6p-19);
+    p = fma_const(p, r, 0x1.a019c9ab213aap-16);
+    p = fma_const(p, r, 0x1.a01a01a4b26e2p-13);
+    p = fma_const(p, r, 0x1.6c16c1738ecf7p-10);
+    p = fma_const(p, r, 0x1.1111111110e6bp-7);
+    p = fma_const(p, r, 0x1.5555555554cb8p-5);
+    p = fma_const(p, r, 0x1.5555555555555p-3);
     p = __builtin_fma(p, r, 0.5);
     p = __builtin_fma(p, r, 1.0);
     p = __builtin_fma(p, r, 1.0);
     return __hiloint2double(__double2hiint(p) + (__double2loint(t) << 20), __double2loint(p));
 }
 
-// The SAMP_GPT groups of a lane: group u starts at entry 4 (gb + u * SAMP_THREADS + lane); entries at or beyond group g1 or entry V
-// come out as `pad`.  VEC: the row is 16-byte aligned and V a multiple of 4; the loads then go out together, with no branch
-// between them (beyond g1 the last group is read again).
+// largest of the wavefront's values, in every lane: vector instructions only (a shuffle would take six trips through the LDS crossbar)
+__device__ inline float wave_max(float x)
+{
+    unsigned u = __float_as_uint(x);
+    auto a = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    x = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    u = __float_as_uint(x);
+    auto b = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    x = fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+    x = fmaxf(x, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x128, 0xf, 0xf, false)));      // row_ror:8, 4, 2, 1
+    x = fmaxf(x, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x124, 0xf, 0xf, false)));
+    x = fmaxf(x, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x122, 0xf, 0xf, false)));
+    return fmaxf(x, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x121, 0xf, 0xf, false)));
+}
+
+// GPT groups of a lane: group u starts at entry 4 (gb + u * SAMP_THREADS + lane).  VEC: the row is 16-byte aligned and V a multiple of 4.  The loads go out
+// together, with no branch between them: beyond group g1 the last group is read again, beyond entry V the last entry.
+template <bool VEC, int GPT>
+__device__ inline void load_round(const float* __restrict__ row, int gb, int g1, int V, float (&v)[GPT][4])
+{
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int u = 0; u < GPT; ++u) {
+        const int g = gb + u * SAMP_THREADS + lane, gc = g < g1 ? g : g1 - 1;
+        if constexpr (VEC) {
+            const float4 a = *(const float4*)(row + 4 * (int64_t)gc);
+            v[u][0] = a.x; v[u][1] = a.y; v[u][2] = a.z; v[u][3] = a.w;
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int at = 4 * gc + j;
+                v[u][j] = row[at < V ? at : V - 1];
+            }
+        }
+    }
+}
+// the same with `pad` in the place of what lies beyond
 template <bool VEC>
 __device__ inline void load_round(const float* __restrict__ row, int gb, int g1, int V, float pad, float (&v)[SAMP_GPT][4])
 {
-    const int lane = threadIdx.x & 63;
-    if constexpr (VEC) {
-        float4 a[SAMP_GPT];
+    load_round<VEC, SAMP_GPT>(row, gb, g1, V, v);
 #pragma unroll
-        for (int u = 0; u < SAMP_GPT; ++u) {
-            const int g = gb + u * SAMP_THREADS + lane;
-            a[u] = *(const float4*)(row + 4 * (int64_t)(g < g1 ? g : g1 - 1));
+    for (int u = 0; u < SAMP_GPT; ++u)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int g = gb + u * SAMP_THREADS + (threadIdx.x & 63);
+            if (!(g < g1 && (VEC || 4 * g + j < V))) v[u][j] = pad;
         }
-#pragma unroll
-        for (int u = 0; u < SAMP_GPT; ++u) {
-            const bool in = gb + u * SAMP_THREADS + lane < g1;
-            v[u][0] = in ? a[u].x : pad; v[u][1] = in ? a[u].y : pad; v[u][2] = in ? a[u].z : pad; v[u][3] = in ? a[u].w : pad;
-        }
-    } else {
-#pragma unroll
-        for (int u = 0; u < SAMP_GPT; ++u)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int g = gb + u * SAMP_THREADS + lane, at = 4 * g + j;
-                const bool in = g < g1 && at < V;
-                const float l = row[in ? at : V - 1];
-                v[u][j] = in ? l : pad;
-            }
-    }
 }
 // whether every row of an array can be read in 16-byte words
 static bool rows_vec(const void* rows, int64_t stride, int V) { return ((uintptr_t)rows & 15) == 0 && (stride & 3) == 0 && (V & 3) == 0; }
@@ -136,21 +154,45 @@ __device__ inline double uniform(double x)
 }
 
 // groups per lane that the round starting at group gb holds (the same for a wavefront)
+template <int GPT>
 __device__ inline int round_groups(int gb, int g1)
 {
     const int n = (g1 - gb + SAMP_THREADS - 1) / SAMP_THREADS;
-    return n < SAMP_GPT ? n : SAMP_GPT;
+    return n < GPT ? n : GPT;
 }
 
-// (largest logit, sum of exp((logit - largest) / T)) of one range of a row.  Each wavefront reads its entries once, takes the maximum
-// of the 16 entries per lane that are in registers as the reference (moving it, and what has been summed, when a later
-// round exceeds it), so there is no second pass over the logits and no barrier before the sums; the wavefronts' pairs are
+// N lanes side by side (a power of two; every N-th lane's group of a wavefront for itself) hold (M_i, S_i); all get M = max M_i and
+// S = sum_i S_i exp((M_i - M) / T), summed in a fixed order.
+template <int N>
+__device__ inline double2 merge_stats(double2 c, double rT)
+{
+    double M = c.x;
+    for (int off = N / 2; off > 0; off >>= 1) M = fmax(M, __shfl_xor(M, off));
+    double S = c.y > 0.0 ? c.y * exp_sum((c.x - M) * rT) : 0.0;
+    for (int off = N / 2; off > 0; off >>= 1) S += __shfl_xor(S, off);
+    return make_double2(M, S);
+}
+
+// a row's statistics from those of its ranges, SAMP_PARTS lanes a row (each with its range's): M = max m_p, S = sum_p s_p exp((m_p - M) / T).  M stays
+// a logit: M / T is formed where it is needed, as M cannot be had back from it when T is infinite (0) or subnormal.  S = 0 says that the row has no
+// distribution: it is -inf throughout, or holds +inf (exp_sum gives such a row's terms the value of exp(-708), not NaN).  Its
+// probabilities are then NaN as 0 / 0 is: no accept test passes and no key is kept.
+__device__ inline double2 row_stat(const double2* __restrict__ stats, int64_t row, double rT)
+{
+    const double2 st = merge_stats<SAMP_PARTS>(stats[row * SAMP_PARTS + (threadIdx.x & (SAMP_PARTS - 1))], rT);
+    return make_double2(st.x, st.x == INFINITY ? 0.0 : st.y);
+}
+
+// (largest logit, sum of exp((logit - largest) / T)) of one range of a row.  Each wavefront reads its entries once, STAT_GPT groups of 4 per lane
+// at a time (for vocabularies of up to 131072 all of them), takes the maximum of what is in registers as the reference (moving it, and what has been
+// summed, when a later round exceeds it), so there is no second pass over the logits and no barrier before the sums; the wavefronts' pairs are
 // merged in a fixed order.
-// Bound by its vector instructions (32 per entry, most of them fp64 at the fp32 rate) with the reads beside them: 1024 rows take
-// 128-130 us = 4.1 TB/s, 355 us as two passes with the library's exponential and a barrier between them; 384 rows 51-55 us, 122 before.
+// Bound by its vector instructions (22 per entry, 17 of them fp64 at the fp32 rate) with the reads beside them; 384 rows of 128256 take 47 us = 4.2 TB/s, 1024 rows
+// 118 (55 and 140 on the same boxes with a Taylor series of one term more, two rounds a wavefront and a serial merge; 122 and 355 as two passes with the library's exponential).
 // (zero_rows != null: the workgroup also clears its eighth of row blockIdx.x of that array, zero_width entries wide - the
 // q rows a mapped draft draw then fills at scattered positions; counters != null: the sequences' arrival counters of the
 // scan that follows, counter_rows rows per sequence)
+constexpr int STAT_GPT = 8;
 template <bool VEC>
 __global__ __launch_bounds__(SAMP_THREADS) void row_stats_kernel(const float* __restrict__ logits, int64_t row_stride, int V, double rT,
                                                                   double2* __restrict__ stats, int32_t* __restrict__ counters,
@@ -168,65 +210,60 @@ __global__ __launch_bounds__(SAMP_THREADS) void row_stats_kernel(const float* __
     int g0, g1;
     part_groups(V, blockIdx.y, &g0, &g1);
     __shared__ double2 l_st[SAMP_WAVES];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     float ref = -INFINITY;                                           // of this wavefront; raw fp32 logit (z is monotone in it)
     double sum = 0.0;
-    for (int gb = g0 + wave * 64; gb < g1; gb += SAMP_THREADS * SAMP_GPT) {
-        float v[SAMP_GPT][4];
+    for (int gb = g0 + wave * 64; gb < g1; gb += SAMP_THREADS * STAT_GPT) {
+        float v[STAT_GPT][4];
+        const int n_u = round_groups<STAT_GPT>(gb, g1);
+        // what lies beyond the range comes out as another entry of it: nothing for the maximum, and taken out before the sums below
+        load_round<VEC, STAT_GPT>(row, gb, g1, V, v);
         float mx = -INFINITY;
-        const int n_u = round_groups(gb, g1);
-        load_round<VEC>(row, gb, g1, V, -INFINITY, v);
 #pragma unroll
-        for (int u = 0; u < SAMP_GPT; ++u)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) mx = v[u][j] > mx ? v[u][j] : mx;          // NaN compares false: left out, as below
-        for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+        for (int u = 0; u < STAT_GPT; ++u) {
+            asm("v_max3_f32 %0, %1, %2, %0" : "+v"(mx) : "v"(v[u][0]), "v"(v[u][1]));            // a NaN is left out, as below
+            asm("v_max3_f32 %0, %1, %2, %0" : "+v"(mx) : "v"(v[u][2]), "v"(v[u][3]));
+        }
+        mx = wave_max(mx);
         if (mx > ref) {                                              // wavefront-uniform
             if (ref > -INFINITY) sum *= exp_sum(((double)ref - (double)mx) * rT);
             ref = mx;
         }
         if (ref == -INFINITY) continue;
         const double m = (double)ref;
-#pragma unroll
-        for (int u = 0; u < SAMP_GPT; ++u) {
-            if (u >= n_u) break;
+        auto add = [&](int u) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const float l = v[u][j];
                 sum += exp_sum(((double)l - m) * rT);                 // the difference is exact: the largest term is exactly 1
             }
+        };
+        const bool whole = gb + (n_u - 1) * SAMP_THREADS + 63 < g1 && (VEC || 4 * (gb + (n_u - 1) * SAMP_THREADS + 64) <= V);
+        if (!whole) {                                                // wavefront-uniform; groups before the last are whole
+#pragma unroll
+            for (int u = 0; u < STAT_GPT; ++u)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int g = gb + u * SAMP_THREADS + lane;
+                    if (!(g < g1 && 4 * g + j < V)) v[u][j] = -INFINITY;
+                }
+        }
+#pragma unroll
+        for (int u = 0; u < STAT_GPT; ++u) {
+            if (u >= n_u) break;
+            add(u);
         }
     }
-    // fixed order: butterfly inside a wavefront, then the wavefronts one after the other
+    // fixed order: butterfly inside a wavefront, then over the wavefronts
     for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
     if (lane == 0) l_st[wave] = make_double2((double)ref, sum);
     __syncthreads();
-    if (threadIdx.x == 0) {
-        double M = -INFINITY, S = 0.0;
-        for (int w = 0; w < SAMP_WAVES; ++w) M = fmax(M, l_st[w].x);
-        for (int w = 0; w < SAMP_WAVES; ++w)
-            if (l_st[w].y > 0.0) S += l_st[w].y * exp_sum((l_st[w].x - M) * rT);
-        if (M == INFINITY) S = 0.0;                                  // no distribution (see row_stat)
-        stats[(int64_t)blockIdx.x * SAMP_PARTS + blockIdx.y] = make_double2(M, S);
+    if (wave == 0) {
+        const double2 c = l_st[lane & (SAMP_WAVES - 1)];
+        double2 st = merge_stats<SAMP_WAVES>(c, rT);
+        if (st.x == INFINITY) st.y = 0.0;                            // no distribution (see row_stat)
+        if (lane == 0) stats[(int64_t)blockIdx.x * SAMP_PARTS + blockIdx.y] = st;
     }
-}
-
-// a row's statistics from those of its ranges, in range order: M = max m_p, S = sum_p s_p exp((m_p - M) / T).  M stays a logit: M / T is
-// formed where it is needed, as M cannot be had back from it when T is infinite (0) or subnormal.  S = 0 says that the row has no
-// distribution: it is -inf throughout, or holds +inf (exp_sum gives such a row's terms the value of exp(-708), not NaN).  Its
-// probabilities are then NaN as 0 / 0 is: no accept test passes and no key is kept.
-__device__ inline double2 row_stat(const double2* __restrict__ stats, int64_t row, double rT)
-{
-    double2 c[SAMP_PARTS];
-#pragma unroll
-    for (int p = 0; p < SAMP_PARTS; ++p) c[p] = stats[row * SAMP_PARTS + p];
-    double M = -INFINITY;
-#pragma unroll
-    for (int p = 0; p < SAMP_PARTS; ++p) M = fmax(M, c[p].x);
-    double S = 0.0;
-#pragma unroll
-    for (int p = 0; p < SAMP_PARTS; ++p) S += c[p].y > 0.0 ? c[p].y * exp_sum((c[p].x - M) * rT) : 0.0;
-    return make_double2(M, M == INFINITY ? 0.0 : S);
 }
 
 __device__ inline void argmax_merge(double& key, int& v, double key2, int v2)
@@ -376,7 +413,7 @@ __device__ inline void race_scan(const RaceRow& row, const RaceExponent& exponen
         float l[SAMP_GPT][4], qv[SAMP_GPT][4];
         load_round<VEC>(row.l, gb, g1, row.V, -INFINITY, l);
         if (KIND == RACE_RES) load_round<VEC>(row.q, gb, g1, row.V, 0.f, qv);
-        race_round<KIND>(row, l, qv, gb, g1, round_groups(gb, g1), exponent, rS, reach, best, best_v);
+        race_round<KIND>(row, l, qv, gb, g1, round_groups<SAMP_GPT>(gb, g1), exponent, rS, reach, best, best_v);
     }
 }
 
@@ -439,15 +476,18 @@ __global__ __launch_bounds__(SAMP_THREADS, 4) void reject_scan_kernel(
         const int i = threadIdx.x;
         bool ok = false;
         double P = 0.0, Q = 0.0, u = 0.0;
+        for (int r = i / SAMP_PARTS; r < (k + SAMP_PARTS) / SAMP_PARTS * SAMP_PARTS; r += 64 / SAMP_PARTS) {     // the same trips for all lanes
+            const double2 st = row_stat(stats, (int64_t)b * (k + 1) + (r <= k ? r : k), rT);
+            if (r <= k && i % SAMP_PARTS == 0) { s_st[r] = st; s_m[r] = st.x / T; }
+        }
+        __builtin_amdgcn_wave_barrier();
         if (i <= k) {
             const int x = i < k ? draft[(int64_t)b * k + i] : -1;
             const bool probe = x >= 0 && x < V;
             const float lx = probe ? L[(int64_t)i * V + x] : 0.f;
             Q = probe ? (Qb ? (double)Qb[(int64_t)i * V + x] : 1.0) : 0.0;      // no q array: one-hot drafts (a deterministic drafter)
-            const double2 st = row_stat(stats, (int64_t)b * (k + 1) + i, rT);
-            const double m = st.x / T;
-            s_st[i] = st;
-            s_m[i] = m;
+            const double2 st = s_st[i];
+            const double m = s_m[i];
             if (probe) {
                 P = exp((double)lx / T - m) / st.y;
                 const Philox4 r = philox4x32_10(0u, (uint32_t)i, (uint32_t)b, step4 + 0u, seed_lo, seed_hi);
@@ -510,7 +550,7 @@ __global__ __launch_bounds__(SAMP_THREADS, 4) void reject_scan_kernel(
 // stream 2.  row_stats_kernel gives the ranges' statistics; draft_scan_kernel (workgroup = sequence, range) merges them,
 // writes its range of q and finds its range's best key; the workgroup that finishes a sequence last picks the token.
 // Bound as reject_scan_kernel, with an fp64 exponential more per entry.  With its statistics the draw takes 125-130 us at B = 256,
-// V = 128256 (335 before) and 40-42 us at B = 64 (87 before).
+// V = 128256 (335 before) and 40-43 us at B = 64 (87 before).
 template <bool VEC, bool MAPPED>
 __global__ __launch_bounds__(SAMP_THREADS, 4) void draft_scan_kernel(
     int V, const float* __restrict__ logits, int64_t logits_stride, double T, double rT, uint32_t seed_lo, uint32_t seed_hi,
@@ -525,14 +565,8 @@ __global__ __launch_bounds__(SAMP_THREADS, 4) void draft_scan_kernel(
     __shared__ int lv[SAMP_WAVES];
     __shared__ int s_last;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    // the row's statistics, one range per lane (every group of 8 lanes the same)
-    const double2 c = stats[(int64_t)b * SAMP_PARTS + (lane & (SAMP_PARTS - 1))];
-    double m = c.x;
-    for (int off = SAMP_PARTS / 2; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off));
-    double S = c.y > 0.0 ? c.y * exp_sum((c.x - m) * rT) : 0.0;
-    for (int off = SAMP_PARTS / 2; off > 0; off >>= 1) S += __shfl_xor(S, off);
-    m = uniform(m);
-    S = m == INFINITY ? 0.0 : uniform(S);
+    const double2 st = row_stat(stats, b, rT);
+    const double m = uniform(st.x), S = uniform(st.y);
     const double rS = S > 0.0 ? 1.0 / S : NAN;                      // without a distribution q is NaN, and the verifier rejects the -1 drawn from it
     const RaceExponent exponent((float)m, rT);
     const float rS32 = (float)rS;
@@ -546,7 +580,7 @@ __global__ __launch_bounds__(SAMP_THREADS, 4) void draft_scan_kernel(
     const RaceRow race = {lrow, nullptr, V, -1, T, m / T, S, seed_lo, seed_hi, row, (uint32_t)b, step4 + 2u};
     for (int gb = g0 + wave * 64; gb < g1; gb += SAMP_THREADS * SAMP_GPT) {
         float l[SAMP_GPT][4];
-        const int n_u = round_groups(gb, g1);
+        const int n_u = round_groups<SAMP_GPT>(gb, g1);
         load_round<VEC>(lrow, gb, g1, V, -INFINITY, l);
 #pragma unroll
         for (int u = 0; u < SAMP_GPT; ++u) {
