@@ -20,7 +20,10 @@
 //                           O^T += V^T P^T v_mfma_f32_16x16x16_bf16 (P^T comes out of S^T's
 //                                          accumulator layout without any shuffle);
 //                         the wavefronts' results are merged through LDS and written as an
-//                         un-normalised partial (O, reference point, sum).
+//                         un-normalised partial (O, reference point, sum).  What it needs of the QKV projection it sums from
+//                         the K-split slices and rotates itself, its rows' queries and the new keys and values of its pages, which
+//                         it writes to the cache.  A kernel of its own for that took 4.5-12.5 us per layer where the attention now takes 2.5-11
+//                         more (8B shape, step at batch 1, 7 and 32: 3 324 -> 3 269, 4 427 -> 4 352, 7 813 -> 7 774 us; equal at 384 rows and more).
 //   attn_reduce_kernel  : merges the chunks of a (batch entry, kv head) and writes the bf16 result
 //                         in the operand order the O-projection GEMM reads.
 // Row r of a (batch entry, kv head) tile is input position r / G, query head kvh*G + r % G.
@@ -87,7 +90,7 @@ __device__ inline float quad_sum(float x)
 // folded into the score scale here, the value scale into the final normalisation (attn_reduce_kernel).
 template <int NRB, bool KV8>
 __global__ __launch_bounds__(256, NRB <= 2 ? 2 : 1) void attn_partial_kernel(
-    const float* __restrict__ q, int T, int G, int Hq, const AttnItem* __restrict__ items, int max_items, KvView kv,
+    QkvSlices in, int T, int G, int Hq, const AttnItem* __restrict__ items, int max_items, KvView kv,
     int layer_pool, int layer, float scale_log2_in, int RG, int rows, int Hkv, int IP,
     float* __restrict__ part_o, float* __restrict__ part_ml)
 {
@@ -111,19 +114,118 @@ __global__ __launch_bounds__(256, NRB <= 2 ? 2 : 1) void attn_partial_kernel(
     __shared__ u32x4_t s_q[NRB][4][2][64];                      // [row block][32 channels][hi | lo][lane]
     __shared__ float s_o[ATT_WAVES][8][64][4];
     __shared__ float s_m[ATT_WAVES][16], s_l[ATT_WAVES][16];
-    for (int f = wave; f < NRB * 4; f += ATT_WAVES) {
-        const int rb = f >> 2, sgm = f & 3;
+    const int32_t* pt = kv.page_table + (int64_t)seq * kv.max_pages;
+    // lane j: physical id of this wavefront's j-th page (chunk_pages <= 256: at most 64 per wavefront), clamped to the chunk
+    int my_pid;
+    {
+        int pg = page0 + wave + ATT_WAVES * lane;
+        my_pid = pt[pg < page_end ? pg : page_end - 1];
+    }
+    // sum of the slices of N adjacent floats, in slice order, the loads four slices at a time
+    auto sum_slices = [&](const float* p, auto n_c, float* v) {
+        constexpr int N = decltype(n_c)::value;
+        typedef float vec_t __attribute__((ext_vector_type(4)));
+#pragma unroll
+        for (int j = 0; j < N; ++j) v[j] = 0.f;
+        auto add = [&](int s0, auto g_c) {
+            constexpr int GN = decltype(g_c)::value;
+            vec_t x[GN][N / 4];
+#pragma unroll
+            for (int u = 0; u < GN; ++u)
+#pragma unroll
+                for (int h = 0; h < N / 4; ++h) x[u][h] = *(const vec_t*)(p + (s0 + u) * in.split_stride + 4 * h);
+#pragma unroll
+            for (int u = 0; u < GN; ++u)
+#pragma unroll
+                for (int j = 0; j < N; ++j) v[j] += x[u][j >> 2][j & 3];
+        };
+        int s0 = 0;
+        for (; s0 + 4 <= in.splits; s0 += 4) add(s0, std::integral_constant<int, 4>{});
+        if (s0 + 2 <= in.splits) { add(s0, std::integral_constant<int, 2>{}); s0 += 2; }
+        if (s0 < in.splits) add(s0, std::integral_constant<int, 1>{});
+    };
+    using n4_t = std::integral_constant<int, 4>;
+    using n8_t = std::integral_constant<int, 8>;
+    // the queries: channels c .. c+7 and c+64 .. c+71 of a row are rotated together
+    for (int f = wave; f < NRB * 2; f += ATT_WAVES) {
+        const int rb = f >> 1, sgm = f & 1;
         const int r = (rb0 + rb) * 16 + lq;
-        float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        float lo[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, hi[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
         if (r < R) {
-            const float* src = q + ((int64_t)(b * T + r / G) * Hq + kvh * G + r % G) * DH + lg * 8 + sgm * 32;
-            float4 a = *(const float4*)src, c = *(const float4*)(src + 4);
-            v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = c.x; v[5] = c.y; v[6] = c.z; v[7] = c.w;
+            const int64_t m = b * T + r / G;
+            const int c0 = lg * 8 + sgm * 32;
+            const float* src = in.part + m * in.ld + (kvh * G + r % G) * DH + c0;
+            const float4* cs = (const float4*)(in.rope + m * (DH / 2) + c0);
+            float l[8], h[8];
+            sum_slices(src, n8_t{}, l);
+            sum_slices(src + DH / 2, n8_t{}, h);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float4 a = cs[j];                                      // cos, sin of two angles
+                lo[2 * j] = l[2 * j] * a.x - h[2 * j] * a.y;
+                hi[2 * j] = h[2 * j] * a.x + l[2 * j] * a.y;
+                lo[2 * j + 1] = l[2 * j + 1] * a.z - h[2 * j + 1] * a.w;
+                hi[2 * j + 1] = h[2 * j + 1] * a.z + l[2 * j + 1] * a.w;
+            }
         }
         uint4 h4, l4;
-        split8(v, h4, l4);
+        split8(lo, h4, l4);
         s_q[rb][sgm][0][lane] = u32x4_t{h4.x, h4.y, h4.z, h4.w};
         s_q[rb][sgm][1][lane] = u32x4_t{l4.x, l4.y, l4.z, l4.w};
+        split8(hi, h4, l4);
+        s_q[rb][sgm + 2][0][lane] = u32x4_t{h4.x, h4.y, h4.z, h4.w};
+        s_q[rb][sgm + 2][1][lane] = u32x4_t{l4.x, l4.y, l4.z, l4.w};
+    }
+    // The new positions that lie in this item's pages go to the cache (speculatively: ctx .. ctx+k): 16 pieces of four rotated key channels and
+    // their partners, 32 of four value channels each.  They are read back from there below, by this workgroup only; row groups of the same item
+    // write the same values.
+    if (page_end > ctx / SPEC_PAGE_SIZE) {
+        const int i0 = page0 * SPEC_PAGE_SIZE > ctx ? page0 * SPEC_PAGE_SIZE - ctx : 0;
+        const int i1 = (page_end * SPEC_PAGE_SIZE < total ? page_end * SPEC_PAGE_SIZE : total) - ctx;
+        for (int e = 255 - threadIdx.x; e < (i1 - i0) * 48; e += 256) {        // (the last wavefronts first: the others may have queries to do)
+            const int i = i0 + e / 48, piece = e % 48, pos = ctx + i, t = pos % SPEC_PAGE_SIZE;
+            const int64_t m = b * T + i, at = ((int64_t)layer_pool * kv.n_pages + pt[pos / SPEC_PAGE_SIZE]) * 2;
+            const float* row = in.part + m * in.ld;
+            if (piece < 16) {
+                const int j = piece * 4;
+                float l[4], h[4], rl[4], ru[4];
+                sum_slices(row + (Hq + kvh) * DH + j, n4_t{}, l);
+                sum_slices(row + (Hq + kvh) * DH + j + DH / 2, n4_t{}, h);
+                const float2* cs = in.rope + m * (DH / 2) + j;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const float2 c = cs[u];
+                    rl[u] = l[u] * c.x - h[u] * c.y;
+                    ru[u] = h[u] * c.x + l[u] * c.y;
+                }
+                if constexpr (KV8) {
+                    const float ks = kv.k_scale[layer * Hkv + kvh];
+                    unsigned char* dst = (unsigned char*)kv.pool + (at * Hkv + kvh) * (SPEC_PAGE_SIZE * DH);
+                    *(unsigned int*)(dst + kv_block_offset(SPEC_FP8_E4M3, 0, t, j, DH)) =
+                        to_e4m3(rl[0] / ks) | (to_e4m3(rl[1] / ks) << 8) | (to_e4m3(rl[2] / ks) << 16) | (to_e4m3(rl[3] / ks) << 24);
+                    *(unsigned int*)(dst + kv_block_offset(SPEC_FP8_E4M3, 0, t, j + DH / 2, DH)) =
+                        to_e4m3(ru[0] / ks) | (to_e4m3(ru[1] / ks) << 8) | (to_e4m3(ru[2] / ks) << 16) | (to_e4m3(ru[3] / ks) << 24);
+                } else {
+                    unsigned short* dst = (unsigned short*)kv.pool + (at * Hkv + kvh) * (SPEC_PAGE_SIZE * DH);
+                    *(uint2*)(dst + kv_block_offset(SPEC_BF16, 0, t, j, DH)) = make_uint2(pack_bf16x2(rl[0], rl[1]), pack_bf16x2(rl[2], rl[3]));
+                    *(uint2*)(dst + kv_block_offset(SPEC_BF16, 0, t, j + DH / 2, DH)) = make_uint2(pack_bf16x2(ru[0], ru[1]), pack_bf16x2(ru[2], ru[3]));
+                }
+            } else {
+                const int c = (piece - 16) * 4;
+                float v[4];
+                sum_slices(row + (Hq + Hkv + kvh) * DH + c, n4_t{}, v);
+                if constexpr (KV8) {
+                    const float vs = kv.v_scale[layer * Hkv + kvh];
+                    unsigned char* dst = (unsigned char*)kv.pool + ((at + 1) * Hkv + kvh) * (SPEC_PAGE_SIZE * DH);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) dst[kv_block_offset(SPEC_FP8_E4M3, 1, t, c + u, DH)] = (unsigned char)to_e4m3(v[u] / vs);
+                } else {
+                    unsigned short* dst = (unsigned short*)kv.pool + ((at + 1) * Hkv + kvh) * (SPEC_PAGE_SIZE * DH);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) dst[kv_block_offset(SPEC_BF16, 1, t, c + u, DH)] = to_bf16(v[u]);
+                }
+            }
+        }
     }
     int row_limit[NRB];
 #pragma unroll
@@ -132,18 +234,11 @@ __global__ __launch_bounds__(256, NRB <= 2 ? 2 : 1) void attn_partial_kernel(
         row_limit[rb] = r < R ? ctx + r / G : -1;
     }
 
-    const int32_t* pt = kv.page_table + (int64_t)seq * kv.max_pages;
     const u32x4_t* pool = (const u32x4_t*)kv.pool;
     const int64_t layer_base = (int64_t)layer_pool * kv.n_pages;
     auto block_ptr = [&](int physical_page, int is_v) {
         return pool + ((((layer_base + physical_page) * 2 + is_v) * Hkv + kvh) * (KV8 ? BLOCK_U4 / 2 : BLOCK_U4)) + lane;
     };
-    // lane j: physical id of this wavefront's j-th page (chunk_pages <= 256: at most 64 per wavefront), clamped to the chunk
-    int my_pid;
-    {
-        int pg = page0 + wave + ATT_WAVES * lane;
-        my_pid = pt[pg < page_end ? pg : page_end - 1];
-    }
     auto pid_at = [&](int it) { return __builtin_amdgcn_readlane(my_pid, it < 63 ? it : 63); };
 
     float mrow[NRB], lrow[NRB];
@@ -177,7 +272,7 @@ __global__ __launch_bounds__(256, NRB <= 2 ? 2 : 1) void attn_partial_kernel(
             return f[i];
         }
     };
-    __syncthreads();                                  // the queries are in LDS
+    __syncthreads();                                  // the queries are in LDS, the new keys and values in the cache
 
     // query fragments of one row block, double buffered: those of the next row block (of the next page after the
     // last) are read from LDS while the softmax of the current one runs
@@ -479,7 +574,7 @@ AttnPlanArgs attention_plan_args(int B, int T, int G, int Hkv, int pages_bound, 
     return AttnPlanArgs{pl.budget, min_pages, pl.forced, pl.max_items, (AttnItem*)items, (int2*)entry_items};
 }
 
-spec_status launch_attention_bf16(const float* q, int B, int T, int G, int Hq, int Hkv, const KvView& kv, int layer_pool, int layer,
+spec_status launch_attention_bf16(const QkvSlices& in, int B, int T, int G, int Hq, int Hkv, const KvView& kv, int layer_pool, int layer,
                                   int pages_bound, const void* items, const void* entry_items, float* part_o, float* part_ml,
                                   int mb_pad, int xf_out, bf16_t* xp_out, hipStream_t s)
 {
@@ -494,8 +589,8 @@ spec_status launch_attention_bf16(const float* q, int B, int T, int G, int Hq, i
     dim3 grid((unsigned)(Hkv * IP), (unsigned)(RG * cdiv(pl.max_items, IP)));
     const AttnItem* it = (const AttnItem*)items;
 #define SPEC_ATTN_LAUNCH(NRBV) do { \
-        if (kv.fp8) attn_partial_kernel<NRBV, true><<<grid, 256, 0, s>>>(q, T, G, Hq, it, pl.max_items, kv, layer_pool, layer, scale_log2, RG, rows, Hkv, IP, part_o, part_ml); \
-        else attn_partial_kernel<NRBV, false><<<grid, 256, 0, s>>>(q, T, G, Hq, it, pl.max_items, kv, layer_pool, layer, scale_log2, RG, rows, Hkv, IP, part_o, part_ml); \
+        if (kv.fp8) attn_partial_kernel<NRBV, true><<<grid, 256, 0, s>>>(in, T, G, Hq, it, pl.max_items, kv, layer_pool, layer, scale_log2, RG, rows, Hkv, IP, part_o, part_ml); \
+        else attn_partial_kernel<NRBV, false><<<grid, 256, 0, s>>>(in, T, G, Hq, it, pl.max_items, kv, layer_pool, layer, scale_log2, RG, rows, Hkv, IP, part_o, part_ml); \
     } while (0)
     switch (pl.RB) {
     case 1: SPEC_ATTN_LAUNCH(1); break;

@@ -12,6 +12,10 @@ constexpr int ATT_WAVES = 4;
 // last row; b = -1: unused slot of the list).  32 bytes, read with two 16-byte loads.
 struct AttnItem { int32_t b, seq, page0, page_end, ctx, total, chunk, pad; };
 
+// What the attention takes the new rows' queries, keys and values from: the K-split slices of the QKV projection (row m = b T + i, columns
+// q heads | k heads | v heads of 128) and cos, sin of every row's 64 angles.
+struct QkvSlices { const float* part; int splits; int64_t split_stride; int ld; const float2* rope; };
+
 struct AttnPlanArgs { int budget, min_pages, forced, max_items; AttnItem* items; int2* entry_items; };
 
 constexpr int PLAN_KEPT = 1024;              // batch entries whose page counts are kept in LDS

@@ -4,8 +4,7 @@
 // value, whichever its matrix was tiled for, see operand.h):
 //   xp_h  = RMSNorm(x) * g                         (fused into the kernel that last touched x)
 //   part  = xp_h W_qkv^T                           gemm, split-K slices
-//   q, K, V = rotary(sum part)                     qkv_rope_kernel: q -> bf16 rows, K/V -> paged cache
-//   xp_a  = attention(q, cache)                    attn_bf16.hip
+//   xp_a  = attention(rotary(sum part), cache)     attn_bf16.hip; it also writes the new K, V to the paged cache
 //   part  = xp_a W_o^T ; x += sum part ; xp_h = RMSNorm(x) * g2        residual_rmsnorm_kernel
 //   part  = xp_h [W_g; W_u]^T ; xp_f = silu(gate) * up                  swiglu_pack_kernel
 //   part  = xp_f W_d^T ; x += sum part ; xp_h = RMSNorm(x) * g_next     residual_rmsnorm_kernel
@@ -40,7 +39,7 @@ spec_status launch_moe_gather(const bf16_t* xp_src, int mb_pad_src, const int32_
                               int rows_bound, int xf_dst, bf16_t* xp_dst, hipStream_t s);
 spec_status launch_moe_combine_norm(float* x, const float* y, const int32_t* pair_row, const float* wts, int M, int top_k,
                                     const void* gain, int d, float eps, int mb_pad, int xf, bf16_t* xp, hipStream_t s);
-spec_status launch_attention_bf16(const float* q, int B, int T, int G, int Hq, int Hkv, const KvView& kv, int layer_pool, int layer,
+spec_status launch_attention_bf16(const QkvSlices& in, int B, int T, int G, int Hq, int Hkv, const KvView& kv, int layer_pool, int layer,
                                   int pages_bound, const void* items, const void* entry_items, float* part_o, float* part_ml,
                                   int mb_pad, int xf_out, bf16_t* xp_out, hipStream_t s);
 
@@ -188,12 +187,8 @@ __global__ __launch_bounds__(512) void fuse_input_kernel(
     }
 }
 
-// Once per forward pass, per input row: cos/sin of pos * theta^(-2j/dh) in fp64 (the angle reaches thousands of radians),
-// and where the row's key and value go: row_slot[m] = page * SPEC_PAGE_SIZE + position in the page, or -1 (the batch entry
-// was dropped, or its sequence holds no page for that position).  The per-layer kernels then need no walk through the
-// bookkeeping (batch entry -> sequence -> length -> page list), three dependent loads each.
-__device__ inline void rope_table(int idx, int M, int T, const KvView& kv, int half, double theta, float2* __restrict__ table,
-                                  int32_t* __restrict__ row_slot)
+// Once per forward pass, per input row: cos/sin of pos * theta^(-2j/dh) in fp64 (the angle reaches thousands of radians)
+__device__ inline void rope_table(int idx, int M, int T, const KvView& kv, int half, double theta, float2* __restrict__ table)
 {
     if (idx >= M * half) return;
     int m = idx / half, j = idx % half;
@@ -201,109 +196,6 @@ __device__ inline void rope_table(int idx, int M, int T, const KvView& kv, int h
     const int pos = seq >= 0 ? kv.ctx_len[seq] + m % T : 0;
     double ang = (double)pos * pow(theta, -2.0 * (double)j / (double)(2 * half));
     table[idx] = make_float2((float)cos(ang), (float)sin(ang));
-    if (j == 0) {
-        int slot = -1;
-        if (seq >= 0) {
-            const int lp = pos / SPEC_PAGE_SIZE;
-            if (lp < kv.n_held[seq]) slot = kv.page_table[(int64_t)seq * kv.max_pages + lp] * SPEC_PAGE_SIZE + pos % SPEC_PAGE_SIZE;
-        }
-        row_slot[m] = slot;
-    }
-}
-
-// sums the split-K slices of the QKV projection, rotates q and k, writes q as bf16 rows and the
-// new k, v into their cache slots (speculatively: positions ctx .. ctx+k).  One workgroup per row.
-// KV8: the cache holds E4M3 codes of x / scale, one scale per (layer, kv head) for keys and one for values.
-template <bool KV8>
-__global__ __launch_bounds__(256) void qkv_rope_kernel(
-    const float* __restrict__ part, int splits, int64_t split_stride, int T, int Hq, int Hkv,
-    const float2* __restrict__ rope, const int32_t* __restrict__ row_slot, KvView kv, int layer_pool, int layer,
-    float* __restrict__ q_out)
-{
-    constexpr int DHc = 128, HALF = 64;
-    const int m = blockIdx.x;
-    const int slot = row_slot[m];
-    const bool writable = slot >= 0;
-    const int64_t page = writable ? slot / SPEC_PAGE_SIZE : 0;
-    const int t = writable ? slot % SPEC_PAGE_SIZE : 0;
-    const int nqkv = (Hq + 2 * Hkv) * DHc;
-    const float* row = part + (int64_t)m * nqkv;
-    unsigned short* pool = (unsigned short*)kv.pool;
-    const int64_t block = (int64_t)SPEC_PAGE_SIZE * DHc;
-    // sum of the slices of 4 adjacent columns, in slice order; the loads go out eight (four, two) at a time - a plain
-    // loop would wait for each slice before asking for the next
-    auto sum4 = [&](int n) {
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        int s = 0;
-        auto add_group = [&](auto n_c) {
-            constexpr int GN = decltype(n_c)::value;
-            float4 p[GN];
-#pragma unroll
-            for (int u = 0; u < GN; ++u) p[u] = *(const float4*)(row + (s + u) * split_stride + n);
-#pragma unroll
-            for (int u = 0; u < GN; ++u) { v.x += p[u].x; v.y += p[u].y; v.z += p[u].z; v.w += p[u].w; }
-            s += GN;
-        };
-        while (s + 8 <= splits) add_group(std::integral_constant<int, 8>{});
-        if (s + 4 <= splits) add_group(std::integral_constant<int, 4>{});
-        if (s + 2 <= splits) add_group(std::integral_constant<int, 2>{});
-        if (s < splits) add_group(std::integral_constant<int, 1>{});
-        return v;
-    };
-    // rotary part: heads 0 .. Hq+Hkv-1, 16 quads of the lower half each
-    for (int e = threadIdx.x + 256 * blockIdx.y; e < (Hq + Hkv) * (HALF / 4); e += 256 * gridDim.y) {
-        int h = e / (HALF / 4), j = (e % (HALF / 4)) * 4;
-        float4 lo = sum4(h * DHc + j), hi = sum4(h * DHc + j + HALF);
-        const float2* cs = rope + (int64_t)m * HALF + j;
-        float l[4] = {lo.x, lo.y, lo.z, lo.w}, u[4] = {hi.x, hi.y, hi.z, hi.w}, rl[4], ru[4];
-#pragma unroll
-        for (int a = 0; a < 4; ++a) {
-            float2 c = cs[a];
-            rl[a] = l[a] * c.x - u[a] * c.y;
-            ru[a] = u[a] * c.x + l[a] * c.y;
-        }
-        uint2 plo = make_uint2(to_bf16(rl[0]) | (to_bf16(rl[1]) << 16), to_bf16(rl[2]) | (to_bf16(rl[3]) << 16));
-        uint2 phi = make_uint2(to_bf16(ru[0]) | (to_bf16(ru[1]) << 16), to_bf16(ru[2]) | (to_bf16(ru[3]) << 16));
-        if (h < Hq) {
-            float* dst = q_out + ((int64_t)m * Hq + h) * DHc;
-            *(float4*)(dst + j) = make_float4(rl[0], rl[1], rl[2], rl[3]);
-            *(float4*)(dst + j + HALF) = make_float4(ru[0], ru[1], ru[2], ru[3]);
-        } else if (writable) {
-            int kh = h - Hq;
-            if constexpr (KV8) {
-                const float ks = kv.k_scale[layer * Hkv + kh];
-                unsigned char* dst = (unsigned char*)kv.pool + ((((int64_t)layer_pool * kv.n_pages + page) * 2 + 0) * Hkv + kh) * block;
-                *(unsigned int*)(dst + kv_block_offset(SPEC_FP8_E4M3, 0, t, j, DHc)) =
-                    to_e4m3(rl[0] / ks) | (to_e4m3(rl[1] / ks) << 8) | (to_e4m3(rl[2] / ks) << 16) | (to_e4m3(rl[3] / ks) << 24);
-                *(unsigned int*)(dst + kv_block_offset(SPEC_FP8_E4M3, 0, t, j + HALF, DHc)) =
-                    to_e4m3(ru[0] / ks) | (to_e4m3(ru[1] / ks) << 8) | (to_e4m3(ru[2] / ks) << 16) | (to_e4m3(ru[3] / ks) << 24);
-            } else {
-                unsigned short* dst = pool + ((((int64_t)layer_pool * kv.n_pages + page) * 2 + 0) * Hkv + kh) * block;
-                *(uint2*)(dst + kv_block_offset(SPEC_BF16, 0, t, j, DHc)) = plo;
-                *(uint2*)(dst + kv_block_offset(SPEC_BF16, 0, t, j + HALF, DHc)) = phi;
-            }
-        }
-    }
-    // values: no rotation
-    if (writable)
-        for (int e = threadIdx.x + 256 * blockIdx.y; e < Hkv * (DHc / 4); e += 256 * gridDim.y) {
-            int kh = e / (DHc / 4), c = (e % (DHc / 4)) * 4;
-            float4 v = sum4((Hq + Hkv + kh) * DHc + c);
-            if constexpr (KV8) {
-                const float vs = kv.v_scale[layer * Hkv + kh];
-                unsigned char* dst8 = (unsigned char*)kv.pool + ((((int64_t)layer_pool * kv.n_pages + page) * 2 + 1) * Hkv + kh) * block;
-                dst8[kv_block_offset(SPEC_FP8_E4M3, 1, t, c + 0, DHc)] = (unsigned char)to_e4m3(v.x / vs);
-                dst8[kv_block_offset(SPEC_FP8_E4M3, 1, t, c + 1, DHc)] = (unsigned char)to_e4m3(v.y / vs);
-                dst8[kv_block_offset(SPEC_FP8_E4M3, 1, t, c + 2, DHc)] = (unsigned char)to_e4m3(v.z / vs);
-                dst8[kv_block_offset(SPEC_FP8_E4M3, 1, t, c + 3, DHc)] = (unsigned char)to_e4m3(v.w / vs);
-                continue;
-            }
-            unsigned short* dst = pool + ((((int64_t)layer_pool * kv.n_pages + page) * 2 + 1) * Hkv + kh) * block;
-            dst[kv_block_offset(SPEC_BF16, 1, t, c + 0, DHc)] = to_bf16(v.x);
-            dst[kv_block_offset(SPEC_BF16, 1, t, c + 1, DHc)] = to_bf16(v.y);
-            dst[kv_block_offset(SPEC_BF16, 1, t, c + 2, DHc)] = to_bf16(v.z);
-            dst[kv_block_offset(SPEC_BF16, 1, t, c + 3, DHc)] = to_bf16(v.w);
-        }
 }
 
 // act = silu(sum gate) * (sum up) from the gate/up projection [M][2F] -> bf16 operand order (K = F)
@@ -347,7 +239,7 @@ __device__ inline void pack_rows(int64_t i, const float* __restrict__ src, int M
 }
 
 // What a forward pass starts with, all of it ready once the pages are reserved, in one launch (three of 3-23 us each, one after the other, before):
-// workgroup 0 the attention's work list, the next `rope_groups` the rotary table and the rows' cache slots, the others the first operand: FIRST_EMBED
+// workgroup 0 the attention's work list, the next `rope_groups` the rotary table, the others the first operand: FIRST_EMBED
 // a row of the embedding and its norm each, FIRST_FEATURES a piece of the multi-layer features before w_fc, FIRST_NONE nothing.
 constexpr int FIRST_NONE = 0, FIRST_EMBED = 1, FIRST_FEATURES = 2;
 struct BeginArgs {
@@ -357,7 +249,6 @@ struct BeginArgs {
     int half;
     double theta;
     float2* rope;
-    int32_t* row_slot;
     // FIRST_EMBED
     float* x;
     const int32_t* tokens;
@@ -375,7 +266,7 @@ __global__ __launch_bounds__(512) void begin_kernel(BeginArgs a)
 {
     const int g = blockIdx.x;
     if (g == 0) attn_plan(a.B, a.T, a.kv, a.plan);
-    else if (g <= a.rope_groups) rope_table((g - 1) * blockDim.x + threadIdx.x, a.M, a.T, a.kv, a.half, a.theta, a.rope, a.row_slot);
+    else if (g <= a.rope_groups) rope_table((g - 1) * blockDim.x + threadIdx.x, a.M, a.T, a.kv, a.half, a.theta, a.rope);
     else if (FIRST == FIRST_EMBED) residual_rmsnorm<RES_EMBED>(g - 1 - a.rope_groups, a.x, nullptr, 0, 0, a.tokens, a.embed, a.vocab, a.gain, a.d, a.eps, a.mb_pad, a.xf, a.xp);
     else if (FIRST == FIRST_FEATURES) pack_rows((int64_t)(g - 1 - a.rope_groups) * blockDim.x + threadIdx.x, a.features, a.M, a.K, a.mb_pad, a.xp);
 }
@@ -395,9 +286,9 @@ struct Bf16Plan {
     int M, mb_pad, max_chunks, RBrows;
     bool fuse_swiglu;
     int s_qkv, s_o, s_gu, s_down, s_head, s_fuse, s_fc;
-    size_t off_x, off_xp_h, off_xp_a, off_xp_f, off_part, off_q, off_rope, off_att_o, off_att_ml, total;
+    size_t off_x, off_xp_h, off_xp_a, off_xp_f, off_part, off_rope, off_att_o, off_att_ml, total;
     int max_items;                          // attention work items the buffers hold
-    size_t off_row_slot, off_items, off_entry_items;
+    size_t off_items, off_entry_items;
     // mixture of experts: padded-row bound, router splits, routing tables, permuted activations, expert outputs
     int moe_rows, s_router;
     size_t off_ids, off_wts, off_row0, off_tiles, off_src_row, off_pair_row, off_xp_e, off_y_e;
@@ -449,9 +340,7 @@ static Bf16Plan make_plan(const spec_model* m, int B, int k, int64_t max_ctx_plu
         p.off_xp_e = take((size_t)p.moe_rows * D * 4);
         p.off_y_e = take((size_t)p.moe_rows * D * 4);
     }
-    p.off_q = take((size_t)p.M * nq * 4);
     p.off_rope = take((size_t)p.M * (d.head_dim / 2) * 8);
-    p.off_row_slot = take((size_t)p.M * 4);
     p.off_items = take((size_t)p.max_items * attn_item_bytes());
     p.off_entry_items = take((size_t)B * 8);
     size_t items = (size_t)p.max_items * d.n_kv_heads;
@@ -488,11 +377,9 @@ spec_status bf16_forward(spec_model* mdl, spec_kv* kv, int B, int k, const int32
     bf16_t* xp_a = (bf16_t*)(base + p.off_xp_a);
     bf16_t* xp_f = (bf16_t*)(base + p.off_xp_f);
     float* part = (float*)(base + p.off_part);
-    float* qbuf = (float*)(base + p.off_q);
     float2* rope = (float2*)(base + p.off_rope);
     float* att_o = (float*)(base + p.off_att_o);
     float* att_ml = (float*)(base + p.off_att_ml);
-    int32_t* row_slot = (int32_t*)(base + p.off_row_slot);
     void* att_items = base + p.off_items;
     void* att_entry_items = base + p.off_entry_items;
 
@@ -510,7 +397,7 @@ spec_status bf16_forward(spec_model* mdl, spec_kv* kv, int B, int k, const int32
     begin.rope_groups = (int)cdiv((int64_t)M * 64, norm_threads);
     begin.kv = view;
     begin.plan = attention_plan_args(B, T, G, Hkv, live_pages, att_items, att_entry_items);
-    begin.half = 64; begin.theta = (double)d.rope_theta; begin.rope = rope; begin.row_slot = row_slot;
+    begin.half = 64; begin.theta = (double)d.rope_theta; begin.rope = rope;
     begin.x = x; begin.tokens = dev_tokens; begin.embed = (const unsigned short*)mdl->embed(); begin.gain = (const unsigned short*)mdl->layer_w(0, 0);
     begin.vocab = d.vocab; begin.d = D; begin.eps = d.rms_eps; begin.mb_pad = p.mb_pad;
     if (d.fuse_hidden) {
@@ -549,12 +436,8 @@ spec_status bf16_forward(spec_model* mdl, spec_kv* kv, int B, int k, const int32
         int lp = kv->alias_mod > 0 ? l % kv->alias_mod : l;
         if ((st = launch_gemm_bf16(mdl->wqkv[l], xp_h, M, part, nqkv, p.s_qkv, false, s)) != SPEC_OK) return st;
         prof_mark(PC_GEMM_QKV, s);
-        if (view.fp8)
-            qkv_rope_kernel<true><<<dim3(M, 4), 256, 0, s>>>(part, p.s_qkv, (int64_t)M * nqkv, T, Hq, Hkv, rope, row_slot, view, lp, l, qbuf);
-        else
-            qkv_rope_kernel<false><<<dim3(M, 4), 256, 0, s>>>(part, p.s_qkv, (int64_t)M * nqkv, T, Hq, Hkv, rope, row_slot, view, lp, l, qbuf);
-        prof_mark(PC_QKV_ROPE, s);
-        if ((st = launch_attention_bf16(qbuf, B, T, G, Hq, Hkv, view, lp, l, live_pages, att_items, att_entry_items, att_o, att_ml, p.mb_pad, xf_of(mdl->wo[l]), xp_a, s)) != SPEC_OK) return st;
+        const QkvSlices qkv{part, p.s_qkv, (int64_t)M * nqkv, nqkv, rope};
+        if ((st = launch_attention_bf16(qkv, B, T, G, Hq, Hkv, view, lp, l, live_pages, att_items, att_entry_items, att_o, att_ml, p.mb_pad, xf_of(mdl->wo[l]), xp_a, s)) != SPEC_OK) return st;
         if ((st = launch_gemm_bf16(mdl->wo[l], xp_a, M, part, D, p.s_o, false, s)) != SPEC_OK) return st;
         prof_mark(PC_GEMM_O, s);
         // (mixture of experts: the router reads this buffer and stays hi + lo; the gather below converts for the experts)
