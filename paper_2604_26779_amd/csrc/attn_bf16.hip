@@ -500,18 +500,42 @@ __global__ void attn_reduce_kernel(const float* __restrict__ part_o, const float
     const int2 mine = entry_items[b];                        // (first item, number of items) of this batch entry
     const int n_chunks = mine.y;
     auto slot = [&](int c) { return ((int64_t)(mine.x + c) * Hkv + kvh) * RBrows + r; };
-    float M = -INFINITY;
-    for (int c = 0; c < n_chunks; ++c) M = fmaxf(M, part_ml[slot(c) * 2]);
-    float L = 0.f, o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int c = 0; c < n_chunks; ++c) {
-        float mc = part_ml[slot(c) * 2];
-        float f = mc > -INFINITY ? exp2f(mc - M) : 0.f;      // branch-free: the loads of all chunks overlap
-        L += f * part_ml[slot(c) * 2 + 1];
-        const float4* src = (const float4*)(part_o + slot(c) * DH + c8 * 8);
-        float4 a = src[0], d = src[1];
-        o[0] += f * a.x; o[1] += f * a.y; o[2] += f * a.z; o[3] += f * a.w;
-        o[4] += f * d.x; o[5] += f * d.y; o[6] += f * d.z; o[7] += f * d.w;
-    }
+    // up to RED chunks at a time, everything they need asked for together (past the last chunk it is read again and weighs nothing); the running
+    // maximum moves between groups.  A trip for the list and one per group: 8.2 -> 5.5 us at 9 chunks a sequence (7 sequences), where a loop took a trip
+    // per chunk and went over the maxima first; 5.1 -> 5.0 at two.
+    constexpr int RED = 8;
+    float M = -INFINITY, L = 0.f, o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    auto merge = [&](int c0, auto n_c) {
+        constexpr int GN = decltype(n_c)::value;
+        float2 ml[GN];
+        float4 a[GN], d[GN];
+#pragma unroll
+        for (int u = 0; u < GN; ++u) {
+            const int64_t at = slot(c0 + u < n_chunks ? c0 + u : n_chunks - 1);
+            ml[u] = *(const float2*)(part_ml + at * 2);
+            const float4* src = (const float4*)(part_o + at * DH + c8 * 8);
+            a[u] = src[0];
+            d[u] = src[1];
+        }
+        float mx = M;
+#pragma unroll
+        for (int u = 0; u < GN; ++u) mx = fmaxf(mx, ml[u].x);
+        const float move = M > -INFINITY ? exp2f(M - mx) : 0.f;
+        M = mx;
+        L *= move;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) o[j] *= move;
+#pragma unroll
+        for (int u = 0; u < GN; ++u) {
+            const float f = c0 + u < n_chunks && ml[u].x > -INFINITY ? exp2f(ml[u].x - M) : 0.f;
+            if (f == 0.f) continue;                        // (whatever an empty chunk's place holds)
+            L += f * ml[u].y;
+            o[0] += f * a[u].x; o[1] += f * a[u].y; o[2] += f * a[u].z; o[3] += f * a[u].w;
+            o[4] += f * d[u].x; o[5] += f * d[u].y; o[6] += f * d[u].z; o[7] += f * d[u].w;
+        }
+    };
+    if (n_chunks > 0 && n_chunks <= 2) merge(0, std::integral_constant<int, 2>{});
+    else for (int c0 = 0; c0 < n_chunks; c0 += RED) merge(c0, std::integral_constant<int, RED>{});
     float inv = L > 0.f ? 1.0f / L : 0.f;
     if (kv.fp8) inv *= kv.v_scale[layer * Hkv + kvh];     // 8-bit cache: the values were accumulated as codes
     float res[8];

@@ -43,11 +43,12 @@ spec_status launch_attention_bf16(const QkvSlices& in, int B, int T, int G, int 
                                   int pages_bound, const void* items, const void* entry_items, float* part_o, float* part_ml,
                                   int mb_pad, int xf_out, bf16_t* xp_out, hipStream_t s);
 
-// sum over the workgroup (blockDim.x a multiple of 64, at most 1024)
+// sum over the workgroup (blockDim.x a multiple of 64, at most 1024); FIRST: lds16 has not been used yet
+template <bool FIRST = false>
 __device__ inline float block_sum(float v, float* lds16)
 {
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    __syncthreads();
+    if (!FIRST) __syncthreads();
     if ((threadIdx.x & 63) == 0) lds16[threadIdx.x >> 6] = v;
     __syncthreads();
     float t = 0.f;
@@ -56,7 +57,9 @@ __device__ inline float block_sum(float v, float* lds16)
 }
 
 // x[m] = embed[token] (RES_EMBED), x[m] + sum_s part[s][m] (RES_ADD) or sum_s part[s][m] (RES_SET);  xp = RMSNorm(x[m]) * gain
-// one workgroup per row (256 or 512 threads, 8 elements per thread and pass); d % 8 == 0
+// one workgroup per row, 8 elements per thread and pass; d % 8 == 0.  A chain of trips: the row is kept in registers between the sum of squares and
+// the scaling where one pass covers it (d <= 8 * threads), and the gain is asked for together with the slices (8B shape, 8 slices, at 4, 28 and
+// 384 rows: 4.5, 5.1, 15.4 us storing the row and reading it back, 4.3, 5.0 and 14.9 now; the last is 4.6 TB/s).
 constexpr int RES_ADD = 0, RES_EMBED = 1, RES_SET = 2;
 template <int MODE>
 __device__ inline void residual_rmsnorm(
@@ -67,12 +70,10 @@ __device__ inline void residual_rmsnorm(
     __shared__ float lds16[16];
     const int stride = blockDim.x * 8;
     float* xr = x + (int64_t)m * d;
-    float ss = 0.f;
     int tok = 0;
     constexpr bool FIRST = MODE == RES_EMBED;
     if (FIRST) { tok = tokens[m]; tok = tok < 0 ? 0 : (tok >= vocab ? vocab - 1 : tok); }
-    for (int c = threadIdx.x * 8; c < d; c += stride) {
-        float v[8];
+    auto row_values = [&](int c, float (&v)[8]) {
         if (FIRST) {
             uint4 e = *(const uint4*)(embed + (int64_t)tok * d + c);
             unsigned int w[4] = {e.x, e.y, e.z, e.w};
@@ -107,25 +108,51 @@ __device__ inline void residual_rmsnorm(
             if (s < splits) add_group(std::integral_constant<int, 1>{});
             v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
         }
+    };
+    auto scaled = [&](int c, const float (&v)[8], float r, const uint4& g) {
+        const float o[8] = {v[0] * r * from_bf16(g.x & 0xffff), v[1] * r * from_bf16(g.x >> 16), v[2] * r * from_bf16(g.y & 0xffff), v[3] * r * from_bf16(g.y >> 16),
+                            v[4] * r * from_bf16(g.z & 0xffff), v[5] * r * from_bf16(g.z >> 16), v[6] * r * from_bf16(g.w & 0xffff), v[7] * r * from_bf16(g.w >> 16)};
+        xp_store8_rt(xp, xf, m, c, mb_pad, o);
+    };
+    auto keep = [&](int c, const float (&v)[8]) {
         *(float4*)(xr + c) = make_float4(v[0], v[1], v[2], v[3]);
         *(float4*)(xr + c + 4) = make_float4(v[4], v[5], v[6], v[7]);
+    };
+    float ss = 0.f;
+    if (d <= stride) {
+        const int c = threadIdx.x * 8;
+        float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        uint4 g = make_uint4(0, 0, 0, 0);
+        if (c < d) {
+            g = *(const uint4*)(gain + c);
+            row_values(c, v);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) ss += v[j] * v[j];
+        }
+        const float r = 1.0f / sqrtf(block_sum<true>(ss, lds16) / (float)d + eps);
+        if (c < d) {
+            keep(c, v);
+            scaled(c, v, r, g);
+        }
+        return;
+    }
+    for (int c = threadIdx.x * 8; c < d; c += stride) {
+        float v[8];
+        row_values(c, v);
+        keep(c, v);
 #pragma unroll
         for (int j = 0; j < 8; ++j) ss += v[j] * v[j];
     }
-    float tot = block_sum(ss, lds16);
-    float r = 1.0f / sqrtf(tot / (float)d + eps);
+    const float r = 1.0f / sqrtf(block_sum<true>(ss, lds16) / (float)d + eps);
     for (int c = threadIdx.x * 8; c < d; c += stride) {
-        float4 a = *(const float4*)(xr + c), b = *(const float4*)(xr + c + 4);      // this thread's own writes
-        uint4 g = *(const uint4*)(gain + c);
-        float v[8] = {a.x * r * from_bf16(g.x & 0xffff), a.y * r * from_bf16(g.x >> 16), a.z * r * from_bf16(g.y & 0xffff),
-                      a.w * r * from_bf16(g.y >> 16),    b.x * r * from_bf16(g.z & 0xffff), b.y * r * from_bf16(g.z >> 16),
-                      b.z * r * from_bf16(g.w & 0xffff), b.w * r * from_bf16(g.w >> 16)};
-        xp_store8_rt(xp, xf, m, c, mb_pad, v);
+        const float4 a = *(const float4*)(xr + c), b = *(const float4*)(xr + c + 4);      // this thread's own writes
+        const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+        scaled(c, v, r, *(const uint4*)(gain + c));
     }
 }
 
 template <int MODE>
-__global__ __launch_bounds__(512) void residual_rmsnorm_kernel(
+__global__ __launch_bounds__(1024) void residual_rmsnorm_kernel(
     float* __restrict__ x, const float* __restrict__ part, int splits, int64_t split_stride, const unsigned short* __restrict__ gain, int d,
     float eps, int mb_pad, int xf, uint4* __restrict__ xp)
 {
@@ -388,6 +415,7 @@ spec_status bf16_forward(spec_model* mdl, spec_kv* kv, int B, int k, const int32
     KvView view = kv->view();
     spec_status st;
     const int norm_threads = D >= 4096 ? 512 : 256;
+    const int row_threads = (int)std::min<int64_t>(1024, cdiv(D, 512) * 64);      // one pass over rows of up to 8192 channels
     // operand format each projection's input is written in: the one its matrix was tiled for at model creation
     auto xf_of = [](const PackedW& W) { return W.f16 ? XF_F16 : XF_HILO; };
     if (!mdl->moe() && mdl->wgu[0].f16 != mdl->wd[0].f16) { set_error("bf16 forward: gate/up and down projection must take the same activation format"); return SPEC_ESTATE; }
@@ -419,7 +447,7 @@ spec_status bf16_forward(spec_model* mdl, spec_kv* kv, int B, int k, const int32
                                                      (const unsigned short*)mdl->fuse_w(1), (const unsigned short*)mdl->fuse_w(2), D, d.rms_eps,
                                                      p.mb_pad, (uint4*)xp_f);
         if ((st = launch_gemm_bf16(mdl->wfuse, xp_f, M, part, D, p.s_fuse, false, s)) != SPEC_OK) return st;
-        residual_rmsnorm_kernel<RES_SET><<<M, norm_threads, 0, s>>>(x, part, p.s_fuse, (int64_t)M * D, (const unsigned short*)mdl->layer_w(0, 0), D, d.rms_eps,
+        residual_rmsnorm_kernel<RES_SET><<<M, row_threads, 0, s>>>(x, part, p.s_fuse, (int64_t)M * D, (const unsigned short*)mdl->layer_w(0, 0), D, d.rms_eps,
                                                                    p.mb_pad, xf_of(mdl->wqkv[0]), (uint4*)xp_h);
     } else {
         begin.xf = xf_of(mdl->wqkv[0]); begin.xp = (uint4*)xp_h;
@@ -441,7 +469,7 @@ spec_status bf16_forward(spec_model* mdl, spec_kv* kv, int B, int k, const int32
         if ((st = launch_gemm_bf16(mdl->wo[l], xp_a, M, part, D, p.s_o, false, s)) != SPEC_OK) return st;
         prof_mark(PC_GEMM_O, s);
         // (mixture of experts: the router reads this buffer and stays hi + lo; the gather below converts for the experts)
-        residual_rmsnorm_kernel<RES_ADD><<<M, norm_threads, 0, s>>>(x, part, p.s_o, (int64_t)M * D,
+        residual_rmsnorm_kernel<RES_ADD><<<M, row_threads, 0, s>>>(x, part, p.s_o, (int64_t)M * D,
                                                          (const unsigned short*)mdl->layer_w(l, 5), D, d.rms_eps, p.mb_pad,
                                                          mdl->moe() ? xf_of(mdl->router[l]) : xf_of(mdl->wgu[l]), (uint4*)xp_h);
         prof_mark(PC_RESID_NORM, s);
@@ -485,7 +513,7 @@ spec_status bf16_forward(spec_model* mdl, spec_kv* kv, int B, int k, const int32
         }
         if ((st = launch_gemm_bf16(mdl->wd[l], xp_f, M, part, D, p.s_down, false, s)) != SPEC_OK) return st;
         prof_mark(PC_GEMM_DOWN, s);
-        residual_rmsnorm_kernel<RES_ADD><<<M, norm_threads, 0, s>>>(x, part, p.s_down, (int64_t)M * D,
+        residual_rmsnorm_kernel<RES_ADD><<<M, row_threads, 0, s>>>(x, part, p.s_down, (int64_t)M * D,
                                                          (const unsigned short*)next_gain, D, d.rms_eps, p.mb_pad, next_xf, (uint4*)xp_h);
         prof_mark(PC_RESID_NORM, s);
         write_taps(l + 1);

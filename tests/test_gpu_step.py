@@ -790,3 +790,21 @@ def test_bf16_work_list_of_many_entries(B, k):
     ok, max_err, worst = _run_custom_bf16(ctx, k=k, seed=B + k, vocab=500, n_layers=1)
     print("B=%d k=%d: logits max abs err %.3e" % (B, k, max_err))
     assert ok, (max_err, worst)
+
+
+@pytest.mark.parametrize("heads", [(8, 2), (4, 4)])
+def test_bf16_attention_merge_of_many_chunks(heads):
+    """One, two, three, eight, nine and eighteen chunks a sequence (the merge takes them two or eight at a time), one of them huge in its keys."""
+    ctx = [0, 60, 120, 180, 505, 570, 1085, 1088]
+    ok, max_err, worst = _with_tune({"attn_chunk_pages": 4}, lambda: _run_custom_bf16(ctx, k=3, seed=5, vocab=700, n_q_heads=heads[0], n_kv_heads=heads[1],
+                                                                                     key_scale=6.0))
+    print("heads %s: logits max abs err %.3e" % (heads, max_err))
+    assert ok, (max_err, worst)
+
+
+@pytest.mark.parametrize("d_model", [256, 1536, 8192, 8448])
+def test_bf16_norm_of_narrow_and_wide_rows(d_model):
+    """Rows of less than one wavefront's channels, of three, of all the workgroup's, and of more than it covers in one pass."""
+    ok, max_err, worst = _run_custom_bf16([5, 40], k=1, seed=3, vocab=300, d_model=d_model, n_layers=1, n_q_heads=2, n_kv_heads=1, ffn_dim=256)
+    print("d=%d: logits max abs err %.3e" % (d_model, max_err))
+    assert ok, (max_err, worst)
