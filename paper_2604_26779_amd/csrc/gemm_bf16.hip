@@ -598,7 +598,14 @@ static GemmShape gemm_shape(const PackedW& W, int M, bool fused_swiglu)
     }
     if (g.mb == 4 && g.m_tiles <= tune("gemm_split_rows") && W.n_blocks % 8 == 0) {
         const int nb = (int)cdiv(M, 32);
-        if (fused_swiglu && nb >= 5 && tune("gemm_tiles_96") != 0) g.mb = nb <= 6 ? 3 : 4;
+        // 129..256 rows, plain epilogue: the tall tiles too, where K stays unsplit and they fill the chip (a reduced head: 32000 rows at 160 and 256
+        // rows 93 -> 65, 94 -> 71 us), where the 64-row ones leave half of it idle (9216 x 4096 at 256 rows, 144 workgroups: 52.8 -> 41.4), and with fp16
+        // inputs against 16-bit weights (down projection at 160 and 256 rows 38.6 -> 32.1, 45.5 -> 35.7, more than the three or four slices
+        // more cost the norm).  Elsewhere those slices make them the slower ones (hi + lo projections of the 8B shape 20.3 -> 23.0; 8-bit down
+        // projection equal).
+        const int n_tall = (int)cdiv(nb, nb <= 6 ? 3 : 4) * (W.n_blocks / 8), n_64 = (int)cdiv(nb, 2) * (W.n_blocks / 8), target = tune("gemm_wg_target");
+        const bool tall = fused_swiglu || (n_tall * 4 >= target * 3 && n_tall <= target) || (n_64 * 2 > target && n_64 * 8 < target * 5) || (W.f16 && !W.w8 && n_64 <= target);
+        if (nb >= 5 && tall && tune("gemm_tiles_96") != 0) g.mb = nb <= 6 ? 3 : 4;
         else g.mb = 2;
         g.m_tiles = (int)cdiv(nb, g.mb); g.wide = true; g.tile_nb = 8; g.n_tiles = W.n_blocks / 8; g.kunit = GEMM_KS * 2;
         return g;

@@ -808,3 +808,17 @@ def test_bf16_norm_of_narrow_and_wide_rows(d_model):
     ok, max_err, worst = _run_custom_bf16([5, 40], k=1, seed=3, vocab=300, d_model=d_model, n_layers=1, n_q_heads=2, n_kv_heads=1, ffn_dim=256)
     print("d=%d: logits max abs err %.3e" % (d_model, max_err))
     assert ok, (max_err, worst)
+
+
+@pytest.mark.parametrize("w8", [False, True])
+@pytest.mark.parametrize("target", [14, 18, 256])
+@pytest.mark.parametrize("B,k", [(33, 3), (40, 3), (43, 4), (64, 3)])
+def test_bf16_tall_tiles_for_plain_projections(B, k, target, w8):
+    """129..256 rows: 96- and 128-row x 256-column tiles for plain outputs too, unsplit (QKV projection at a workgroup target of 14 or 18) and split
+    (down projection), 132, 160, 215 and 256 rows in either operand format and weight type."""
+    rng = np.random.default_rng(B * 10 + k)
+    ctx = [int(c) for c in rng.integers(3, 120, size=B)]
+    ok, max_err, worst = _with_tune({"gemm_wg_target": target, "gemm_min_ksteps": 16, "gemm_big_min_blocks": 0 if target == 18 else 5},
+                                    lambda: _run_custom_bf16(ctx, k=k, seed=B + k, vocab=1000, **(dict(w_dtype="fp8_e4m3") if w8 else {})))
+    print("M=%d, target %d, 8-bit matrices %s: logits max abs err %.3e" % (B * (k + 1), target, w8, max_err))
+    assert ok, (max_err, worst)
