@@ -22,7 +22,7 @@
 //                         the wavefronts' results are merged through LDS and written as an
 //                         un-normalised partial (O, reference point, sum).  What it needs of the QKV projection it sums from
 //                         the K-split slices and rotates itself, its rows' queries and the new keys and values of its pages, which
-//                         it writes to the cache.  A kernel of its own for that took 4.5-12.5 us per layer where the attention now takes 2.5-11
+//                         it writes to the cache.  A kernel of its own for that took 4.5-12.5 us per layer where the attention now takes 2-9
 //                         more (8B shape, step at batch 1, 7 and 32: 3 324 -> 3 269, 4 427 -> 4 352, 7 813 -> 7 774 us; equal at 384 rows and more).
 //   attn_reduce_kernel  : merges the chunks of a (batch entry, kv head) and writes the bf16 result
 //                         in the operand order the O-projection GEMM reads.
@@ -121,60 +121,66 @@ __global__ __launch_bounds__(256, NRB <= 2 ? 2 : 1) void attn_partial_kernel(
         int pg = page0 + wave + ATT_WAVES * lane;
         my_pid = pt[pg < page_end ? pg : page_end - 1];
     }
-    // sum of the slices of N adjacent floats, in slice order, the loads four slices at a time
-    auto sum_slices = [&](const float* p, auto n_c, float* v) {
-        constexpr int N = decltype(n_c)::value;
-        typedef float vec_t __attribute__((ext_vector_type(4)));
+    // sums of the slices of four adjacent floats in one or two places, in slice order: the loads of up to eight slices go out together
+    auto sum_slices = [&](auto two_c, const float* p, const float* p2, f32x4_t& v, f32x4_t& v2) {
+        constexpr bool TWO = decltype(two_c)::value;
+        v = v2 = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        f32x4_t x[8], y[8];
+        auto load = [&](auto at_c, auto n_c, int s0) {
 #pragma unroll
-        for (int j = 0; j < N; ++j) v[j] = 0.f;
-        auto add = [&](int s0, auto g_c) {
-            constexpr int GN = decltype(g_c)::value;
-            vec_t x[GN][N / 4];
-#pragma unroll
-            for (int u = 0; u < GN; ++u)
-#pragma unroll
-                for (int h = 0; h < N / 4; ++h) x[u][h] = *(const vec_t*)(p + (s0 + u) * in.split_stride + 4 * h);
-#pragma unroll
-            for (int u = 0; u < GN; ++u)
-#pragma unroll
-                for (int j = 0; j < N; ++j) v[j] += x[u][j >> 2][j & 3];
+            for (int u = 0; u < decltype(n_c)::value; ++u) {
+                x[decltype(at_c)::value + u] = *(const f32x4_t*)(p + (s0 + u) * in.split_stride);
+                if (TWO) y[decltype(at_c)::value + u] = *(const f32x4_t*)(p2 + (s0 + u) * in.split_stride);
+            }
         };
-        int s0 = 0;
-        for (; s0 + 4 <= in.splits; s0 += 4) add(s0, std::integral_constant<int, 4>{});
-        if (s0 + 2 <= in.splits) { add(s0, std::integral_constant<int, 2>{}); s0 += 2; }
-        if (s0 < in.splits) add(s0, std::integral_constant<int, 1>{});
+        auto add = [&](auto at_c, auto n_c) {
+#pragma unroll
+            for (int u = 0; u < decltype(n_c)::value; ++u) {
+                v += x[decltype(at_c)::value + u];
+                if (TWO) v2 += y[decltype(at_c)::value + u];
+            }
+        };
+        using i0 = std::integral_constant<int, 0>; using i1 = std::integral_constant<int, 1>; using i2 = std::integral_constant<int, 2>;
+        using i4 = std::integral_constant<int, 4>; using i6 = std::integral_constant<int, 6>; using i8 = std::integral_constant<int, 8>;
+        const int whole = in.splits & ~7, four = in.splits & 4, two = in.splits & 2;
+        for (int s0 = 0; s0 < whole; s0 += 8) { load(i0{}, i8{}, s0); add(i0{}, i8{}); }
+        if (four) load(i0{}, i4{}, whole);
+        if (two) load(i4{}, i2{}, whole + four);
+        if (in.splits & 1) load(i6{}, i1{}, whole + four + two);
+        if (four) add(i0{}, i4{});
+        if (two) add(i4{}, i2{});
+        if (in.splits & 1) add(i6{}, i1{});
     };
-    using n4_t = std::integral_constant<int, 4>;
-    using n8_t = std::integral_constant<int, 8>;
-    // the queries: channels c .. c+7 and c+64 .. c+71 of a row are rotated together
-    for (int f = wave; f < NRB * 2; f += ATT_WAVES) {
-        const int rb = f >> 1, sgm = f & 1;
+    // the queries: channels c .. c+3 and c+64 .. c+67 of a row are rotated together
+    for (int f = wave; f < NRB * 4; f += ATT_WAVES) {
+        const int rb = f >> 2, c = (f & 3) * 16 + lg * 4;
         const int r = (rb0 + rb) * 16 + lq;
-        float lo[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, hi[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        f32x4_t lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
         if (r < R) {
             const int64_t m = b * T + r / G;
-            const int c0 = lg * 8 + sgm * 32;
-            const float* src = in.part + m * in.ld + (kvh * G + r % G) * DH + c0;
-            const float4* cs = (const float4*)(in.rope + m * (DH / 2) + c0);
-            float l[8], h[8];
-            sum_slices(src, n8_t{}, l);
-            sum_slices(src + DH / 2, n8_t{}, h);
+            const float* src = in.part + m * in.ld + (kvh * G + r % G) * DH + c;
+            const f32x4_t* cs = (const f32x4_t*)(in.rope + m * (DH / 2) + c);
+            const f32x4_t cs01 = cs[0], cs23 = cs[1];                        // cos, sin of two angles each
+            f32x4_t l, h;
+            sum_slices(std::true_type{}, src, src + DH / 2, l, h);
+            const f32x4_t co = {cs01[0], cs01[2], cs23[0], cs23[2]}, si = {cs01[1], cs01[3], cs23[1], cs23[3]};
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const float4 a = cs[j];                                      // cos, sin of two angles
-                lo[2 * j] = l[2 * j] * a.x - h[2 * j] * a.y;
-                hi[2 * j] = h[2 * j] * a.x + l[2 * j] * a.y;
-                lo[2 * j + 1] = l[2 * j + 1] * a.z - h[2 * j + 1] * a.w;
-                hi[2 * j + 1] = h[2 * j + 1] * a.z + l[2 * j + 1] * a.w;
+                lo[j] = l[j] * co[j] - h[j] * si[j];
+                hi[j] = h[j] * co[j] + l[j] * si[j];
             }
         }
-        uint4 h4, l4;
-        split8(lo, h4, l4);
-        s_q[rb][sgm][0][lane] = u32x4_t{h4.x, h4.y, h4.z, h4.w};
-        s_q[rb][sgm][1][lane] = u32x4_t{l4.x, l4.y, l4.z, l4.w};
-        split8(hi, h4, l4);
-        s_q[rb][sgm + 2][0][lane] = u32x4_t{h4.x, h4.y, h4.z, h4.w};
-        s_q[rb][sgm + 2][1][lane] = u32x4_t{l4.x, l4.y, l4.z, l4.w};
+        const int at = lq + 16 * ((c & 31) >> 3), half = (c >> 2) & 1;       // operand lane, and which half of its eight channels
+        u32x2_t w, wl;
+        unsigned int x, y;
+        split2(lo[0], lo[1], x, y); w.x = x; wl.x = y;
+        split2(lo[2], lo[3], x, y); w.y = x; wl.y = y;
+        ((u32x2_t*)&s_q[rb][c >> 5][0][at])[half] = w;
+        ((u32x2_t*)&s_q[rb][c >> 5][1][at])[half] = wl;
+        split2(hi[0], hi[1], x, y); w.x = x; wl.x = y;
+        split2(hi[2], hi[3], x, y); w.y = x; wl.y = y;
+        ((u32x2_t*)&s_q[rb][(c >> 5) + 2][0][at])[half] = w;
+        ((u32x2_t*)&s_q[rb][(c >> 5) + 2][1][at])[half] = wl;
     }
     // The new positions that lie in this item's pages go to the cache (speculatively: ctx .. ctx+k): 16 pieces of four rotated key channels and
     // their partners, 32 of four value channels each.  They are read back from there below, by this workgroup only; row groups of the same item
@@ -188,9 +194,9 @@ __global__ __launch_bounds__(256, NRB <= 2 ? 2 : 1) void attn_partial_kernel(
             const float* row = in.part + m * in.ld;
             if (piece < 16) {
                 const int j = piece * 4;
-                float l[4], h[4], rl[4], ru[4];
-                sum_slices(row + (Hq + kvh) * DH + j, n4_t{}, l);
-                sum_slices(row + (Hq + kvh) * DH + j + DH / 2, n4_t{}, h);
+                f32x4_t l, h;
+                float rl[4], ru[4];
+                sum_slices(std::true_type{}, row + (Hq + kvh) * DH + j, row + (Hq + kvh) * DH + j + DH / 2, l, h);
                 const float2* cs = in.rope + m * (DH / 2) + j;
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
@@ -212,8 +218,8 @@ __global__ __launch_bounds__(256, NRB <= 2 ? 2 : 1) void attn_partial_kernel(
                 }
             } else {
                 const int c = (piece - 16) * 4;
-                float v[4];
-                sum_slices(row + (Hq + Hkv + kvh) * DH + c, n4_t{}, v);
+                f32x4_t v, none;
+                sum_slices(std::false_type{}, row + (Hq + Hkv + kvh) * DH + c, nullptr, v, none);
                 if constexpr (KV8) {
                     const float vs = kv.v_scale[layer * Hkv + kvh];
                     unsigned char* dst = (unsigned char*)kv.pool + ((at + 1) * Hkv + kvh) * (SPEC_PAGE_SIZE * DH);
@@ -272,6 +278,16 @@ __global__ __launch_bounds__(256, NRB <= 2 ? 2 : 1) void attn_partial_kernel(
             return f[i];
         }
     };
+    const int n_plain = plain_end > page0 + wave ? (plain_end - page0 - wave + ATT_WAVES - 1) / ATT_WAVES : 0;
+    // The first pages are asked for before the wait for the other wavefronts' queries (batch 7 and 32 of the 8B shape 4 180 -> 4 137, 7 763 -> 7 723 us a step;
+    // with 8-bit entries, half the bytes, 5 616 -> 5 670: there behind it).
+    auto load_first = [&]() {
+        if (n_plain <= 0) return;
+        load_page(0, pid_at(0));
+        load_page(1, pid_at(1));
+        load_page(2, pid_at(2));
+    };
+    if (!KV8) load_first();
     __syncthreads();                                  // the queries are in LDS, the new keys and values in the cache
 
     // query fragments of one row block, double buffered: those of the next row block (of the next page after the
@@ -401,12 +417,9 @@ __global__ __launch_bounds__(256, NRB <= 2 ? 2 : 1) void attn_partial_kernel(
     // and has no branch in its body, so that the compiler can count the loads in flight exactly; the last one or two
     // pages follow it.  Loads past the wavefront's last page re-read its clamped id (cache hits, results unused).
     static_assert(ATT_DEPTH == 3, "the loop body below is written for a ring of 3");
-    const int n_plain = plain_end > page0 + wave ? (plain_end - page0 - wave + ATT_WAVES - 1) / ATT_WAVES : 0;
     auto lpage_of = [&](int it) { return page0 + wave + ATT_WAVES * it; };
+    if (KV8) load_first();
     if (n_plain > 0) {
-        load_page(0, pid_at(0));
-        load_page(1, pid_at(1));
-        load_page(2, pid_at(2));
         process(plain_t{}, init_t{}, 0, lpage_of(0));
         int it = 1;
         for (; it + 3 <= n_plain; it += 3) {
