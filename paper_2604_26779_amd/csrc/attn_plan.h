@@ -16,14 +16,17 @@ struct AttnItem { int32_t b, seq, page0, page_end, ctx, total, chunk, pad; };
 // q heads | k heads | v heads of 128) and cos, sin of every row's 64 angles.
 struct QkvSlices { const float* part; int splits; int64_t split_stride; int ld; const float2* rope; };
 
-struct AttnPlanArgs { int budget, min_pages, forced, max_items; AttnItem* items; int2* entry_items; };
+struct AttnPlanArgs { int budget, min_pages, alone_pages, forced, max_items; AttnItem* items; int2* entry_items; };
 
 constexpr int PLAN_KEPT = 1024;              // batch entries whose page counts are kept in LDS
 
 // The whole workgroup (a multiple of 64 threads, at most 1024).  pages(b) = pages holding the keys batch entry b may see
 // (0 for a dropped entry).  Chunk length L: the smallest multiple of 4 in [min_pages, 256] with sum_b ceil(pages(b) / L)
 // <= budget (256 if none; `forced` > 0 fixes L instead); entry b then has n = ceil(pages / L) items of
-// ceil(pages / n) pages rounded up to a multiple of 4 (the 4 wavefronts take every 4th page).  Items are listed in batch
+// ceil(pages / n) pages rounded up to a multiple of 4 (the 4 wavefronts take every 4th page).  While chunks of up to alone_pages make at most
+// half that many items, no CU gets two of them: each costs the sums of its queries and a share of the merge, and a CU with two takes
+// as long as one chunk of twice the length (8B shape, us a step or eight layers of it: 7 sequences of 1k-8k 4 102 -> 4 042, two of 7k-8k 1 041 -> 1 017, four of
+// 500-4 000 with 8-bit matrices and cache 737 -> 705; chunks beyond 120 pages gain nothing or lose, 23 sequences of 500-4 000 1 560 -> 1 575).  Items are listed in batch
 // order; entry_items[b] = (first item, number of items).  Slots of the list beyond the last item get b = -1.  More
 // items than max_items (contexts beyond the bound the launch was sized for) set KV_ERR_BOUND and are dropped.
 // A chain of dependent steps on one workgroup: 7.7, 11 and 23 us at 5, 64 and 256 entries as a launch of its own that read the bookkeeping
@@ -64,8 +67,10 @@ __device__ inline void attn_plan(int B, int T, const KvView& kv, const AttnPlanA
             cnt = 0;
             for (int w = 0; w < waves; ++w) cnt += s_cnt[w * 64 + lane];
             const unsigned long long fits = __builtin_amdgcn_ballot_w64(len >= a.min_pages && cnt <= a.budget);
+            const unsigned long long alone = __builtin_amdgcn_ballot_w64(len >= a.min_pages && len <= a.alone_pages && 2 * cnt <= a.budget);
+            const unsigned long long take = alone ? alone : fits;
             if (lane == 0) {
-                s_len = a.forced > 0 ? a.forced : (fits ? 4 * (__builtin_ctzll(fits) + 1) : ATT_CP_MAX);
+                s_len = a.forced > 0 ? a.forced : (take ? 4 * (__builtin_ctzll(take) + 1) : ATT_CP_MAX);
                 s_carry = 0;
             }
         }
