@@ -447,3 +447,26 @@ def test_mapped_draft_sample_parity(B, Vd, V, temperature):
     assert np.all(q2_gpu[:, np.setdiff1d(np.arange(V), bad[valid])] == 0)
     assert np.all(guard[B * k * V:].cpu().numpy() == 0.25) and np.all(q2[:, [i for i in range(k) if i != row], :].cpu().numpy() == 0.25)
     assert np.all(np.isin(tok_b.cpu().numpy(), bad[valid]))
+
+
+@pytest.mark.parametrize("d_model", [256, 1536, 8448])
+def test_fused_input_of_narrow_and_wide_rows(d_model):
+    """The fusion operand for rows of less than a wavefront's channels, of three wavefronts', and of more than the workgroup covers in one pass."""
+    from paper_2604_26779_amd.session import VerifySession
+    rng = np.random.default_rng(4)
+    cfg = dict(si.MODELS["draft_fused_small_bf16"], vocab=300, d_model=d_model, n_q_heads=2, n_kv_heads=1, ffn_dim=2 * d_model)
+    B, k = 3, 1
+    weights = random_norm_gains(si.make_weights(cfg, seed=5), 5)
+    ctx = np.zeros(B, dtype=np.int64)
+    sess = VerifySession(cfg, {n: t.cuda() for n, t in weights.items()}, max_seqs=B, max_ctx_len=64, n_pages=16)
+    for b in range(B):
+        sess.assign(b, 0, [])
+    tokens = rng.integers(0, cfg["vocab"], size=(B, k + 1)).astype(np.int32)
+    hid = (rng.standard_normal((B, k + 1, d_model)) * 3.0).astype(np.float32)
+    want = of.verify_forward(cfg, si.weights_for_oracle(cfg, weights), si.kv_for_oracle(si.make_logical_kv(cfg, ctx, seed=5)), tokens, ctx, hidden_in=hid)[0]
+    got = sess.forward(torch.arange(B, dtype=torch.int32, device="cuda"), torch.from_numpy(tokens).cuda(), hidden_in=torch.from_numpy(hid).cuda())
+    torch.cuda.synchronize()
+    ok, max_err, worst = logits_close(got.cpu().numpy(), want, *TOL["bf16"])
+    print("d=%d: logits max abs err %.3e" % (d_model, max_err))
+    sess.close()
+    assert ok, (max_err, worst)
