@@ -513,7 +513,7 @@ __global__ void attn_reduce_kernel(const float* __restrict__ part_o, const float
     const int2 mine = entry_items[b];                        // (first item, number of items) of this batch entry
     const int n_chunks = mine.y;
     auto slot = [&](int c) { return ((int64_t)(mine.x + c) * Hkv + kvh) * RBrows + r; };
-    // up to RED chunks at a time, everything they need asked for together (past the last chunk it is read again and weighs nothing); the running
+    // up to RED chunks at a time, everything they need asked for together (past the last chunk it is read again and left out); the running
     // maximum moves between groups.  A trip for the list and one per group: 8.2 -> 5.5 us at 9 chunks a sequence (7 sequences), where a loop took a trip
     // per chunk and went over the maxima first; 5.1 -> 5.0 at two.
     constexpr int RED = 8;
@@ -540,11 +540,12 @@ __global__ void attn_reduce_kernel(const float* __restrict__ part_o, const float
         for (int j = 0; j < 8; ++j) o[j] *= move;
 #pragma unroll
         for (int u = 0; u < GN; ++u) {
-            const float f = c0 + u < n_chunks && ml[u].x > -INFINITY ? exp2f(ml[u].x - M) : 0.f;
-            if (f == 0.f) continue;                        // (whatever an empty chunk's place holds)
-            L += f * ml[u].y;
-            o[0] += f * a[u].x; o[1] += f * a[u].y; o[2] += f * a[u].z; o[3] += f * a[u].w;
-            o[4] += f * d[u].x; o[5] += f * d[u].y; o[6] += f * d[u].z; o[7] += f * d[u].w;
+            if (c0 + u >= n_chunks) continue;
+            const float f = ml[u].x > -INFINITY ? exp2f(ml[u].x - M) : 0.f;      // (0 for a chunk of NaN scores only: its NaN sums come through)
+            const float v[8] = {a[u].x, a[u].y, a[u].z, a[u].w, d[u].x, d[u].y, d[u].z, d[u].w};
+            L = fmaf(f, ml[u].y, L);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) o[j] = fmaf(f, v[j], o[j]);
         }
     };
     if (n_chunks > 0 && n_chunks <= 2) merge(0, std::integral_constant<int, 2>{});

@@ -802,6 +802,36 @@ def test_bf16_attention_merge_of_many_chunks(heads):
     assert ok, (max_err, worst)
 
 
+@pytest.mark.parametrize("model", ["small_bf16"])
+def test_nan_keys_of_one_chunk_are_not_dropped(model):
+    """Cached keys that are NaN over all of one chunk (four pages) make the sequence's logits what NaN
+    keys everywhere make them, instead of falling out of the merge and leaving logits that look sound; the other sequences do not notice."""
+    from paper_2604_26779_amd.session import VerifySession
+    cfg = dict(si.MODELS[model], vocab=500)
+    ctx_len, k = np.array([300, 300, 40]), 1
+    weights = {n: t.cuda() for n, t in si.make_weights(cfg, seed=2).items()}
+    kv = si.make_logical_kv(cfg, ctx_len, seed=2)
+
+    def logits(nan_from, nan_to):
+        sess = VerifySession(cfg, weights, max_seqs=3, max_ctx_len=512, n_pages=64)
+        for b, c in enumerate(ctx_len):
+            pages = list(range(20 * b, 20 * b + -(-int(c) // si.PAGE_SIZE)))
+            sess.assign(b, int(c), pages)
+            for l in range(cfg["n_layers"]):
+                K = kv[l][b][0].clone()
+                if b == 1:
+                    K[nan_from:nan_to] = float("nan")
+                sess.write_logical_kv(l, pages, K, kv[l][b][1])
+        got = sess.forward(torch.arange(3, dtype=torch.int32, device="cuda"), torch.full((3, k + 1), 7, dtype=torch.int32, device="cuda")).cpu().numpy()
+        sess.close()
+        return got
+
+    clean, chunk, whole = (_with_tune({"attn_chunk_pages": 4}, lambda: logits(*at)) for at in ((0, 0), (64, 128), (0, 300)))
+    assert np.isfinite(clean).all()
+    assert np.array_equal(chunk[[0, 2]], clean[[0, 2]])
+    assert np.array_equal(chunk[1], whole[1]) and not np.array_equal(chunk[1], clean[1])
+
+
 @pytest.mark.parametrize("d_model", [256, 1536, 8192, 8448])
 def test_bf16_norm_of_narrow_and_wide_rows(d_model):
     """Rows of less than one wavefront's channels, of three, of all the workgroup's, and of more than it covers in one pass."""
