@@ -419,10 +419,10 @@ __global__ __launch_bounds__(256) void f32_attention_split_kernel(const float* _
     __syncthreads();
     if ((int)threadIdx.x < dh) {
         float M = -INFINITY, L = 0.f, o = 0.f;
-        for (int w = 0; w < F32_ATT_WAVES; ++w) M = fmaxf(M, s_m[w]);
-        for (int w = 0; w < F32_ATT_WAVES; ++w) {
-            if (s_m[w] == -INFINITY) continue;                 // no position of its own
-            const float f = expf(s_m[w] - M);
+        const int waves = visible > 64 * (F32_ATT_WAVES - 1) ? F32_ATT_WAVES : (visible + 63) >> 6;      // those with positions of their own
+        for (int w = 0; w < waves; ++w) M = fmaxf(M, s_m[w]);
+        for (int w = 0; w < waves; ++w) {
+            const float f = s_m[w] > -INFINITY ? expf(s_m[w] - M) : 0.f;      // (0 where all scores are NaN: the NaN sums come through)
             L += f * s_l[w];
             for (int i = 0; i < groups; ++i) o += f * ((const float*)&s_o[w][i * quads])[threadIdx.x];
         }

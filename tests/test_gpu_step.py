@@ -802,9 +802,9 @@ def test_bf16_attention_merge_of_many_chunks(heads):
     assert ok, (max_err, worst)
 
 
-@pytest.mark.parametrize("model", ["small_bf16"])
+@pytest.mark.parametrize("model", ["small_bf16", "tiny_fp32"])
 def test_nan_keys_of_one_chunk_are_not_dropped(model):
-    """Cached keys that are NaN over all of one chunk (four pages) make the sequence's logits what NaN
+    """Cached keys that are NaN over all of one chunk (bf16: four pages; fp32: one wavefront's only 64 positions) make the sequence's logits what NaN
     keys everywhere make them, instead of falling out of the merge and leaving logits that look sound; the other sequences do not notice."""
     from paper_2604_26779_amd.session import VerifySession
     cfg = dict(si.MODELS[model], vocab=500)
