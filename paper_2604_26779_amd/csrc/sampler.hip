@@ -221,8 +221,17 @@ __global__ __launch_bounds__(SAMP_THREADS) void row_stats_kernel(const float* __
         float mx = -INFINITY;
 #pragma unroll
         for (int u = 0; u < STAT_GPT; ++u) {
-            asm("v_max3_f32 %0, %1, %2, %0" : "+v"(mx) : "v"(v[u][0]), "v"(v[u][1]));            // a NaN is left out, as below
-            asm("v_max3_f32 %0, %1, %2, %0" : "+v"(mx) : "v"(v[u][2]), "v"(v[u][3]));
+            asm("v_maximum3_f32 %0, %1, %2, %0" : "+v"(mx) : "v"(v[u][0]), "v"(v[u][1]));        // NaN as soon as one of the three is
+            asm("v_maximum3_f32 %0, %1, %2, %0" : "+v"(mx) : "v"(v[u][2]), "v"(v[u][3]));
+        }
+        // A NaN is left out, as below.  By comparisons and only where there is one: v_max3_f32 would leave out quiet ones, but lose what
+        // stands beside a signalling one.
+        if (__builtin_amdgcn_ballot_w64(mx != mx) != 0) {
+            mx = -INFINITY;
+#pragma unroll
+            for (int u = 0; u < STAT_GPT; ++u)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) mx = v[u][j] > mx ? v[u][j] : mx;
         }
         mx = wave_max(mx);
         if (mx > ref) {                                              // wavefront-uniform

@@ -257,3 +257,40 @@ def test_draft_draw_whose_map_leaves_out_the_top(V, top):
     want = p.copy()
     want[:, V // 3] = 0.0
     assert np.all(np.abs(q.cpu().numpy() - want) <= 2.0 ** -23 * want + 1.2e-38)
+
+
+@pytest.mark.parametrize("V", [50, 1003, 16384, 140000])
+@pytest.mark.parametrize("nan_bits", [0x7FC00000, 0x7F800001, 0xFF800001])
+@pytest.mark.parametrize("temperature", [1.0, 0.01])
+def test_nan_beside_the_largest_logit(V, nan_bits, temperature):
+    """A NaN among a row's finite logits, quiet or signalling, is left out: the same draws as with -inf in its place, also where the row's largest logit stands
+    right beside it (on either side, at any place of a group of four) and nothing else counts."""
+    from paper_2604_26779_amd import binding as sv
+    B, k = 12, 1
+    rng = np.random.default_rng(V)
+    logits = rng.standard_normal((B, k + 1, V)).astype(np.float32)
+    holes = np.zeros(logits.shape, dtype=bool)
+    for b in range(B):
+        for i in range(k + 1):
+            at = int(rng.integers(0, V - 8)) // 4 * 4 + b % 4
+            logits[b, i, at] = 30.0
+            holes[b, i, at + 1 if b % 2 or at == 0 else at - 1] = True
+            holes[b, i, rng.integers(0, V)] |= b >= 8
+            holes[b, i, at] = False
+    q = _softmax(rng.standard_normal((B, k, V))).astype(np.float32)
+    draft = rng.integers(0, V, size=(B, k)).astype(np.int32)
+    draft[::2, 0] = logits[::2, 0].argmax(-1)
+    outcome = []
+    for fill in (nan_bits, 0xFF800000):
+        L = logits.copy()
+        L.view(np.uint32)[holes] = fill
+        dl = torch.from_numpy(L.view(np.int32)).cuda().view(torch.float32)
+        n, out = torch.empty(B, dtype=torch.int32, device="cuda"), torch.empty((B, k + 1), dtype=torch.int32, device="cuda")
+        ws = torch.empty(sv.spec_sample_workspace_bytes(B, k), dtype=torch.uint8, device="cuda")
+        sv.spec_reject_sample(B, k, V, dl, torch.from_numpy(q).cuda(), torch.from_numpy(draft).cuda(), temperature, 77, 4, n, out, None, ws)
+        tok, qd = torch.empty(B, dtype=torch.int32, device="cuda"), torch.empty((B, V), device="cuda")
+        sv.spec_draft_sample(B, V, dl, (k + 1) * V, temperature, 5, 2, 1, tok, 1, None, 1, qd, V)
+        outcome.append([n.cpu().numpy(), out.cpu().numpy(), tok.cpu().numpy(), qd.cpu().numpy()[~holes[:, 0]]])
+    for a, b in zip(*outcome):
+        assert np.array_equal(a, b)
+    assert np.array_equal(outcome[0][2], logits[:, 0].argmax(-1)) or temperature == 1.0
