@@ -32,8 +32,21 @@ constexpr int GEMM_WD = 2;          // slabs of weight fragments each wavefront 
 constexpr int GEMM_KUNIT = GEMM_KS * 4;             // K is a multiple of 16 times this
 
 // how many slabs ahead the activations of a tile of mb row blocks are requested.  Two, but one for the large slabs of two hi + lo row blocks and more
-// (QKV / output projection of the 8B shape at 64 rows 14.2 / 10.9 us with two, 14.0 / 10.7 with one; at 4 rows 10.9 / 8.1 and 11.2 / 8.2)
+// (QKV / output projection of the 8B shape at 64 rows 14.2 / 10.9 us with two, 14.0 / 10.7 with one; at 4 rows 10.9 / 8.1 and 11.2 / 8.2), and
+// one in an unsplit launch that crowds the chip: workgroups on one CU cover each other's waits, and requests further ahead only hold up the weight
+// stream.  With 16-bit weights that is from one workgroup per CU to three (gate/up of 2 x 18944 and 2 x 28672 columns at 64 rows 71.5 -> 69.5,
+// 80.3 -> 78.1 us, heads of 48000 at 4 rows and 64000 at 64 68.8 -> 66.0, 86.7 -> 84.1; with one each or less 45.6 -> 46.5; with four and five either way
+// within 2 %: 128256 at 32 and 96 rows 163.8 -> 161.4, 189.5 -> 191.7); with 8-bit ones at 65 rows and more from one on (18944 columns at 96 rows 57.6 ->
+// 54.4), below, where few bytes are in flight, from 7/4 on (heads of 96000 columns at 48 rows 76.9 -> 73.5, 128256 at 4, 16 and 32 rows 84.0 -> 80.5,
+// 90.7 -> 85.4, 91.9 -> 87.2; 18944 columns at 4 rows 38.1 -> 39.8, 32000 26.0 -> 30.8).  Of the 256-column tiles only the 8-bit ones of 64 rows gain
+// (128256 at 64 rows 89.6 -> 87.5).  All at K = 4096.
 constexpr int gemm_slabs_ahead(int mb, int xf) { return mb == 1 || xf == XF_F16 ? 2 : 1; }
+static bool gemm_crowded(int64_t workgroups, bool w8, int mb, bool one_block)
+{
+    constexpr int CUS = 256;
+    if (!w8) return workgroups > CUS && workgroups <= 3 * CUS;
+    return workgroups * 4 > CUS * (one_block && mb <= 2 ? 7 : 4);
+}
 
 // from gemm_big.hip
 spec_status launch_gemm_big(const PackedW& W, const bf16_t* Xp, int M, int mb, int mb_pad, float* out, int ldo, int kps, bool swiglu,
@@ -214,13 +227,14 @@ spec_status w8_pack_matrix(const unsigned char* const* dev_parts, const float* c
 // queue and the last slab of the weights re-read past the end / now: QKV, output, gate/up and down projection at 4 rows 12.2, 8.9, 36.6, 19.9 /
 // 10.6, 7.8, 35.0, 19.0; at 64 rows 14.3, 10.8, 40.0, 21.3 / 13.7, 10.1, 37.2, 20.3; at 96 rows 18.5, 14.3, 44.5, 24.5 / 16.2, 11.8, 42.3, 22.2; at 128
 // rows 20.0, 15.3, 48.1, 26.7 / 19.1, 14.5, 46.5, 25.5.  With 8-bit weights at 4 rows 10.0, 7.1, 27.5, 14.3 / 8.5, 6.1, 21.6, 11.7, at 128 rows 17.8, 13.7, 40.7,
-// 23.2 / 16.5, 12.9, 35.0, 21.1; only a head of 1002 tiles, four workgroups on a CU, loses 3-5 % with 8-bit weights and up to 64 rows.
+// 23.2 / 16.5, 12.9, 35.0, 21.1.
 // EPI: PLAIN, SWIGLU (fused), or for an output that is not split along K - in the first place the head's logits, tens of megabytes that
 // nobody reads before the launch ends - STREAM: stored past the L2s, it does not push out what the workgroups share there (head of 128256
 // rows at 64, 74 and 128 rows: 171 -> 164, 198 -> 177, 184 -> 172 us; slices of a split output are small and gain nothing).  STREAM_SHARED: the
 // same with several row tiles, whose workgroups also share the weights: ordinary instead of nontemporal loads (32000 rows at 160
 // and 256 rows: 104 -> 91, 116 -> 93 us; with one row tile, or split, the nontemporal ones are ahead, 164 against 181 us at 64 rows).
-template <int MB, int WM, int EPI, bool GROUPED = false, int NBW_T = WM, bool W8 = false, int XF = XF_HILO, int WD = GEMM_WD>
+template <int MB, int WM, int EPI, bool GROUPED = false, int NBW_T = WM, bool W8 = false, int XF = XF_HILO, int WD = GEMM_WD,
+          int LA = gemm_slabs_ahead(MB, XF)>
 __global__ __launch_bounds__(GEMM_THREADS, (MB >= 3 && WM == 1 && NBW_T == 2) ? 1 : 2) void gemm_bf16_kernel(
     const u32x4_t* __restrict__ Wp, const u32x4_t* __restrict__ Xp, float* __restrict__ out, int n_blocks, int k_steps,
     int ksteps_per_split, int mb_pad, int M, int N, int ldo, int64_t split_stride,
@@ -234,7 +248,7 @@ __global__ __launch_bounds__(GEMM_THREADS, (MB >= 3 && WM == 1 && NBW_T == 2) ? 
     constexpr int SLAB = KS * MB * 64 * XF;             // u32x4_t per slab (XF operand words per lane and k-step)
     constexpr int XPT = SLAB / GEMM_THREADS;            // u32x4_t per thread per slab
     static_assert(SLAB % GEMM_THREADS == 0, "a slab must divide over the threads");
-    constexpr int LA = gemm_slabs_ahead(MB, XF), NX = LA + 1;
+    constexpr int NX = LA + 1;
     static_assert(LA <= WD && (WD == 2 || WD == 4), "the waits below count the weight loads behind an activation slab");
     // the fused SwiGLU epilogue re-uses the slabs as an fp32 transpose tile, which may be the larger of the two
     constexpr int EPI_WORDS = EPI != GEMM_EPI_SWIGLU ? 0 : (WM == 1 ? 32 * 129 : MB * 32 * 65) / 4 + 1;
@@ -652,12 +666,16 @@ spec_status launch_gemm_bf16(const PackedW& W, const bf16_t* Xp, int M, float* o
     const u32x4_t* xp = (const u32x4_t*)Xp;
     if (swiglu && !gemm_can_fuse_swiglu(W, M, splits)) { set_error("gemm: SwiGLU cannot be fused for this shape"); return SPEC_EUNSUPPORTED; }
     const int epi = swiglu ? GEMM_EPI_SWIGLU : (grid.y > 1 ? GEMM_EPI_PLAIN : (grid.z > 1 ? GEMM_EPI_STREAM_SHARED : GEMM_EPI_STREAM));
+    const bool crowded = gemm_crowded((int64_t)grid.x * grid.z, W.w8, mb, g.one_block || mb == 1);
 #define SPEC_GEMM_CALL(...) gemm_bf16_kernel<__VA_ARGS__><<<grid, GEMM_THREADS, 0, s>>>(wp, xp, out, W.n_blocks, W.k_steps, kps, mb_pad, M, W.N, ldo, stride, nullptr, 0, W.scale)
     // MB row blocks, WM wavefronts along the rows, NBW column blocks per wavefront.  One column block and 8-bit weights, half the bytes a slab: a weight ring
-    // of four slabs where the split allows it (gate/up of the 8B shape at 4 and 128 rows 26.3 -> 22.9, 39.6 -> 36 us)
+    // of four slabs where the split allows it and the launch does not crowd the chip (gate/up of the 8B shape at 4 and 128 rows 26.3 -> 22.9, 39.6 -> 36 us;
+    // heads of 64000 and 151936 columns, K = 2048, at 64 and 32 rows 32.7 / 31.9, 61.4 / 59.3 with four / two)
 #define SPEC_GEMM_TILE(MB, WM, NBW, E, W8, XF) do { \
-        if (W8 && NBW == 1 && kps % (4 * GEMM_KS) == 0) SPEC_GEMM_CALL(MB, WM, E, false, NBW, W8, XF, W8 && NBW == 1 ? 4 : 2); \
-        else SPEC_GEMM_CALL(MB, WM, E, false, NBW, W8, XF, 2); } while (0)
+        constexpr int FAR = gemm_slabs_ahead(MB, XF), NEAR = (NBW == 1 || WM == 2 || (W8 && MB == 2)) && E != GEMM_EPI_PLAIN ? 1 : FAR; \
+        if (crowded) SPEC_GEMM_CALL(MB, WM, E, false, NBW, W8, XF, 2, NEAR); \
+        else if (W8 && NBW == 1 && kps % (4 * GEMM_KS) == 0) SPEC_GEMM_CALL(MB, WM, E, false, NBW, W8, XF, W8 && NBW == 1 ? 4 : 2, FAR); \
+        else SPEC_GEMM_CALL(MB, WM, E, false, NBW, W8, XF, 2, FAR); } while (0)
     // the four combinations of 8-bit or 16-bit weights and hi + lo or fp16 activations
 #define SPEC_GEMM_BY_TYPE(MB, WM, NBW, E) do { \
         if (W.w8) { if (W.f16) SPEC_GEMM_TILE(MB, WM, NBW, E, true, XF_F16); else SPEC_GEMM_TILE(MB, WM, NBW, E, true, XF_HILO); } \

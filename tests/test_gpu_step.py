@@ -832,6 +832,18 @@ def test_nan_keys_of_one_chunk_are_not_dropped(model):
     assert np.array_equal(chunk[1], whole[1]) and not np.array_equal(chunk[1], clean[1])
 
 
+@pytest.mark.parametrize("w8", [False, True])
+@pytest.mark.parametrize("B,k", [(1, 3), (9, 4), (12, 7), (25, 3)])
+def test_bf16_more_workgroups_than_cus(B, k, w8):
+    """A head of 313 column tiles and a fused gate/up projection of 260, more than the chip has CUs, so that the activations are requested one slab ahead:
+    one to four row blocks, K of eight slabs."""
+    rng = np.random.default_rng(B)
+    ctx = [int(c) for c in rng.integers(3, 60, size=B)]
+    ok, max_err, worst = _run_custom_bf16(ctx, k=k, seed=B, vocab=40000, n_layers=1, ffn_dim=16640, **(dict(w_dtype="fp8_e4m3") if w8 else {}))
+    print("M=%d, 8-bit matrices %s: logits max abs err %.3e" % (B * (k + 1), w8, max_err))
+    assert ok, (max_err, worst)
+
+
 @pytest.mark.parametrize("d_model", [256, 1536, 8192, 8448])
 def test_bf16_norm_of_narrow_and_wide_rows(d_model):
     """Rows of less than one wavefront's channels, of three, of all the workgroup's, and of more than it covers in one pass."""
