@@ -31,9 +31,9 @@ static std::map<std::string, int>& tune_table()
         {"fuse_swiglu", 1},        // 1: silu(gate) * up in the gate/up projection's epilogue, where K is unsplit
         {"attn_row_blocks", 0},    // most 16-row blocks per attention workgroup (1..4; 0 = up to 4, groups as equal as possible)
         {"gemm_max_mb", 4},        // 32-row blocks per GEMM tile (1..4): smaller tiles = more workgroups, weights read once per tile
-        {"gemm_split_rows", 2},     // GEMMs of up to this many 128-row tiles (97..256 rows at 2) run as 64-row x 256-column tiles instead (0 = never)
+        {"gemm_split_rows", 2},     // GEMMs of up to this many 128-row tiles (97..256 rows at 2) run as 64-row x 256-column tiles instead, or as those of gemm_tiles_96 (0 = never)
         {"gemm_big_min_tiles", 200}, // a GEMM with at least this many 256-column tiles takes them without further conditions
-        {"gemm_tiles_96", 1},       // 129..256 rows, fused gate/up projection: two 96- or 128-row x 256-column tiles per column stripe instead of three or four 64-row ones
+        {"gemm_tiles_96", 1},       // 129..256 rows: two 96- or 128-row x 256-column tiles per column stripe instead of three or four 64-row ones, for the fused gate/up projection and where plain outputs are ahead with them (0 = never)
         {"gemm_wide4", 400},        // single-tile 128-row GEMMs with a plain epilogue take 128 x 256 tiles from this many such tiles on (0 = never)
         {"gemm_one_block", 1},      // 33..64 rows, and 97..128 rows with fp16 activations: one tile of all rows x 128 columns, wavefronts 1 x 4 with one column block each (0: 2 x 2, or as with hi + lo operands)
         {"moe_wide_tiles", 1},      // grouped expert GEMMs: 64 x 256 tiles, wavefronts 1 x 4 (0: 64 x 128, wavefronts 2 x 2)
@@ -270,6 +270,7 @@ extern "C" spec_status spec_model_create(const spec_model_desc* desc, const void
             }
         }
         if (st == SPEC_OK) st = pack8({m->head_w()}, {m->head_scale()}, {head_rows(d)}, D, &m->head, f16_mask & 8);
+        m->head.whole = 1;
         if (st == SPEC_OK && hipDeviceSynchronize() != hipSuccess) { set_error("spec_model_create: weight tiling failed on the device"); st = SPEC_EHIP; }
         if (st != SPEC_OK) { (void)hipFree(m->arena); delete m; return st; }
     } else if (desc->dtype == SPEC_BF16) {
@@ -324,6 +325,7 @@ extern "C" spec_status spec_model_create(const spec_model_desc* desc, const void
             }
         }
         if (st == SPEC_OK) st = pack({m->head_w()}, {head_rows(d)}, D, &m->head, f16_mask & 8);
+        m->head.whole = 1;
         if (st == SPEC_OK && d.fuse_hidden) st = pack({m->fuse_w(0)}, {D}, 2 * D, &m->wfuse, false);
         if (st == SPEC_OK && d.fuse_taps) st = pack({m->fuse_w(3)}, {D}, d.fuse_taps * D, &m->wfc, false);
         if (st == SPEC_OK && hipDeviceSynchronize() != hipSuccess) { set_error("spec_model_create: weight tiling failed on the device"); st = SPEC_EHIP; }

@@ -76,6 +76,7 @@ struct PackedW {
     int32_t f16 = 0;               // 1: the activations come as one fp16 per value and the weights are fp16 (converted once;
                                    //    8-bit codes are widened to fp16); 0: hi + lo bf16 pairs against bf16 weights
     const float* scale = nullptr;
+    int32_t whole = 0;             // 1: K is never split (the output head, whose logits are written in place)
 };
 
 }  // namespace specv

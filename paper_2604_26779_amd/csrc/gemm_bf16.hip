@@ -231,8 +231,10 @@ spec_status w8_pack_matrix(const unsigned char* const* dev_parts, const float* c
 // EPI: PLAIN, SWIGLU (fused), or for an output that is not split along K - in the first place the head's logits, tens of megabytes that
 // nobody reads before the launch ends - STREAM: stored past the L2s, it does not push out what the workgroups share there (head of 128256
 // rows at 64, 74 and 128 rows: 171 -> 164, 198 -> 177, 184 -> 172 us; slices of a split output are small and gain nothing).  STREAM_SHARED: the
-// same with several row tiles, whose workgroups also share the weights: ordinary instead of nontemporal loads (32000 rows at 160
-// and 256 rows: 104 -> 91, 116 -> 93 us; with one row tile, or split, the nontemporal ones are ahead, 164 against 181 us at 64 rows).
+// same with several row tiles of 64 rows, whose workgroups also share the weights: ordinary instead of nontemporal loads (two 8B layers and a head of
+// 40960 columns at 160 and 256 rows 625 -> 615, 769 -> 746 us; QKV of 10240 x 2048 and the attention's prologue at 256 rows 54.6 -> 52.7).  Not with tall
+// tiles, of which two share them (a draft pass with a head of 32000 columns at 140 and 256 rows 492 -> 505, 624 -> 650), with one row tile
+// (164 -> 181 at 64 rows) or where K is split.
 template <int MB, int WM, int EPI, bool GROUPED = false, int NBW_T = WM, bool W8 = false, int XF = XF_HILO, int WD = GEMM_WD,
           int LA = gemm_slabs_ahead(MB, XF)>
 __global__ __launch_bounds__(GEMM_THREADS, (MB >= 3 && WM == 1 && NBW_T == 2) ? 1 : 2) void gemm_bf16_kernel(
@@ -566,7 +568,7 @@ int gemm_mb_pad(int M)
 }
 
 struct GemmShape { int mb, tile_nb, kunit, m_tiles, n_tiles; bool wide = false, one_block = false; };
-static GemmShape gemm_shape(const PackedW& W, int M, bool fused_swiglu)
+GemmShape gemm_shape(const PackedW& W, int M, bool fused_swiglu)      // (not static: the dispatch has a test)
 {
     GemmShape g;
     const int pad = gemm_mb_pad(M), big = gemm_big_mb(M);
@@ -614,15 +616,24 @@ static GemmShape gemm_shape(const PackedW& W, int M, bool fused_swiglu)
     }
     if (g.mb == 4 && g.m_tiles <= tune("gemm_split_rows") && W.n_blocks % 8 == 0) {
         const int nb = (int)cdiv(M, 32);
-        // 129..256 rows, plain epilogue: the tall tiles too, where K stays unsplit and they fill the chip (a reduced head: 32000 rows at 160 and 256
-        // rows 93 -> 65, 94 -> 71 us), where the 64-row ones leave half of it idle (9216 x 4096 at 256 rows, 144 workgroups: 52.8 -> 41.4), and with fp16
-        // inputs against 16-bit weights (down projection at 160 and 256 rows 38.6 -> 32.1, 45.5 -> 35.7, more than the three or four slices
-        // more cost the norm).  Elsewhere those slices make them the slower ones (hi + lo projections of the 8B shape 20.3 -> 23.0; 8-bit down
-        // projection equal).
-        const int n_tall = (int)cdiv(nb, nb <= 6 ? 3 : 4) * (W.n_blocks / 8), n_64 = (int)cdiv(nb, 2) * (W.n_blocks / 8), target = tune("gemm_wg_target");
-        const bool tall = fused_swiglu || (n_tall * 4 >= target * 3 && n_tall <= target) || (n_64 * 2 > target && n_64 * 8 < target * 5) || (W.f16 && !W.w8 && n_64 <= target);
-        if (nb >= 5 && tall && tune("gemm_tiles_96") != 0) g.mb = nb <= 6 ? 3 : 4;
-        else g.mb = 2;
+        // 129..256 rows, plain epilogue: the tall tiles too (K = 4096 unless stated; us, 64-row / tall)
+        //  - where K stays whole in either and their workgroups fill the chip in one round, which the 64-row ones exceed: two 8B layers and a head of 24576
+        //    columns at 160 and 256 rows 564 / 557, 681 / 658, of 32000 598 / 569, 698 / 669; a draft pass with 32000 at 256 rows 666 / 624.  Not with 8-bit
+        //    weights and four row blocks: 602 / 609, 616 / 618;
+        //  - where the 64-row ones leave K whole on part of the chip and the tall ones get enough slices to do less each (1.5 or 2 times the rows in 1/2 or
+        //    1/3 of K; projection and the reader of its slices): 9216, 10240 columns at 256 rows 78.0 / 67.7, 78.5 / 69.6; 12288, 16384 at 160 88.7 / 75.9, 97.4 /
+        //    86.1; with two slices for twice the rows 92.5 / 89.7 at best (K = 4096), 72.8 / 74.1 (K = 2560).  The slices cost the same whatever K: 9216 columns at
+        //    256 rows 64.0 / 60.2 at K = 3072, 57.7 / 57.0 at 2560, 50.1 / 53.0 at 2048.  Never the head, which is not split (with
+        //    one of 16384 columns at 160 and 256 rows 530 / 552, 627 / 653);
+        //  - K split either way, fp16 inputs against 16-bit weights, from an eighth of the chip on (down projection and the norm, K = 3.5 N: 4096 columns at 160
+        //    and 256 rows 61.3 / 57.7, 69.9 / 65.6, 8192 columns 192 / 144, 200 / 162; 3072 at 160 46.2 / 45.4, 2048 at 256 38.7 / 40.7, 1024 28.8 / 32.5).
+        //    Hi + lo (20.3 / 23.0) and 8-bit weights (49.4 / 49.4, 58.4 / 60.2) lose by the additional slices.
+        const int cols = W.n_blocks / 8, mb_tall = nb <= 6 ? 3 : 4, target = tune("gemm_wg_target");
+        const int n_tall = (int)cdiv(nb, mb_tall) * cols, n_64 = (int)cdiv(nb, 2) * cols, slices = std::max(1, target / n_tall);
+        const bool fills = n_tall * 4 >= target * 3 && n_tall <= target && !(W.w8 && mb_tall == 4);
+        const bool idle = !W.whole && n_64 * 2 > target && n_64 <= target && mb_tall < 2 * slices && W.k_steps >= 160;
+        const bool split = !W.whole && W.f16 && !W.w8 && n_64 * 8 > target && n_64 <= target;
+        g.mb = nb >= 5 && (fused_swiglu || fills || idle || split) && tune("gemm_tiles_96") != 0 ? mb_tall : 2;
         g.m_tiles = (int)cdiv(nb, g.mb); g.wide = true; g.tile_nb = 8; g.n_tiles = W.n_blocks / 8; g.kunit = GEMM_KS * 2;
         return g;
     }

@@ -86,3 +86,23 @@ def random_norm_gains(weights, seed):
         if name.endswith("norm"):
             weights[name] = (1.0 + 0.3 * torch.randn(t.shape, generator=g)).to(t.dtype).to(t.device)
     return weights
+
+
+def gemm_shape(N, K, M, w8=False, f16=False, whole=False, swiglu=False):
+    """The tile the library takes for a GEMM of N columns at M rows: dict(mb = 32-row blocks, tile_nb = 32-column blocks, kunit, m_tiles, n_tiles, wide,
+    one_block), under the tuning parameters as they are.  Needs no GPU.  f16: one fp16 value per activation; whole: K is never split (the head)."""
+    import ctypes
+
+    from paper_2604_26779_amd import binding
+
+    class PackedW(ctypes.Structure):
+        _fields_ = [("data", ctypes.c_void_p)] + [(n, ctypes.c_int32) for n in ("N", "K", "n_blocks", "k_steps", "w8", "f16")] + \
+                   [("scale", ctypes.c_void_p), ("whole", ctypes.c_int32)]
+
+    class GemmShape(ctypes.Structure):
+        _fields_ = [(n, ctypes.c_int) for n in ("mb", "tile_nb", "kunit", "m_tiles", "n_tiles")] + [("wide", ctypes.c_bool), ("one_block", ctypes.c_bool)]
+
+    fn = binding.lib()["_ZN5specv10gemm_shapeERKNS_7PackedWEib"]
+    fn.restype, fn.argtypes = GemmShape, [ctypes.POINTER(PackedW), ctypes.c_int, ctypes.c_bool]
+    g = fn(ctypes.byref(PackedW(None, N, K, -(-N // 32), K // 16, int(w8), int(f16), None, int(whole))), M, swiglu)
+    return {n: getattr(g, n) for n, _ in GemmShape._fields_}

@@ -16,7 +16,7 @@ import synth_inputs as si
 from oracle import commit as oracle_commit
 from oracle import forward as of
 from oracle import sampler as oracle_sampler
-from tests.helpers import random_norm_gains, assert_sampler_parity, logits_close, oracle_drafts
+from tests.helpers import random_norm_gains, assert_sampler_parity, gemm_shape, logits_close, oracle_drafts
 
 pytestmark = pytest.mark.gpu
 
@@ -853,14 +853,36 @@ def test_bf16_norm_of_narrow_and_wide_rows(d_model):
 
 
 @pytest.mark.parametrize("w8", [False, True])
-@pytest.mark.parametrize("target", [14, 18, 256])
+@pytest.mark.parametrize("target", [10, 16, 40])
 @pytest.mark.parametrize("B,k", [(33, 3), (40, 3), (43, 4), (64, 3)])
 def test_bf16_tall_tiles_for_plain_projections(B, k, target, w8):
-    """129..256 rows: 96- and 128-row x 256-column tiles for plain outputs too, unsplit (QKV projection at a workgroup target of 14 or 18) and split
-    (down projection), 132, 160, 215 and 256 rows in either operand format and weight type."""
-    rng = np.random.default_rng(B * 10 + k)
-    ctx = [int(c) for c in rng.integers(3, 120, size=B)]
-    ok, max_err, worst = _with_tune({"gemm_wg_target": target, "gemm_min_ksteps": 16, "gemm_big_min_blocks": 0 if target == 18 else 5},
-                                    lambda: _run_custom_bf16(ctx, k=k, seed=B + k, vocab=1000, **(dict(w_dtype="fp8_e4m3") if w8 else {})))
-    print("M=%d, target %d, 8-bit matrices %s: logits max abs err %.3e" % (B * (k + 1), target, w8, max_err))
+    """129..256 rows: 96- and 128-row x 256-column tiles for plain outputs too, K whole (the head at a workgroup target of 10, the QKV projection at 16) and split
+    (the down projection at 40), 132, 160, 215 and 256 rows in either operand format and weight type."""
+    M, cfg = B * (k + 1), si.MODELS["small_bf16"]
+    d, nq, nkv = cfg["d_model"], cfg["n_q_heads"] * cfg["head_dim"], cfg["n_kv_heads"] * cfg["head_dim"]
+    tall = 3 if M <= 192 else 4
+
+    def run():
+        shapes = {10: gemm_shape(1000, d, M, w8, True, whole=True), 16: gemm_shape(nq + 2 * nkv, d, M, w8), 40: gemm_shape(d, cfg["ffn_dim"], M, w8, True)}
+        reaches = not w8 if target == 40 else not (w8 and tall == 4)
+        assert shapes[target]["wide"] and shapes[target]["mb"] == (tall if reaches else 2), shapes
+        rng = np.random.default_rng(B * 10 + k)
+        ctx = [int(c) for c in rng.integers(3, 120, size=B)]
+        return _run_custom_bf16(ctx, k=k, seed=B + k, vocab=1000, **(dict(w_dtype="fp8_e4m3") if w8 else {}))
+
+    ok, max_err, worst = _with_tune({"gemm_wg_target": target, "gemm_min_ksteps": 16, "gemm_big_min_blocks": 0 if target == 16 else 5}, run)
+    print("M=%d, target %d, 8-bit matrices %s: logits max abs err %.3e" % (M, target, w8, max_err))
+    assert ok, (max_err, worst)
+
+
+@pytest.mark.parametrize("w8", [False, True])
+@pytest.mark.parametrize("B,k,heads,mb", [(33, 3, 96, 3), (64, 3, 72, 4), (64, 3, 80, 4)])
+def test_bf16_tall_tiles_where_64_row_ones_leave_cus_idle(B, k, heads, mb, w8):
+    """QKV projections of K = 2560 whose 64-row tiles would not be split and leave part of the chip idle: two or three slices of tall tiles."""
+    M, d = B * (k + 1), 2560
+    shape = gemm_shape(heads * 128, d, M, w8)
+    assert shape["wide"] and shape["mb"] == mb and gemm_shape(heads * 128, 2048, M, w8)["mb"] == 2
+    ok, max_err, worst = _run_custom_bf16([(5 * b) % 37 for b in range(B)], k=k, seed=B, vocab=300, n_layers=1, d_model=d, n_q_heads=heads - 16, n_kv_heads=8, ffn_dim=256,
+                                          **(dict(w_dtype="fp8_e4m3") if w8 else {}))
+    print("M=%d, %d heads, 8-bit matrices %s: logits max abs err %.3e" % (M, heads, w8, max_err))
     assert ok, (max_err, worst)
