@@ -42,7 +42,7 @@ static std::map<std::string, int>& tune_table()
         {"splits_qkv", 0}, {"splits_o", 0}, {"splits_gu", 0}, {"splits_down", 0}, {"splits_head", 0},   // 0 = auto (splits_gu: a gate/up projection of an even row-block count never splits K while fuse_swiglu is on)
         {"attn_chunk_pages", 0},   // KV pages per attention workgroup (a multiple of 4 up to 256; 0 = chosen on the device from the batch's contexts)
         {"attn_rounds", 1},        // the attention's work list is cut to fill the chip's resident workgroups this many times over (B=32, contexts 1k..8k: 3.41 ms of attention per step at 1, 3.54 at 2, 3.60 at 3)
-        {"attn_alone_pages", 120},   // chunks of up to this many pages are chosen so long that no CU gets two of them
+        {"attn_alone_pages", 120},   // at attn_rounds = 1, chunks of up to this many pages are chosen so long that no CU gets two of them (0 = never)
         {"attn_min_pages", 16},    // shortest chunk the device-side choice may take (pages)
         // Which projections take one fp16 activation per value (one MFMA per weight fragment, weights tiled as fp16) instead of
         // hi + lo bf16 pairs (two MFMAs): bit 0 QKV, 1 attention output, 2 feed-forward (gate/up and down, experts included),

@@ -609,7 +609,8 @@ AttnPlanArgs attention_plan_args(int B, int T, int G, int Hkv, int pages_bound, 
     const AttnPlan pl = attn_layout(T * G, B, Hkv, pages_bound);
     int min_pages = tune("attn_min_pages");
     if (min_pages < ATT_WAVES) min_pages = ATT_WAVES;
-    return AttnPlanArgs{pl.budget, min_pages, pl.RB <= 2 ? tune("attn_alone_pages") : 0, pl.forced, pl.max_items, (AttnItem*)items, (int2*)entry_items};
+    // (half the budget is one workgroup per CU where two fit and the list is cut for one round of them)
+    return AttnPlanArgs{pl.budget, min_pages, pl.RB <= 2 && tune("attn_rounds") <= 1 ? tune("attn_alone_pages") : 0, pl.forced, pl.max_items, (AttnItem*)items, (int2*)entry_items};
 }
 
 spec_status launch_attention_bf16(const QkvSlices& in, int B, int T, int G, int Hq, int Hkv, const KvView& kv, int layer_pool, int layer,

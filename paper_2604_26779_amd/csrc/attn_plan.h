@@ -23,7 +23,7 @@ constexpr int PLAN_KEPT = 1024;              // batch entries whose page counts 
 // The whole workgroup (a multiple of 64 threads, at most 1024).  pages(b) = pages holding the keys batch entry b may see
 // (0 for a dropped entry).  Chunk length L: the smallest multiple of 4 in [min_pages, 256] with sum_b ceil(pages(b) / L)
 // <= budget (256 if none; `forced` > 0 fixes L instead); entry b then has n = ceil(pages / L) items of
-// ceil(pages / n) pages rounded up to a multiple of 4 (the 4 wavefronts take every 4th page).  While chunks of up to alone_pages make at most
+// ceil(pages / n) pages rounded up to a multiple of 4 (the 4 wavefronts take every 4th page).  While chunks of up to alone_pages (0 if the list is cut for several rounds) make at most
 // half that many items, no CU gets two of them: each costs the sums of its queries and a share of the merge, and a CU with two takes
 // as long as one chunk of twice the length (8B shape, us a step or eight layers of it: 7 sequences of 1k-8k 4 102 -> 4 042, two of 7k-8k 1 041 -> 1 017, four of
 // 500-4 000 with 8-bit matrices and cache 737 -> 705; chunks beyond 120 pages gain nothing or lose, 23 sequences of 500-4 000 1 560 -> 1 575).  Items are listed in batch

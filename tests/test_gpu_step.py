@@ -792,6 +792,28 @@ def test_bf16_work_list_of_many_entries(B, k):
     assert ok, (max_err, worst)
 
 
+def test_bf16_work_list_of_more_than_one_round():
+    """A work list cut for two rounds of workgroups is what attn_rounds and attn_min_pages make it, whatever attn_alone_pages says; cut for one it gets the
+    longer chunks of one workgroup per CU.  (Another chunk length is another order of the sums: other bits.)"""
+    from paper_2604_26779_amd.session import VerifySession
+    cfg = dict(si.MODELS["small_bf16"], n_layers=1, vocab=300)
+    B, ctx = 60, 300
+    sess = VerifySession(cfg, {n: t.cuda() for n, t in si.make_weights(cfg, seed=1).items()}, max_seqs=B, max_ctx_len=512, n_pages=B * 24)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    sess.pool.normal_(generator=g)
+    for b in range(B):
+        sess.assign(b, ctx, list(range(20 * b, 20 * b + 19)))
+    ids, tokens = torch.arange(B, dtype=torch.int32, device="cuda"), torch.full((B, 1), 7, dtype=torch.int32, device="cuda")
+
+    def logits(rounds, alone):
+        return _with_tune({"attn_rounds": rounds, "attn_alone_pages": alone, "attn_min_pages": 4}, lambda: sess.forward(ids, tokens).cpu().numpy())
+
+    assert np.array_equal(logits(2, 120), logits(2, 0))
+    assert not np.array_equal(logits(1, 120), logits(1, 0))
+    sess.close()
+
+
 @pytest.mark.parametrize("heads", [(8, 2), (4, 4)])
 def test_bf16_attention_merge_of_many_chunks(heads):
     """One, two, three, eight, nine and eighteen chunks a sequence (the merge takes them two or eight at a time), one of them huge in its keys."""
