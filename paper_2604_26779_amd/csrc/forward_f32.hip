@@ -531,8 +531,9 @@ spec_status f32_forward(spec_model* mdl, spec_kv* kv, int B, int k, const int32_
 
     f32_embed_kernel<<<M, 256, 0, s>>>(dev_tokens, (const float*)mdl->embed(), D, d.vocab, T, view, w.x, w.row_at);
     const bool quads = dh % 4 == 0;
-    // Four wavefronts per row and head while one each would not give every SIMD of the chip one: forward pass at contexts of 700, one / four, us: 64 rows x 8
-    // heads 516 / 332, x 16 heads 925 / 764; 256 rows x 8 heads 391 / 405, x 16 heads 2566 / 2825.
+    // Four wavefronts per row and head while one each would not give every SIMD of the chip one.  Forward pass of two layers at contexts of 128, 700 and
+    // 3000, one / four, us: 128 rows x 8 heads 173 / 171, 291 / 254, 925 / 592; 192 x 8 213 / 220, 375 / 355, 1016 / 844; 256 x 8 242 / 261, 428 / 437,
+    // 1128 / 1085; 256 x 16 at 128 and 700 527 / 566, 870 / 896.  (The contexts are not known here.)
     const bool split_attention = quads && ((uintptr_t)view.pool & 15) == 0 && (int64_t)M * Hq <= 1024;
     F32Fused f;
     f.eps = d.rms_eps;

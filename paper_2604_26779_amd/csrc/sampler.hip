@@ -55,7 +55,7 @@ __device__ inline void part_groups(int V, int part, int* g0, int* g1)
 // ulps was noise; in fp64 the choice differs from an fp64 reference's only where its own keys agree to 15 digits.
 //
 // What keeps that cheap (both kernels should be bound by reading the logits):
-//   * the sums need an fp64 exponential per entry: exp_sum below, 17 fp64 instructions, no branch, no special cases;
+//   * the sums need an fp64 exponential per entry: exp_sum below, 15 fp64 instructions, no branch, no special cases;
 //   * a race needs its keys in fp64 only where they can win: every entry's key is first bounded in fp32 from above and
 //     below, and the entries whose upper bound reaches the best lower bound known to the wavefront are then evaluated in fp64.
 //     Those are few unless the weights cancel: a residual that is rounding noise everywhere (q = p) leaves every entry.
@@ -187,7 +187,7 @@ __device__ inline double2 row_stat(const double2* __restrict__ stats, int64_t ro
 // at a time (for vocabularies of up to 131072 all of them), takes the maximum of what is in registers as the reference (moving it, and what has been
 // summed, when a later round exceeds it), so there is no second pass over the logits and no barrier before the sums; the wavefronts' pairs are
 // merged in a fixed order.
-// Bound by its vector instructions (22 per entry, 17 of them fp64 at the fp32 rate) with the reads beside them; 384 rows of 128256 take 47 us = 4.2 TB/s, 1024 rows
+// Bound by its vector instructions (21 per entry, 19 of them fp64 at the fp32 rate: 15 of the exponential, the conversion, difference, scaling and sum) with the reads beside them; 384 rows of 128256 take 47 us = 4.2 TB/s, 1024 rows
 // 118 (55 and 140 on the same boxes with a Taylor series of one term more, two rounds a wavefront and a serial merge; 122 and 355 as two passes with the library's exponential).
 // (zero_rows != null: the workgroup also clears its eighth of row blockIdx.x of that array, zero_width entries wide - the
 // q rows a mapped draft draw then fills at scattered positions; counters != null: the sequences' arrival counters of the
