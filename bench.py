@@ -400,6 +400,7 @@ def main():
     gemm_flops = alg["gemm_flops"]                              # 2 flop per weight an input row meets, per position
     classes = {
         "gemm_bf16_kernel": dict(ms=gemm_ms, raw_ms=gemm_ms_raw, launches=gemm_launches, bytes=alg["gemm"], flops=gemm_flops),
+        # (the class also holds the sums of the QKV projection's slices, the rotation and the cache write; its bytes are the cached keys and values alone)
         "attn_partial_kernel": dict(ms=net["attn"], raw_ms=per_step["attn"], launches=launches["attn"], bytes=alg["attn"], flops=0.0),
     }
     dom = max(classes, key=lambda n: classes[n]["ms"])

@@ -16,6 +16,7 @@ int tune(const char* name);
 // per-kernel-class timing with HIP events (spec_profile_begin / spec_profile_end); prof_mark(c, s)
 // is called after the launches of class c and costs one branch when profiling is off
 enum ProfClass {
+    // PC_ATTN holds the sums of the QKV projection's slices, the rotation and the cache write too
     PC_OTHER = 0, PC_EMBED_NORM, PC_GEMM_QKV, PC_ATTN, PC_ATTN_REDUCE, PC_GEMM_O, PC_RESID_NORM,
     PC_GEMM_GU, PC_SWIGLU, PC_GEMM_DOWN, PC_GEMM_HEAD, PC_SAMPLE_STATS, PC_SAMPLE_DRAW, PC_KV_RESERVE, PC_KV_COMMIT,
     PC_DRAFT_SAMPLE, PC_KV_TRUNCATE, PC_MOE_ROUTE, PC_MOE_GATHER, PC_NGRAM, PC_COUNT
